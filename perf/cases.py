@@ -1,0 +1,211 @@
+"""The work a user has this library do, as cases that can be timed and compared.
+
+Four kinds of program call the library:
+  train   one layer's attention in a training step: forward, then backward (hmar_attn_fwd_masked and
+          hmar_attn_bwd_masked, or hmar_attn_bwd_noalloc where the caller cannot allocate)
+  sample  the attention of one layer while an image batch is generated: one hmar_attn_step_fwd per
+          scale, coarse to fine, each its own call because each scale depends on the one before
+  serve   requests that sit at different scales, batched: all steps in one hmar_attn_steps_fwd call
+  refine  one masked-refinement pass inside a scale: hmar_attn_step_fwd_rows over the rows that are
+          predicted again
+
+A case is a dict of plain values.  `sizes` lists the scales, coarse to fine: side lengths, or token
+counts where `counts` is true.  Inputs are iid N(0, 1) in bf16, as in the library's own workloads.
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+import paper_2506_04421_amd as hm
+
+D = 64                                   # the head dimension the library takes
+SIDES_TINY = "1,2,3,4"
+SIDES_256 = "1,2,3,4,5,6,8,10,13,16"
+SIDES_512 = "1,2,3,4,6,9,13,18,24,32"
+SIDES_LARGE = SIDES_512 + ",48,64"
+
+# No drawn case asks for more than the largest listed one.
+MAX_TRAIN_FLOPS = 1.5e12
+MAX_BYTES = 0.8e9
+
+
+def _train(name, sizes, B, H, causal=False, counts=False, sm_scale=0.0, noalloc=False):
+    return {"name": name, "kind": "train", "sizes": sizes, "counts": counts, "causal": causal, "B": B, "H": H,
+            "sm_scale": sm_scale, "noalloc": noalloc}
+
+
+def listed():
+    return [
+        # a unit test or a debugging run: a handful of tokens, launches and host work are all there is
+        _train("tiny_train", SIDES_TINY, 2, 2),
+        # fine-tuning or a debugging batch of the 256px schedule, fewer heads than the chip has compute
+        # units; a loop that owns all its buffers
+        _train("256px_train_b2_h16", SIDES_256, 2, 16, noalloc=True),
+        # the 256px training shapes: the base model's, and the large model's (the benchmark's headline)
+        _train("256px_train_b16_h16", SIDES_256, 16, 16),
+        _train("256px_train_b32_h24", SIDES_256, 32, 24),
+        # the 512px training shape: scales of up to 1024 tokens, arithmetic dominates
+        _train("512px_train_b8_h24", SIDES_512, 8, 24),
+        # the longest sequence of the benchmark (L = 8640)
+        _train("large_train_b2_h24", SIDES_LARGE, 2, 24),
+        # the same model trained under the block-causal mask, the pattern Markovian attention is compared with
+        _train("256px_causal_train_b16_h16", SIDES_256, 16, 16, causal=True),
+        # token maps of 2:3 photographs (1x1, 1x2, 2x3, 3x5, 4x6, 6x9, 9x13, 13x19): odd counts, odd batch,
+        # a softmax scale of the caller's
+        _train("maps_train_b5_h20", "1,2,6,15,24,54,117,247", 5, 20, counts=True, sm_scale=0.1),
+        # generation: a large batch, throughput; and one image with its unconditional twin, latency
+        {"name": "256px_sample_b64_h24", "kind": "sample", "sizes": SIDES_256, "B": 64, "H": 24},
+        {"name": "256px_sample_b2_h24", "kind": "sample", "sizes": SIDES_256, "B": 2, "H": 24},
+        # continuous batching: groups of requests at all ten scales at once
+        {"name": "256px_serve_b64_h24", "kind": "serve", "sizes": SIDES_256, "B": 64, "H": 24},
+        # re-predicting 3 of 8 tokens of the last 512px scale
+        {"name": "512px_refine_b8_h24", "kind": "refine", "n_prev": 576, "n_cur": 1024, "n_rows": 384, "B": 8, "H": 24},
+    ]
+
+
+def _draw_sides(rng, last_max):
+    """A coarse-to-fine schedule of side lengths 1 < ... < last, growing roughly geometrically."""
+    last = int(round(math.exp(rng.uniform(math.log(4), math.log(last_max)))))
+    k = rng.randint(3, min(12, last))
+    sides = {1, last}
+    for i in range(1, k - 1):
+        s = math.exp(math.log(last) * i / (k - 1) + rng.uniform(-0.15, 0.15))
+        sides.add(min(max(int(round(s)), 1), last))
+    return sorted(sides)
+
+
+def _draw_batch(rng, per_head_bytes, per_head_flops, max_flops):
+    """B and H spread over the logarithm of their range, within what the largest case may ask for."""
+    H = rng.choice((6, 8, 12, 15, 16, 20, 24, 30))
+    most = min(MAX_BYTES / per_head_bytes, max_flops / per_head_flops) / H
+    B = int(math.exp(rng.uniform(0.0, math.log(min(max(most, 1.0), 64.0)))))
+    while H > 1 and H * max(B, 1) * max(per_head_bytes / MAX_BYTES, per_head_flops / max_flops) > 1:
+        H -= 1
+    return max(B, 1), H
+
+
+def draw(rng):
+    kind = rng.choice(("train", "train", "train", "sample", "serve", "refine"))
+    if kind == "train":
+        causal, counts = rng.random() < 0.25, rng.random() < 0.3
+        sides = _draw_sides(rng, 64)
+        if counts:
+            aspect = math.exp(rng.uniform(-0.7, 0.7))
+            sizes = [max(1, round(s * aspect)) * s for s in sides]
+        else:
+            sizes = sides
+        case = {"kind": kind, "sizes": ",".join(map(str, sizes)), "counts": counts, "causal": causal, "B": 1, "H": 1,
+                "sm_scale": rng.choice((0.0, 0.0, 0.1, 0.2)), "noalloc": False}
+        w = work(case)
+        case["B"], case["H"] = _draw_batch(rng, w["bytes"], w["flops"], MAX_TRAIN_FLOPS)
+        L = sum(_counts(case))
+        case["noalloc"] = not causal and not counts and L <= 8192 and case["B"] * case["H"] * L <= 1 << 20 and rng.random() < 0.3
+        return case
+    if kind == "refine":
+        side = int(round(math.exp(rng.uniform(math.log(4), math.log(48)))))
+        n_cur = side * side
+        case = {"kind": kind, "n_prev": int(round(side * rng.uniform(0.6, 0.85))) ** 2, "n_cur": n_cur,
+                "n_rows": rng.randint(1, n_cur), "B": 1, "H": 1}
+    else:
+        case = {"kind": kind, "sizes": ",".join(map(str, _draw_sides(rng, 40))), "B": 1, "H": 1}
+    w = work(case)
+    case["B"], case["H"] = _draw_batch(rng, w["bytes"], w["flops"], MAX_TRAIN_FLOPS)
+    return case
+
+
+def _sizes(case):
+    return tuple(int(s) for s in case["sizes"].split(","))
+
+
+def _counts(case):
+    return [n if case.get("counts") else n * n for n in _sizes(case)]
+
+
+def _steps(case):
+    """(n_prev, n_cur) of every step of a schedule."""
+    n = _counts(case)
+    return [(n[i - 1] if i else 0, n[i]) for i in range(len(n))]
+
+
+def prepare(case, seed):
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(seed)
+    B, H = case["B"], case["H"]
+
+    def rnd(n):
+        return torch.randn((B, H, n, D), device=dev, generator=g).to(torch.bfloat16)
+
+    s = {"case": case}
+    if case["kind"] == "train":
+        L = sum(_counts(case))
+        s["sizes"] = _sizes(case)
+        s["mask"] = (hm.HMAR_MASK_BLOCK_CAUSAL if case["causal"] else hm.HMAR_MASK_MARKOV) | (
+            hm.HMAR_SCALE_COUNTS if case["counts"] else 0)
+        s["qkv"], s["dO"] = [rnd(L) for _ in range(3)], rnd(L)
+        if case["noalloc"]:              # a loop that owns its buffers
+            s["out"] = [torch.empty_like(s["dO"]) for _ in range(4)]
+            s["lse"] = torch.empty((B, H, L), dtype=torch.float32, device=dev)
+    elif case["kind"] == "refine":
+        n_prev, n_cur = case["n_prev"], case["n_cur"]
+        s["q"], s["k"], s["v"] = rnd(n_cur), rnd(n_prev + n_cur), rnd(n_prev + n_cur)
+        s["rows"] = torch.randperm(n_cur, device=dev, generator=g)[:case["n_rows"]].sort().values.to(torch.int32)
+        # what the pass before left for the rows that stay
+        s["o"] = rnd(n_cur)
+        s["lse"] = torch.randn((B, H, n_cur), device=dev, generator=g)
+    else:
+        s["n_prev"] = [p for p, _ in _steps(case)]
+        s["q"] = [rnd(c) for _, c in _steps(case)]
+        s["k"] = [rnd(p + c) for p, c in _steps(case)]
+        s["v"] = [rnd(p + c) for p, c in _steps(case)]
+    return s
+
+
+def run(s):
+    case = s["case"]
+    if case["kind"] == "train":
+        q, k, v = s["qkv"]
+        if case["noalloc"]:
+            O, dQ, dK, dV = s["out"]
+            O, LSE = hm.hmar_attn_fwd(q, k, v, s["sizes"], case["sm_scale"], O=O, LSE=s["lse"])
+            grads = hm.hmar_attn_bwd_noalloc(q, k, v, O, s["dO"], LSE, s["sizes"], dQ, dK, dV, case["sm_scale"])
+        else:
+            O, LSE = hm.hmar_attn_fwd_masked(q, k, v, s["sizes"], s["mask"], case["sm_scale"])
+            grads = hm.hmar_attn_bwd_masked(q, k, v, O, s["dO"], LSE, s["sizes"], s["mask"], case["sm_scale"])
+        return (O, LSE) + tuple(grads)
+    if case["kind"] == "sample":
+        return [hm.hmar_attn_step_fwd(q, k, v, p) for q, k, v, p in zip(s["q"], s["k"], s["v"], s["n_prev"])]
+    if case["kind"] == "serve":
+        return hm.hmar_attn_steps_fwd(s["q"], s["k"], s["v"], s["n_prev"])
+    return hm.hmar_attn_step_fwd_rows(s["q"], s["k"], s["v"], case["n_prev"], s["rows"], s["o"], s["lse"])
+
+
+def work(case):
+    """Every input of a call read once, every output written once; element-exact flops of the unmasked
+    pairs.  A training pass is two calls, and the second cannot begin before the whole of the first is done
+    and its operands have left the chip: what both read counts in both."""
+    heads = case["B"] * case["H"]
+    row = 2 * D
+    if case["kind"] == "train":
+        n = _counts(case)
+        seen = 0
+        pairs = 0
+        for i, c in enumerate(n):
+            seen += c
+            pairs += c * (seen if case["causal"] else c + (n[i - 1] if i else 0))
+        # forward: Q K V -> O LSE; backward: Q K V O dO LSE -> dQ dK dV
+        return {"bytes": heads * seen * (12 * row + 8), "flops": heads * 14 * D * pairs}
+    if case["kind"] == "refine":
+        keys, rows = case["n_prev"] + case["n_cur"], case["n_rows"]
+        return {"bytes": heads * (rows * (2 * row + 4) + 2 * keys * row) + 4 * rows, "flops": heads * 4 * D * rows * keys}
+    return {"bytes": heads * sum(c * (2 * row + 4) + 2 * (p + c) * row for p, c in _steps(case)),
+            "flops": heads * sum(4 * D * c * (p + c) for p, c in _steps(case))}
+
+
+def tolerance(case):
+    """bf16 results.  Against the same attention in float64 on sampled heads of these cases the relative
+    2-norm error is up to 2.4e-3 (outputs) and 2.9e-3 (gradients), the largest error 0.059 of the root
+    mean square: the roundings of the result, of the probabilities and of dS.  About four times that."""
+    return {"rel": 1.0e-2, "max": 0.25}
