@@ -209,3 +209,60 @@ def tolerance(case):
     2-norm error is up to 2.4e-3 (outputs) and 2.9e-3 (gradients), the largest error 0.059 of the root
     mean square: the roundings of the result, of the probabilities and of dS.  About four times that."""
     return {"rel": 1.0e-2, "max": 0.25}
+
+
+def _attend64(q, k, v, sm):
+    """(O, LSE, P) of dense softmax attention; float64, heads in front."""
+    s = (q @ k.transpose(-1, -2).contiguous()) * sm
+    lse = torch.logsumexp(s, dim=-1)
+    p = torch.exp(s - lse.unsqueeze(-1))
+    return p @ v, lse, p
+
+
+def _heads64(t):
+    return t.reshape((-1,) + tuple(t.shape[2:])).double()
+
+
+def _head_chunks(n_heads, pairs):
+    """Chunks of heads whose score matrices stay within 1 GB."""
+    step = max(1, (1 << 27) // max(1, pairs))
+    return [slice(i, min(i + step, n_heads)) for i in range(0, n_heads, step)]
+
+
+def exact(case, seed):
+    """What `run` returns for these inputs, in float64: dense attention over each scale's key window."""
+    s = prepare(case, seed)
+    sm = case.get("sm_scale") or 1.0 / math.sqrt(D)
+    if case["kind"] == "train":
+        q, k, v, g = (_heads64(t) for t in s["qkv"] + [s["dO"]])
+        O, dQ, dK, dV = (torch.zeros_like(q) for _ in range(4))
+        lse = torch.zeros(q.shape[:2], dtype=torch.float64, device=q.device)
+        end, start = 0, 0
+        for n in _counts(case):
+            key0 = 0 if case["causal"] else start
+            start, end = end, end + n
+            rows, keys = slice(start, end), slice(key0, end)
+            for h in _head_chunks(q.shape[0], n * (end - key0)):
+                qh, kh, gh = q[h, rows], k[h, keys], g[h, rows]
+                o, l, p = _attend64(qh, kh, v[h, keys], sm)
+                O[h, rows], lse[h, rows] = o, l
+                ds = p * (gh @ v[h, keys].transpose(-1, -2).contiguous() - (gh * o).sum(-1, keepdim=True)) * sm
+                dQ[h, rows] = ds @ kh
+                dK[h, keys] += ds.transpose(-1, -2).contiguous() @ qh
+                dV[h, keys] += p.transpose(-1, -2).contiguous() @ gh
+        shape = s["dO"].shape
+        return (O.reshape(shape), lse.reshape(shape[:3])) + tuple(t.reshape(shape) for t in (dQ, dK, dV))
+
+    def step(Q, K, V):
+        parts = [_attend64(_heads64(Q)[h], _heads64(K)[h], _heads64(V)[h], sm)[:2]
+                 for h in _head_chunks(Q.shape[0] * Q.shape[1], Q.shape[2] * K.shape[2])]
+        return (torch.cat([o for o, _ in parts]).reshape(Q.shape), torch.cat([l for _, l in parts]).reshape(Q.shape[:3]))
+
+    if case["kind"] == "refine":
+        rows = s["rows"].long()
+        o, l = step(s["q"][:, :, rows].contiguous(), s["k"], s["v"])
+        O, LSE = s["o"].double(), s["lse"].double()
+        O[:, :, rows], LSE[:, :, rows] = o, l
+        return O, LSE
+    outs = [step(*t) for t in zip(s["q"], s["k"], s["v"])]
+    return outs if case["kind"] == "sample" else ([o for o, _ in outs], [l for _, l in outs])
