@@ -4,6 +4,10 @@ Every step of the path (tile schedule, forward, backward) runs inside the librar
 module turns torch tensors into device pointers and a stream handle, checks dtypes and
 shapes, and raises on a non-zero status.  There is no fallback: if the library has not
 been built, importing the entry points fails with an error that says how to build it.
+
+A plainly valid call of the entry points goes through the native module _launch, which does the same
+checks, allocations and library call in a fraction of the host time; whatever it does not accept
+(it returns None) takes the Python code below it, which decides and words the errors.  Measured per
 """
 from __future__ import annotations
 
@@ -18,6 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libhmar_attn.so")
 
 HMAR_OK = 0
 _lib = None
+_launch = None      # the native module, bound to the library's functions
 
 
 class HmarError(RuntimeError):
@@ -25,8 +30,8 @@ class HmarError(RuntimeError):
 
 
 def load_library() -> ctypes.CDLL:
-    """dlopen the in-tree library (once) and declare the C signatures."""
-    global _lib
+    """dlopen the in-tree library (once), declare the C signatures and bind the native call path."""
+    global _lib, _launch
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -70,6 +75,15 @@ def load_library() -> ctypes.CDLL:
     lib.hmar_profile_end.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
     lib.hmar_calibration_copy.restype = ctypes.c_int
     lib.hmar_calibration_copy.argtypes = [vp, vp, sz, vp]
+    try:
+        from . import _launch as launch
+    except ImportError as e:
+        raise HmarError(f"the native call path of the binding is missing or does not load ({e}): build it with "
+                        "`python -m paper_2506_04421_amd.build`") from e
+    launch.bind(*[ctypes.cast(f, vp).value for f in
+                  (lib.hmar_attn_fwd_masked, lib.hmar_attn_bwd_masked, lib.hmar_attn_bwd_noalloc,
+                   lib.hmar_attn_bwd_workspace_bytes_masked, lib.hmar_attn_steps_fwd, lib.hmar_attn_step_fwd_rows)])
+    _launch = launch
     _lib = lib
     return lib
 
@@ -84,18 +98,39 @@ def _check(code: int, what: str) -> None:
 
 
 _SIDES_CACHE = {}
+_SIDES_NATIVE = {}      # the same entries as the native path takes them; the arrays live in _SIDES_CACHE
 
 
 def _sides_array(side_lens: Sequence[int], counts: bool = False):
     """(ctypes int32 array, count, L) of a schedule given as side lengths (or, with `counts`, as
-    token counts per scale); cached, the hot path calls this per launch."""
+    token counts per scale); cached."""
     key = (tuple(side_lens), bool(counts))
     hit = _SIDES_CACHE.get(key)
     if hit is None:
         sides = [int(s) for s in key[0]]
         hit = ((ctypes.c_int32 * len(sides))(*sides), len(sides), sum(s if counts else s * s for s in sides))
         _SIDES_CACHE[key] = hit
+        _SIDES_NATIVE[key] = (ctypes.addressof(hit[0]),) + hit[1:]
     return hit
+
+
+def _known_sides(side_lens, mask_kind):
+    """(address, count, L) of a schedule that _sides_array has seen, or None."""
+    if type(side_lens) is not tuple:
+        if type(side_lens) is not list:
+            return None
+        side_lens = tuple(side_lens)
+    try:
+        return _SIDES_NATIVE.get((side_lens, mask_kind & HMAR_SCALE_COUNTS != 0))
+    except TypeError:            # an unhashable entry, or a mask kind that is no integer
+        return None
+
+
+def _done(res, what: str):
+    """The outputs of a native call, or the error its status stands for."""
+    if type(res) is int:
+        _check(res, what)
+    return res
 
 
 def _bf16_4d(name: str, t: torch.Tensor, shape=None, device=None):
@@ -179,6 +214,11 @@ def hmar_attn_fwd_masked(Q, K, V, side_lens, mask_kind: int, sm_scale: float = 0
     """Forward under the Markovian (0) or block-causal (1) mask; OR HMAR_SCALE_COUNTS into mask_kind
     to give token counts per scale instead of side lengths.  Returns (O bf16, LSE fp32)."""
     lib = load_library()
+    known = _known_sides(side_lens, mask_kind)
+    if known is not None:
+        res = _launch.fwd(Q, K, V, O, LSE, *known, mask_kind, sm_scale)
+        if res is not None:
+            return _done(res, "hmar_attn_fwd_masked")
     _bf16_4d("Q", Q)
     B, H, L, D = Q.shape
     _bf16_4d("K", K, Q.shape, Q.device)
@@ -216,6 +256,9 @@ def _step_tensors(Q, K, V, n_prev, O, LSE):
 def hmar_attn_step_fwd(Q, K, V, n_prev: int, sm_scale: float = 0.0, O=None, LSE=None):
     """One inference step: Q [B,H,n_cur,D] against K, V [B,H,n_prev+n_cur,D].  Returns (O, LSE)."""
     lib = load_library()
+    res = _launch.step(Q, K, V, n_prev, O, LSE, sm_scale)
+    if res is not None:
+        return _done(res, "hmar_attn_step_fwd")
     O, LSE = _step_tensors(Q, K, V, n_prev, O, LSE)
     B, H, n_cur, D = Q.shape
     with _on_device(Q.device):
@@ -229,6 +272,9 @@ def hmar_attn_steps_fwd(Qs, Ks, Vs, n_prevs, sm_scale: float = 0.0, Os=None, LSE
     """Several independent inference steps in one call (see hmar_attn_step_fwd for one step's
     tensors).  Qs, Ks, Vs, n_prevs: equally long sequences.  Returns (list of O, list of LSE)."""
     lib = load_library()
+    res = _launch.steps(Qs, Ks, Vs, n_prevs, Os, LSEs, sm_scale)
+    if res is not None:
+        return _done(res, "hmar_attn_steps_fwd")
     n = len(Qs)
     if n < 1 or not (len(Ks) == len(Vs) == len(n_prevs) == n):
         raise HmarError("hmar_attn_steps_fwd needs equally long, non-empty lists")
@@ -255,6 +301,9 @@ def hmar_attn_step_fwd_rows(Q, K, V, n_prev: int, rows: torch.Tensor, O, LSE, sm
     """One refinement pass inside a scale: only the query rows listed in `rows` (device int32,
     distinct values in [0, n_cur)) are computed; the other rows of O and LSE stay as they are."""
     lib = load_library()
+    res = _launch.rows(Q, K, V, n_prev, rows, O, LSE, sm_scale)
+    if res is not None:
+        return _done(res, "hmar_attn_step_fwd_rows")
     O, LSE = _step_tensors(Q, K, V, n_prev, O, LSE)
     B, H, n_cur, D = Q.shape
     if (not isinstance(rows, torch.Tensor) or not rows.is_cuda or rows.device != Q.device or rows.dtype != torch.int32
@@ -291,6 +340,11 @@ def hmar_attn_bwd_masked(Q, K, V, O, dO, LSE, side_lens, mask_kind: int, sm_scal
     """Backward under the Markovian (0) or block-causal (1) mask (HMAR_SCALE_COUNTS as in the
     forward).  Returns (dQ, dK, dV) bf16."""
     lib = load_library()
+    known = _known_sides(side_lens, mask_kind)
+    if known is not None:
+        res = _launch.bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, *known, mask_kind, sm_scale)
+        if res is not None:
+            return _done(res, "hmar_attn_bwd_masked")
     _bf16_4d("Q", Q)
     B, H, L, D = Q.shape
     for name, t in (("K", K), ("V", V), ("O", O), ("dO", dO)):
@@ -321,6 +375,11 @@ def hmar_attn_bwd_noalloc(Q, K, V, O, dO, LSE, side_lens, dQ, dK, dV, sm_scale: 
     """The backward without a workspace and without any allocation (not even of outputs: the
     caller passes dQ, dK, dV).  Markovian mask.  Returns (dQ, dK, dV)."""
     lib = load_library()
+    known = _known_sides(side_lens, 0)
+    if known is not None:
+        res = _launch.bwd_noalloc(Q, K, V, O, dO, LSE, dQ, dK, dV, *known, sm_scale)
+        if res is not None:
+            return _done(res, "hmar_attn_bwd_noalloc")
     _bf16_4d("Q", Q)
     B, H, L, D = Q.shape
     for name, t in (("K", K), ("V", V), ("O", O), ("dO", dO), ("dQ", dQ), ("dK", dK), ("dV", dV)):

@@ -1,15 +1,18 @@
-"""Builds libhmar_attn.so (HIP kernels + C ABI) in-tree with hipcc for gfx950."""
+"""Builds libhmar_attn.so (HIP kernels + C ABI, hipcc for gfx950) and _launch.so (the binding's native call
+path, host code only) in-tree."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libhmar_attn.so")
+LAUNCH_PATH = os.path.join(HERE, "_launch.so")
 
 SOURCES = ["api.cpp", "schedule.cpp", "fwd.hip", "bwd.hip", "no_alloc.hip"]
 
@@ -29,21 +32,41 @@ def variant_path(name: str) -> str:
     return os.path.join(HERE, f"libhmar_attn_{name}.so")
 
 
+def _launch_command(out: str) -> list:
+    """g++ command of the Python module _launch: host code against torch's C++ interface, no device code."""
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
+    return [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+            "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"), "-I", os.path.join(rocm, "include"),
+            "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "py_launch.cpp"),
+            "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python", "-lc10_hip", "-o", out]
+
+
 def build_library(verbose: bool = False, variant: str = "", defines=()) -> str:
-    """Compile every source and link the shared library.  Always recompiles.
-    With `variant`, builds libhmar_attn_<variant>.so with the given -D knobs (see the list at the
-    top of csrc/device_common.h) next to the library instead: for measurements only."""
+    """Compile every source: the shared library and, beside it, the binding's _launch module.  Always
+    recompiles.  With `variant`, builds libhmar_attn_<variant>.so alone with the given -D knobs (see the
+    list at the top of csrc/device_common.h) next to the library instead: for measurements only."""
     out = variant_path(variant) if variant else LIB_PATH
-    cmd = [hipcc_path(), "-O3", "-std=c++17", "-fPIC", "-shared", "-x", "hip", *DEVICE_FLAGS,
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC, *[f"-D{d}" for d in defines],
-           *[os.path.join(CSRC, s) for s in SOURCES], "-o", out + ".tmp"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError(f"hipcc failed building {os.path.basename(out)}")
-    os.replace(out + ".tmp", out)
+    jobs = [(out, [hipcc_path(), "-O3", "-std=c++17", "-fPIC", "-shared", "-x", "hip", *DEVICE_FLAGS,
+                   "-I", os.path.join(ROOT, "include"), "-I", CSRC, *[f"-D{d}" for d in defines],
+                   *[os.path.join(CSRC, s) for s in SOURCES], "-o", out + ".tmp"])]
+    if not variant:
+        jobs.append((LAUNCH_PATH, _launch_command(LAUNCH_PATH + ".tmp")))
+    procs = []
+    for target, cmd in jobs:
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append((target, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    results = [(target, proc.communicate()[0], proc.returncode) for target, proc in procs]
+    for target, log, code in results:
+        if code != 0:
+            sys.stderr.write(log)
+            raise RuntimeError(f"the compiler failed building {os.path.basename(target)}")
+    for target, _, _ in results:
+        os.replace(target + ".tmp", target)
     return out
 
 
