@@ -54,11 +54,14 @@ struct StepParams {
     float c;
 };
 
-// The running reference maximum of a row is only raised when a tile exceeds it by more
-// than this many binades; until then probabilities are at most 2^8, which fp32 sums and
-// bf16 operands hold without loss.  The final division by the row sum makes the result
-// independent of the reference.
-constexpr float kRescaleThreshold = 8.0f;
+// Softmax reference.  A row's reference maximum is taken from the tile in which its keys begin; the
+// tiles after it are exponentiated against that reference at once, and only if a lane's sum over a
+// tile comes out above this bound are the tile's scores formed again, their maximum taken and the
+// reference raised to it.  So every probability that is used is at most 2^8, which fp32 sums and bf16
+// operands hold without loss (the final division by the row sum makes the result independent of
+// the reference), and the 24 maximum instructions of a 64 x 32 tile step (of 140 vector
+// instructions: the loop is bound by instruction issue) leave the common path.
+constexpr float kMaxTileSum = 256.0f;
 
 #ifndef HMAR_FWD_MIN_WAVES
 #define HMAR_FWD_MIN_WAVES 4
@@ -285,26 +288,33 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
             const uint32_t Kt = smem_base + ST * (2 * kTileBytes);
             const uint32_t Vt = Kt + kTileBytes;
             f32x16 s[2];
+            auto scores = [&]() {
+                // opaque to the compiler: the two uses below share no operand and no comparison (kept live
+                // from one to the other they would not fit the registers)
+                asm volatile("" ::: "memory");
+                int lim_lo = lo - kt - 4 * h, lim_hi = hi - kt - 4 * h;
+                asm volatile("" : "+v"(lim_lo), "+v"(lim_hi));
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
+                for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+                    for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    s[kb] = mfma32(lds_a_row(Kt, lo_, kb, t), q[t], s[kb]);
-            }
-            // element i of block kb is key kt + 4h + 32kb + 8(i/4) + i%4; allowed iff lo <= key < hi
+                    for (int t = 0; t < 4; ++t)
+                        s[kb] = mfma32(lds_a_row(Kt, lo_, kb, t), q[t], s[kb]);
+                }
+                // element i of block kb is key kt + 4h + 32kb + 8(i/4) + i%4; allowed iff lo <= key < hi
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-                mask_block(s[kb], 32 * kb, lo - kt - 4 * h, hi - kt - 4 * h, kt < full_lo, kt + kTile > full_hi);
-            float mt = s[0][0];
+                for (int kb = 0; kb < 2; ++kb)
+                    mask_block(s[kb], 32 * kb, lim_lo, lim_hi, kt < full_lo, kt + kTile > full_hi);
+            };
+            // the reference becomes the largest score so far; what was accumulated follows it
+            auto raise_reference = [&]() {
+                float mt = s[0][0];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) mt = fmaxf(mt, s[kb][i]);
-            mt = half_max(mt) * p.c;
-            if (__builtin_amdgcn_ballot_w64(mt > m_ref + kRescaleThreshold) != 0) {
-                const float m_new = fmaxf(m_ref, mt);
+                    for (int i = 0; i < 16; ++i) mt = fmaxf(mt, s[kb][i]);
+                const float m_new = fmaxf(m_ref, half_max(mt) * p.c);
                 if (!o_empty) {
                     const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
                     lsum *= alpha;
@@ -314,17 +324,33 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                         for (int i = 0; i < 16; ++i) o[mb][i] *= alpha;
                 }
                 m_ref = m_new;
+            };
+            // scores become probabilities; returns the lane's sum of them
+            auto exponentials = [&]() {
+                const float neg_m = -m_ref;
+                float sum = 0.f;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], p.c, neg_m));
+                        sum += pv;
+                        s[kb][i] = pv;
+                    }
+                return sum;
+            };
+            float tsum;
+            bool raise = kt <= full_lo;                 // rows may begin in this tile: they have no reference yet
+#pragma nounroll
+            while (true) {                              // at most twice
+                scores();
+                if (raise) raise_reference();
+                tsum = exponentials();
+                if (raise || __builtin_amdgcn_ballot_w64(tsum > kMaxTileSum) == 0) break;
+                raise = true;
             }
+            lsum += tsum;
             o_empty = false;
-            const float neg_m = -m_ref;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], p.c, neg_m));
-                    lsum += pv;
-                    s[kb][i] = pv;
-                }
 #pragma unroll
             for (int tp = 0; tp < 4; ++tp) {
                 const int kb = tp >> 1, e0 = 8 * (tp & 1);
