@@ -434,24 +434,24 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
         p.row_hi = s.row_hi[dir];
         p.n_items = s.n_items[dir];
         p.tail_groups = tail_groups_for(s.num_cus, s.n_items[dir]);
-        const long long groups = 8LL * ((n_heads + 7) / 8) * s.n_items[dir];
-        if (groups <= 0 || groups > 0x7fffffffLL) return hipErrorInvalidValue;
+        const unsigned groups = launch_groups(s.n_items[dir], n_heads);
+        if (groups == 0) return hipErrorInvalidValue;
         const int kid = dir == 1 ? kKernelDkDv : kKernelDq;
         profile_before(kid, stream);
 #if HMAR_DKDV_KEYS_PER_WAVE == 16
-        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv16_kernel, dim3((unsigned)groups), dim3(kThreads16), 0, stream, p);
+        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv16_kernel, dim3(groups), dim3(kThreads16), 0, stream, p);
 #elif defined(HMAR_DKDV_PIPE)
-        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv_pipe_kernel, dim3((unsigned)groups), dim3(kThreads), 0, stream, p);
+        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv_pipe_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #elif defined(HMAR_DKDV_PERSIST)
         if (dir == 1) {
             const long long resident = 2LL * s.num_cus / 8 * 8;       // two workgroups per CU, a multiple of 8
-            hipLaunchKernelGGL(hmar_dkdv_persist_kernel, dim3((unsigned)std::min(groups, resident)), dim3(kThreads), 0, stream,
+            hipLaunchKernelGGL(hmar_dkdv_persist_kernel, dim3((unsigned)std::min((long long)groups, resident)), dim3(kThreads), 0, stream,
                                p, (int)groups);
         }
 #else
-        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv_kernel, dim3((unsigned)groups), dim3(kThreads), 0, stream, p);
+        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
-        else          hipLaunchKernelGGL(hmar_dq_kernel, dim3((unsigned)groups), dim3(kThreads), 0, stream, p);
+        else          hipLaunchKernelGGL(hmar_dq_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
         const hipError_t e = hipGetLastError();
         profile_after(kid, stream);
         if (e != hipSuccess) return e;

@@ -117,23 +117,41 @@ typedef const __attribute__((address_space(1))) void global_void;
 //    heaviest items, then the next, ...): the launch then ends on the lightest items, and the
 //    period in which the device drains is as short as those.  The batch is sized to about one
 //    round of resident workgroups, small enough for its heads' K and V to share the L2.
+//  - The n_heads % 8 heads that fill no group are walked with that batch, their items dealt out to
+//    all XCDs: unit u = item * rest + head goes to XCD u % 8, behind the batch's units of that item.
+//    Their rows are fetched by several L2s, but no XCD works on a head while others have none:
+//    12 heads of the 8640-token schedule take 140 / 182 / 241 us (forward / dQ / dK,dV), with one XCD
+//    for each of the last four heads 159 / 214 / 278; one head 100 / 107 / 111 against 101 / 118 / 127; at
+//    2240 tokens and below, where launches are short, +-2 %.
 //  - With `reverse` the groups are walked from the last to the first: a kernel that follows
 //    another one over the same tensors then starts on the heads that kernel touched last,
 //    which are the ones still in the last-level cache.
+// The launch holds launch_groups(n_items, n_heads) workgroups (csrc/kernels.h); false: no work.
 __device__ __forceinline__ bool map_unit(int wg, int n_items, int n_heads, int tail_groups, int* head, int* item,
                                          bool reverse = false) {
-    const int xcd = wg & 7;
-    const int slot = wg >> 3;
-    const int n_groups = (n_heads + 7) / 8;
+    const int xcd = wg & 7, slot = wg >> 3;
+    const int n_groups = n_heads >> 3, rest = n_heads & 7;
     const int tail = min(max(tail_groups, 1), n_groups);
     const int head_major = (n_groups - tail) * n_items;       // slots before the tail batch
-    int group, it;
-    if (slot < head_major) { group = slot / n_items; it = slot % n_items; }
-    else { const int s2 = slot - head_major; it = s2 / tail; group = n_groups - tail + s2 % tail; }
-    if (reverse) group = n_groups - 1 - group;
-    *head = group * 8 + xcd;
+    int group = -1, it;
+    if (slot < head_major) {
+        group = slot / n_items;
+        it = slot % n_items;
+    } else {
+        const int s2 = slot - head_major;
+        // slots of this XCD before item i of the batch: its groups' and its share of the other heads'
+        auto before = [&](int i) { return i * tail + ((i * rest + 7 - xcd) >> 3); };
+        if (s2 >= before(n_items)) return false;
+        it = min(8 * s2 / (8 * tail + rest), n_items - 1);
+        while (before(it) > s2) --it;
+        while (before(it + 1) <= s2) ++it;
+        const int at = s2 - before(it);
+        if (at < tail) group = n_groups - tail + at;
+        else *head = 8 * n_groups + ((xcd - it * rest) & 7);
+    }
     *item = it;
-    return *head < n_heads;
+    if (group >= 0) *head = (reverse ? n_groups - 1 - group : group) * 8 + xcd;
+    return true;
 }
 __device__ __forceinline__ bool map_workgroup(int n_items, int n_heads, int tail_groups, int* head, int* item,
                                               bool reverse = false) {

@@ -438,14 +438,14 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     p.L = s.L;
     p.Lk = s.Lk;
     p.c = sm_scale * kLog2e;
-    const long long groups = 8LL * ((n_heads + 7) / 8) * s.n_items[0];
-    if (groups <= 0 || groups > 0x7fffffffLL) return hipErrorInvalidValue;
+    const unsigned groups = launch_groups(s.n_items[0], n_heads);
+    if (groups == 0) return hipErrorInvalidValue;
     profile_before(kKernelFwd, stream);
 #ifdef HMAR_TUNE_FWD_STUDY
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
-                       dim3((unsigned)groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
+                       dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
-    hipLaunchKernelGGL(hmar_fwd_kernel, dim3((unsigned)groups), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL(hmar_fwd_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
     const hipError_t e = hipGetLastError();
     profile_after(kKernelFwd, stream);
@@ -491,10 +491,10 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     p.n_heads = n_heads;
     p.tail_groups = tail_groups_for(num_cus, items);
     p.c = sm_scale * kLog2e;
-    const long long groups = 8LL * ((n_heads + 7) / 8) * items;
-    if (groups <= 0 || groups > 0x7fffffffLL) return hipErrorInvalidValue;
+    const unsigned groups = launch_groups(items, n_heads);
+    if (groups == 0) return hipErrorInvalidValue;
     profile_before(kKernelFwd, stream);
-    hipLaunchKernelGGL(hmar_fwd_steps_kernel, dim3((unsigned)groups), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL(hmar_fwd_steps_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
     const hipError_t e = hipGetLastError();
     profile_after(kKernelFwd, stream);
     return e;

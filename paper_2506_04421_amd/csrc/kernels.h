@@ -30,6 +30,13 @@ inline int tail_groups_for(int num_cus, int n_items) {
     return g < 1 ? 1 : g;
 }
 
+// Workgroups of a launch over n_items items of each head (see map_unit), or 0 if they would be too many
+// for a grid.
+inline unsigned launch_groups(int n_items, int n_heads) {
+    if (n_items < 1 || n_heads < 1 || 8LL * ((n_heads + 7LL) / 8) * n_items > 0x7fffffffLL) return 0;
+    return 8u * ((unsigned)(n_heads / 8) * (unsigned)n_items + ((unsigned)(n_heads % 8) * (unsigned)n_items + 7) / 8);
+}
+
 // Per-kernel event bracketing for hmar_profile_begin/end (no-ops unless profiling is on).
 enum KernelId { kKernelFwd = 0, kKernelDkDv = 1, kKernelDq = 2, kNumKernels = 3 };
 void profile_before(int kernel_id, hipStream_t stream);

@@ -186,6 +186,22 @@ def test_long_scales_and_head_counts_off_the_xcd_grid(sides, B, H):
     _compare(res, _oracle_heads(Q, K, V, dO, sides, 1.0 / math.sqrt(D), heads), heads, f"{sides} B{B} H{H}")
 
 
+@pytest.mark.parametrize("sides,H,heads", [
+    ((2, 7, 12, 15), 1, (0,)), ((2, 7, 12, 15), 3, (0, 1, 2)), ((2, 7, 12, 15), 7, (0, 3, 6)),
+    ((2, 7, 12, 15), 9, (0, 7, 8)), ((2, 7, 12, 15), 12, (7, 8, 11)), ((2, 7, 12, 15), 23, (15, 16, 22)),
+    (si.WORKLOADS["512px_b8_h24"].sides, 107, (0, 8, 103, 104, 106))])
+def test_heads_that_fill_no_group_of_eight(sides, H, heads):
+    # their work items are dealt out to all XCDs at the end of the launch; every output starts as
+    # NaN and must be finite, so an item that no workgroup took shows whichever head it is of
+    L = sum(s * s for s in sides)
+    Q, K, V, dO = si.draw((1, H, L, 64), seed=1300 + H, n_tensors=4)
+    res = _gpu_run(Q, K, V, dO, sides, 0.125)
+    heads = [(0, h) for h in heads]
+    ref = _oracle_heads(Q, K, V, dO, sides, 0.125, heads)
+    bounds = _operand_rounding_bounds(Q, K, V, dO, sides, 0.125, heads, ref)      # see the full-size test
+    _compare(res, ref, heads, "heads off the XCD grid", grad_bounds={t: np.maximum(x, TOL_ABS) for t, x in bounds.items()})
+
+
 @pytest.mark.parametrize("name", ["256px_b16_h16", "256px_b32_h24", "256px_b32_h30", "512px_b8_h24"])
 def test_full_size_workloads_every_head(name):
     # Full problem size in the launch configuration the benchmark times; every (b, h) slice is
