@@ -81,6 +81,9 @@ void pack_tables(const Schedule& s, unsigned char* staging, unsigned char* base,
         std::memcpy(staging + o, s.items[d].data(), bytes);
         dev->items[d] = base + o;
         dev->n_items[d] = (int32_t)s.items[d].size();
+        dev->max_tiles[d] = 0;
+        for (const TileItem& it : s.items[d])
+            dev->max_tiles[d] = std::max(dev->max_tiles[d], (it.other_end - it.other_begin + 63) / 64);
         o += bytes;
     }
     for (int d = 0; d < 2; ++d) {

@@ -202,6 +202,55 @@ def test_heads_that_fill_no_group_of_eight(sides, H, heads):
     _compare(res, ref, heads, "heads off the XCD grid", grad_bounds={t: np.maximum(x, TOL_ABS) for t, x in bounds.items()})
 
 
+@pytest.mark.parametrize("sides,H", [((17, 20), 3), ((17, 20), 40), ((17, 20), 60),      # 7 items, 11 tiles each
+                                     ((3, 23, 25), 2), ((3, 23, 25), 24), ((3, 23, 25), 48), ((3, 23, 25), 90),  # 11, 19
+                                     ((39, 41), 5)])                                          # 27, 51
+def test_small_launches_divide_the_streamed_tiles(sides, H):
+    # every form a workgroup can take: the launches hold from a few to two units per compute unit,
+    # with streams of fewer and of more than 16 and 48 tiles, ragged last items and tiles
+    L = sum(s * s for s in sides)
+    Q, K, V, dO = si.draw((1, H, L, 64), seed=1400 + H, n_tensors=4)
+    res = _gpu_run(Q, K, V, dO, sides, 0.125)
+    heads = [(0, h) for h in sorted({0, H // 2, H - 1})]
+    ref = _oracle_heads(Q, K, V, dO, sides, 0.125, heads)
+    bounds = _operand_rounding_bounds(Q, K, V, dO, sides, 0.125, heads, ref)      # see the full-size test
+    _compare(res, ref, heads, "divided tiles", grad_bounds={t: np.maximum(x, TOL_ABS) for t, x in bounds.items()})
+
+
+@pytest.mark.parametrize("n_prev,n_cur,H", [(150, 200, 5), (150, 200, 100), (600, 500, 4), (600, 500, 50), (600, 500, 90)])
+def test_small_steps_divide_the_keys(n_prev, n_cur, H):
+    # the same forms for inference steps, alone, with a step small enough to share the last item, and
+    # over a row list
+    d = _dev()
+    p, c = [n_prev, 3], [n_cur, 9]
+    Qs = [si.draw((1, H, n, 64), seed=1500 + n, n_tensors=1)[0] for n in c]
+    KVs = [si.draw((1, H, m + n, 64), seed=1550 + n, n_tensors=2) for m, n in zip(p, c)]
+    q, k, v = [t.to(d) for t in Qs], [kv[0].to(d) for kv in KVs], [kv[1].to(d) for kv in KVs]
+    Os, LSEs = hm.hmar_attn_steps_fwd(q, k, v, p, Os=[_nan_like(t) for t in q], LSEs=[_nan_stats(t.shape[:3], d) for t in q])
+    one = hm.hmar_attn_step_fwd(q[0], k[0], v[0], n_prev)
+    rows = torch.arange(n_cur - 1, -1, -3, dtype=torch.int32, device=d)
+    O, LSE = torch.full_like(q[0], 7.0), torch.full((1, H, n_cur), -3.0, device=d)
+    hm.hmar_attn_step_fwd_rows(q[0], k[0], v[0], n_prev, rows, O, LSE)
+    torch.cuda.synchronize()
+    for t in list(Os) + list(LSEs):
+        assert torch.isfinite(t.float()).all()
+    heads = [(0, h) for h in sorted({0, H // 2, H - 1})]
+    idx = rows.cpu().numpy()
+    for i in range(2):
+        ref = {"O": [], "LSE": []}
+        for _, h in heads:
+            rO, rL = orc.attn_step_fwd(*[si.to_f64(t[:, h:h + 1]) for t in (Qs[i], KVs[i][0], KVs[i][1])], p[i])
+            ref["O"].append(rO[0, 0]); ref["LSE"].append(rL[0, 0])
+        ref = {n: np.stack(t) for n, t in ref.items()}
+        _compare(dict(O=Os[i], LSE=LSEs[i]), ref, heads, "divided keys")
+        if i == 0:
+            _compare(dict(O=one[0], LSE=one[1]), ref, heads, "divided keys")
+            _compare(dict(O=O[:, :, rows.long()], LSE=LSE[:, :, rows.long()]), {n: t[:, idx] for n, t in ref.items()},
+                     heads, "divided keys, listed rows")
+            keep = np.setdiff1d(np.arange(n_cur), idx)
+            assert (si.to_f64(O)[:, :, keep] == 7.0).all() and (si.to_f64(LSE)[:, :, keep] == -3.0).all()
+
+
 @pytest.mark.parametrize("name", ["256px_b16_h16", "256px_b32_h24", "256px_b32_h30", "512px_b8_h24"])
 def test_full_size_workloads_every_head(name):
     # Full problem size in the launch configuration the benchmark times; every (b, h) slice is
