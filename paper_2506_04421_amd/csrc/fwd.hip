@@ -76,106 +76,123 @@ constexpr float kMaxTileSum = 256.0f;
 constexpr int kFwdStages = HMAR_FWD_STAGES;
 static_assert(kFwdStages >= 2 && kFwdStages <= 4, "ring depth");
 
-// The pack item of a steps launch: inference steps with at most 64 keys.  A wavefront takes the
-// units u = wave, wave + 4, ... and computes each alone, without the workgroup: the unit's 32 query
-// rows and the step's key rows go from global memory straight into registers (both are row-wise
-// operands), the value rows go by DMA into the wavefront's own quarter of the ring (8 KB, one
-// tile), from where the transpose load feeds the second contraction; the same quarter then
-// serves as the patch of the result.  One tile holds all keys, so the softmax is the plain
+// A unit of the small steps (at most 64 keys): one wavefront computes 32 query rows of one head
+// alone, without the workgroup: the rows and the step's key rows go from global memory straight into
+// registers (both are row-wise operands), the value rows go by DMA into the wavefront's own 8 KB of
+// LDS (one tile, at Vt), from where the transpose load feeds the second contraction; the same LDS
+// then serves as the patch of the result.  One tile holds all keys, so the softmax is the plain
 // one: row maximum, exponentials, row sum.  No barrier: nothing is shared between wavefronts.
+__device__ __forceinline__ void small_step_unit(const StepParams& p, int head, int unit, uint32_t Vt, const LaneOffsets& lo_) {
+    const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+    static_assert(kPatchBytes <= kTileBytes, "the result patch reuses the value tile");
+    const StepDesc& sd = p.step[unit >> 1];
+    const int n_q = sd.n_q, Lk = sd.Lk;                 // Lk <= 64, no row map
+    const int row0 = 32 * (unit & 1);                   // < n_q
+    const size_t in_head = (size_t)HMAR_INPUT_HEAD(head);
+    const __bf16* Qh = sd.Q + in_head * n_q * kD;
+    const __bf16* Kh = sd.K + in_head * Lk * kD;
+    const __bf16* Vh = sd.V + in_head * Lk * kD;
+    const bool two_blocks = Lk > 32;                    // uniform: keys 32..63 exist
+
+    // value rows: this wavefront moves the whole tile, 8 rows per load, rows clamped to the
+    // last key (every LDS row the contraction reads must hold finite numbers).  The
+    // previous unit's patch reads have been consumed by its stores' operands by now.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        if (b < 4 || two_blocks) {
+            const int r = 8 * b + (lane >> 3);
+            const uint32_t voff = min(r, Lk - 1) * kRowBytes + (((lane & 7) ^ swz(r)) << 4);
+            dma16(Vh, voff, Vt + b * 1024);
+        }
+    }
+    const int qrow = min(row0 + lr, n_q - 1);
+    bf16x8 q[4], ka[2][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        q[t] = *reinterpret_cast<const bf16x8*>(Qh + (size_t)qrow * kD + 16 * t + 8 * h);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+            ka[kb][t] = *reinterpret_cast<const bf16x8*>(Kh + (size_t)min(32 * kb + lr, Lk - 1) * kD + 16 * t + 8 * h);
+    }
+    // all twelve loads are in flight before the first one is awaited; loads complete in order,
+    // so the value tile requested before them has landed as well
+    asm volatile("" :: "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]), "v"(ka[0][0]), "v"(ka[0][1]), "v"(ka[0][2]),
+                 "v"(ka[0][3]), "v"(ka[1][0]), "v"(ka[1][1]), "v"(ka[1][2]), "v"(ka[1][3]));
+
+    f32x16 s[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) s[kb] = mfma32(ka[kb][t], q[t], s[kb]);
+    }
+    // element i of block kb is key 4h + 32kb + 8(i/4) + i%4; keys >= Lk do not exist
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) mask_block(s[kb], 32 * kb, -4 * h, Lk - 4 * h, false, Lk < 64);
+    float mt = s[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mt = fmaxf(mt, s[kb][i]);
+    const float m_ref = half_max(mt) * p.c;            // key 0 exists: finite
+    float lsum = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], p.c, -m_ref));
+            lsum += pv;
+            s[kb][i] = pv;
+        }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (already true; the compiler cannot know)
+    f32x16 o[2];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
+#pragma unroll
+    for (int tp = 0; tp < 4; ++tp) {
+        if (tp < 2 || two_blocks) {
+            const int kb = tp >> 1, e0 = 8 * (tp & 1);
+            const bf16x8 pb = pack8(s[kb][e0 + 0], s[kb][e0 + 1], s[kb][e0 + 2], s[kb][e0 + 3],
+                                    s[kb][e0 + 4], s[kb][e0 + 5], s[kb][e0 + 6], s[kb][e0 + 7]);
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) o[mb] = mfma32(lds_a_tr(Vt, lo_, mb, tp), pb, o[mb]);
+        }
+    }
+    const float l = half_sum(lsum);
+    // LDS operations of a wavefront execute in order: the patch writes follow the tile reads
+    store_block_rows(Vt, o, 1.0f / l, sd.O + (size_t)head * n_q * kD, row0, n_q - row0, lane);
+    if (row0 + lr < n_q && h == 0) sd.LSE[(size_t)head * n_q + qrow] = (m_ref + log2f(l)) * kLn2;
+}
+
+// The pack item of a steps launch that has larger steps too: wavefront w takes the units w, w + WAVES, ...
+// of the workgroup's head.
 template <int WAVES>
 __device__ __forceinline__ void small_steps_pack(const StepParams& p, int head, char* smem) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lr = lane & 31, h = lane >> 5;
-    const LaneOffsets lo_ = make_lane_offsets(lane, 0);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const LaneOffsets lo_ = make_lane_offsets(threadIdx.x & 63, 0);
     const uint32_t Vt = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kTileBytes);
-    static_assert(kPatchBytes <= kTileBytes, "the result patch reuses the value tile");
-
-    for (int u = wave; u < p.n_pack; u += WAVES) {
-        const int unit = p.pack_unit[u];
-        const StepDesc& sd = p.step[unit >> 1];
-        const int n_q = sd.n_q, Lk = sd.Lk;                 // Lk <= 64, no row map
-        const int row0 = 32 * (unit & 1);                   // < n_q
-        const size_t in_head = (size_t)HMAR_INPUT_HEAD(head);
-        const __bf16* Qh = sd.Q + in_head * n_q * kD;
-        const __bf16* Kh = sd.K + in_head * Lk * kD;
-        const __bf16* Vh = sd.V + in_head * Lk * kD;
-        const bool two_blocks = Lk > 32;                    // uniform: keys 32..63 exist
-
-        // value rows: this wavefront moves the whole tile, 8 rows per load, rows clamped to the
-        // last key (every LDS row the contraction reads must hold finite numbers).  The
-        // previous unit's patch reads have been consumed by its stores' operands by now.
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            if (b < 4 || two_blocks) {
-                const int r = 8 * b + (lane >> 3);
-                const uint32_t voff = min(r, Lk - 1) * kRowBytes + (((lane & 7) ^ swz(r)) << 4);
-                dma16(Vh, voff, Vt + b * 1024);
-            }
-        }
-        const int qrow = min(row0 + lr, n_q - 1);
-        bf16x8 q[4], ka[2][4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            q[t] = *reinterpret_cast<const bf16x8*>(Qh + (size_t)qrow * kD + 16 * t + 8 * h);
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-                ka[kb][t] = *reinterpret_cast<const bf16x8*>(Kh + (size_t)min(32 * kb + lr, Lk - 1) * kD + 16 * t + 8 * h);
-        }
-        // all twelve loads are in flight before the first one is awaited; loads complete in order,
-        // so the value tile requested before them has landed as well
-        asm volatile("" :: "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]), "v"(ka[0][0]), "v"(ka[0][1]), "v"(ka[0][2]),
-                     "v"(ka[0][3]), "v"(ka[1][0]), "v"(ka[1][1]), "v"(ka[1][2]), "v"(ka[1][3]));
-
-        f32x16 s[2];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) s[kb] = mfma32(ka[kb][t], q[t], s[kb]);
-        }
-        // element i of block kb is key 4h + 32kb + 8(i/4) + i%4; keys >= Lk do not exist
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) mask_block(s[kb], 32 * kb, -4 * h, Lk - 4 * h, false, Lk < 64);
-        float mt = s[0][0];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mt = fmaxf(mt, s[kb][i]);
-        const float m_ref = half_max(mt) * p.c;            // key 0 exists: finite
-        float lsum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][i], p.c, -m_ref));
-                lsum += pv;
-                s[kb][i] = pv;
-            }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (already true; the compiler cannot know)
-        f32x16 o[2];
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
-#pragma unroll
-        for (int tp = 0; tp < 4; ++tp) {
-            if (tp < 2 || two_blocks) {
-                const int kb = tp >> 1, e0 = 8 * (tp & 1);
-                const bf16x8 pb = pack8(s[kb][e0 + 0], s[kb][e0 + 1], s[kb][e0 + 2], s[kb][e0 + 3],
-                                        s[kb][e0 + 4], s[kb][e0 + 5], s[kb][e0 + 6], s[kb][e0 + 7]);
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb) o[mb] = mfma32(lds_a_tr(Vt, lo_, mb, tp), pb, o[mb]);
-            }
-        }
-        const float l = half_sum(lsum);
-        // LDS operations of a wavefront execute in order: the patch writes follow the tile reads
-        store_block_rows(Vt, o, 1.0f / l, sd.O + (size_t)head * n_q * kD, row0, n_q - row0, lane);
-        if (row0 + lr < n_q && h == 0) sd.LSE[(size_t)head * n_q + qrow] = (m_ref + log2f(l)) * kLn2;
-    }
+    for (int u = wave; u < p.n_pack; u += WAVES) small_step_unit(p, head, p.pack_unit[u], Vt, lo_);
 }
+
+// A launch of small steps alone: every wavefront takes one unit of one head, the units of a head side by
+// side.  (One workgroup per head, as the pack has it, leaves three of four wavefronts without work in a
+// step of up to 32 rows, and 1536 heads take two rounds of workgroups where this takes less than one.
+// SMALL_FIGURES)
+__global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_steps_kernel(StepParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned u = blockIdx.x * 4 + wave;
+    const unsigned head = u / (unsigned)p.n_pack;
+    if (head >= (unsigned)p.n_heads) return;
+    const LaneOffsets lo_ = make_lane_offsets(threadIdx.x & 63, 0);
+    small_step_unit(p, (int)head, p.pack_unit[u % (unsigned)p.n_pack],
+                    __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kTileBytes), lo_);
+}
+
 // One body serves both launches: with STEPS the item, its buffers and its (trivial) pair ranges
 // come from the step descriptors, otherwise from the schedule tables.
 template <bool STEPS, int RW, int KS, typename Params>
@@ -552,7 +569,10 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     const unsigned groups = launch_groups(items, n_heads);
     if (groups == 0) return hipErrorInvalidValue;
     profile_before(kKernelFwd, stream);
-    with_split(split, [&](auto rw, auto ks) {
+    if (p.n_tiled == 0) {
+        const unsigned units = (unsigned)n_heads * (unsigned)p.n_pack;      // at most 2^24 * 32
+        hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((units + 3) / 4), dim3(kThreads), 0, stream, p);
+    } else with_split(split, [&](auto rw, auto ks) {
         hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks()>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
     });
     const hipError_t e = hipGetLastError();
