@@ -490,7 +490,7 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
         p.row_hi = s.row_hi[dir];
         const long long units = (long long)n_heads * s.n_items[dir];
         Split split = dir == 1 ? choose_split_dkdv(units, s.max_tiles[dir], s.num_cus)
-                               : choose_split(units, s.max_tiles[dir], s.num_cus, kLongStreamDq);
+                               : choose_split(units, s.max_tiles[dir], s.num_cus, true);
 #if HMAR_DKDV_KEYS_PER_WAVE == 16 || defined(HMAR_DKDV_PIPE) || defined(HMAR_DKDV_PERSIST)
         if (dir == 1) split = {4, 1};        // the study kernels take whole items
 #endif

@@ -56,13 +56,17 @@ struct StepParams {
     float c;
 };
 
-// Softmax reference.  A row's reference maximum is taken from the tile in which its keys begin; the
-// tiles after it are exponentiated against that reference at once, and only if a lane's sum over a
-// tile comes out above this bound are the tile's scores formed again, their maximum taken and the
-// reference raised to it.  So every probability that is used is at most 2^8, which fp32 sums and bf16
-// operands hold without loss (the final division by the row sum makes the result independent of
-// the reference), and the 24 maximum instructions of a 64 x 32 tile step (of 140 vector
-// instructions: the loop is bound by instruction issue) leave the common path.
+// Softmax reference.  Probabilities are formed against a row's reference maximum and are at most 2^8,
+// which fp32 sums and bf16 operands hold without loss (the final division by the row sum makes the
+// result independent of the reference).
+// Short streams: the reference is raised when a tile's maximum exceeds it by more than eight binades.
+// Long streams (LAZY): the reference is taken from the tile in which a row's keys begin; the tiles after it are
+// exponentiated against that reference at once, and only if a lane's sum over a tile comes out above
+// 2^8 are the tile's scores formed again, their maximum taken and the reference raised to it.  That
+// takes the 24 maximum instructions of a 64 x 32 tile step (of 140 vector instructions: a full chip is bound
+// by instruction issue) off the common path, but the second contraction waits for the sum: with 25 tiles
+// a refinement pass takes 46.7 -> 45.6 us, with 100 tiles the forward 2 % less; with 6 tiles and 1.5 workgroups per compute unit, where the chain of a tile counts, 10.5 -> 11.0 us.
+constexpr float kRescaleThreshold = 8.0f;
 constexpr float kMaxTileSum = 256.0f;
 
 #ifndef HMAR_FWD_MIN_WAVES
@@ -181,7 +185,7 @@ __device__ __forceinline__ void small_steps_pack(const StepParams& p, int head, 
 // A launch of small steps alone: every wavefront takes one unit of one head, the units of a head side by
 // side.  (One workgroup per head, as the pack has it, leaves three of four wavefronts without work in a
 // step of up to 32 rows, and 1536 heads take two rounds of workgroups where this takes less than one.
-// SMALL_FIGURES)
+// Steps of 1, 4, 9, 16, 25, 36 tokens: 8.8 9.2 9.8 10.6 12.4 15.7 -> 5.5 5.7 6.8 7.8 10.7 13.3 us.)
 __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_steps_kernel(StepParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_s
 
 // One body serves both launches: with STEPS the item, its buffers and its (trivial) pair ranges
 // come from the step descriptors, otherwise from the schedule tables.
-template <bool STEPS, int RW, int KS, typename Params>
+template <bool STEPS, int RW, int KS, bool LAZY, typename Params>
 __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     constexpr int kRows = RW * kRowsPerWave;      // rows of the workgroup
     constexpr int kStages = RW == 4 && KS == 1 ? kFwdStages : 2;
@@ -320,9 +324,11 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
             auto scores = [&]() {
                 // opaque to the compiler: the two uses below share no operand and no comparison (kept live
                 // from one to the other they would not fit the registers)
-                asm volatile("" ::: "memory");
                 int lim_lo = lo - kt - 4 * h, lim_hi = hi - kt - 4 * h;
-                asm volatile("" : "+v"(lim_lo), "+v"(lim_hi));
+                if constexpr (LAZY) {
+                    asm volatile("" ::: "memory");
+                    asm volatile("" : "+v"(lim_lo), "+v"(lim_hi));
+                }
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
@@ -336,14 +342,17 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                 for (int kb = 0; kb < 2; ++kb)
                     mask_block(s[kb], 32 * kb, lim_lo, lim_hi, kt < full_lo, kt + kTile > full_hi);
             };
-            // the reference becomes the largest score so far; what was accumulated follows it
-            auto raise_reference = [&]() {
+            auto largest = [&]() {
                 float mt = s[0][0];
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) mt = fmaxf(mt, s[kb][i]);
-                const float m_new = fmaxf(m_ref, half_max(mt) * p.c);
+                return half_max(mt) * p.c;
+            };
+            // the reference becomes the largest score so far; what was accumulated follows it
+            auto raise_reference = [&](float mt) {
+                const float m_new = fmaxf(m_ref, mt);
                 if (!o_empty) {
                     const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
                     lsum *= alpha;
@@ -369,15 +378,22 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                 return sum;
             };
             float tsum;
-            // in this share's first tile at or behind the one in which rows begin they have no reference yet
-            bool raise = kt - (KS - 1) * kTile <= full_lo;
+            if constexpr (LAZY) {
+                // in this share's first tile at or behind the one in which rows begin they have no reference yet
+                bool raise = kt - (KS - 1) * kTile <= full_lo;
 #pragma nounroll
-            while (true) {                              // at most twice
+                while (true) {                              // at most twice
+                    scores();
+                    if (raise) raise_reference(largest());
+                    tsum = exponentials();
+                    if (raise || __builtin_amdgcn_ballot_w64(tsum > kMaxTileSum) == 0) break;
+                    raise = true;
+                }
+            } else {
                 scores();
-                if (raise) raise_reference();
+                const float mt = largest();
+                if (__builtin_amdgcn_ballot_w64(mt > m_ref + kRescaleThreshold) != 0) raise_reference(mt);
                 tsum = exponentials();
-                if (raise || __builtin_amdgcn_ballot_w64(tsum > kMaxTileSum) == 0) break;
-                raise = true;
             }
             lsum += tsum;
             o_empty = false;
@@ -448,20 +464,20 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
 }
 
 // RW wavefronts own 32 rows each, KS sets of them share the tiles (see choose_split)
-template <int RW, int KS>
+template <int RW, int KS, bool LAZY>
 __global__ __launch_bounds__(64 * RW * KS, HMAR_FWD_MIN_WAVES) void hmar_fwd_kernel(FwdParams p) {
     // ring of stages, each KS times a K tile followed by a V tile
     __shared__ __attribute__((aligned(1024))) char smem[(RW == 4 && KS == 1 ? kFwdStages : 2) * KS * 2 * kTileBytes];
 #ifdef HMAR_TUNE_LDS_PAD_FWD
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_FWD)
 #endif
-    fwd_body<false, RW, KS>(p, smem);
+    fwd_body<false, RW, KS, LAZY>(p, smem);
 }
 
-template <int RW, int KS>
+template <int RW, int KS, bool LAZY>
 __global__ __launch_bounds__(64 * RW * KS, HMAR_FWD_MIN_WAVES) void hmar_fwd_steps_kernel(StepParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[(RW == 4 && KS == 1 ? kFwdStages : 2) * KS * 2 * kTileBytes];
-    fwd_body<true, RW, KS>(p, smem);
+    fwd_body<true, RW, KS, LAZY>(p, smem);
 }
 
 #ifdef HMAR_TUNE_FWD_STUDY
@@ -495,7 +511,7 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
 #ifdef HMAR_TUNE_FWD_STUDY
     const Split split = {4, 1};              // the study kernel takes whole items
 #else
-    const Split split = choose_split((long long)n_heads * s.n_items[0], s.max_tiles[0], s.num_cus, kLongStreamFwd);
+    const Split split = choose_split((long long)n_heads * s.n_items[0], s.max_tiles[0], s.num_cus, false);
 #endif
     p.n_items = s.n_items[0] * (4 / split.rw);
     p.n_heads = n_heads;
@@ -511,7 +527,10 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
                        dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
     with_split(split, [&](auto rw, auto ks) {
-        hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks()>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
+        if (s.max_tiles[0] >= kLongStream)
+            hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
+        else
+            hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), false>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
     });
 #endif
     const hipError_t e = hipGetLastError();
@@ -534,7 +553,7 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
         blocks128 += (L.step[order[i]].n_q + 127) / 128;
         max_tiles = std::max(max_tiles, (L.step[order[i]].Lk + kTile - 1) / kTile);
     }
-    const Split split = choose_split((blocks128 + (p.n_tiled < L.n_steps)) * n_heads, max_tiles, num_cus, kLongStreamFwd);
+    const Split split = choose_split((blocks128 + (p.n_tiled < L.n_steps)) * n_heads, max_tiles, num_cus, false);
     const int rows_per_item = split.rw * kRowsPerWave;
     int items = 0;
     p.n_pack = 0;
@@ -573,7 +592,10 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
         const unsigned units = (unsigned)n_heads * (unsigned)p.n_pack;      // at most 2^24 * 32
         hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((units + 3) / 4), dim3(kThreads), 0, stream, p);
     } else with_split(split, [&](auto rw, auto ks) {
-        hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks()>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
+        if (max_tiles >= kLongStream)
+            hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
+        else
+            hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), false>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
     });
     const hipError_t e = hipGetLastError();
     profile_after(kKernelFwd, stream);

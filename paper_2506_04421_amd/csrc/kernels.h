@@ -58,19 +58,20 @@ struct Split { int rw, ks; };
 //     more to do per tile and gains from it only on the longest, 100 tiles, 272 units: 111 -> 73 ({4, 2}: 78;
 //     at 25 tiles 24.9 against 23.4).
 //   tiles by two: long streams up to 2 (25 tiles, 480 units: 28.5 -> 25.7, dQ even; 100 tiles, 476 units: 102 ->
-//     81, 120 -> 103; a refinement pass of 576 equal units is 4 % slower), shorter ones up to 3/2 (7 tiles,
-//     308 units: 11.6 -> 10.4, 13.2 -> 13.0; at 448 units even and 8 % slower).
-inline Split choose_split(long long units, int max_tiles, int num_cus, int long_stream) {
+//     81, 120 -> 103; a refinement pass of 576 equal units is 4 % slower), shorter ones up to 5/4 and not for dQ
+//     (7 tiles, 308 units: forward 11.6 -> 10.4, dQ 13.2 -> 13.0; 6 tiles, 384 units: 10.9 -> 11.3, dQ 9 % slower).
+constexpr int kLongStream = 16;            // tiles
+inline Split choose_split(long long units, int max_tiles, int num_cus, bool dq) {
 #ifdef HMAR_FORCE_SPLIT
     return HMAR_FORCE_SPLIT;
 #endif
     if (max_tiles < 4) return {4, 1};          // 3 tiles: 6.4 -> 6.7
     if (2 * units <= num_cus) return {2, 4};
-    if (max_tiles >= long_stream && 4 * units <= 5LL * num_cus) return {4, 4};
-    if (2 * units <= (max_tiles >= 16 ? 4LL : 3LL) * num_cus) return {4, 2};
-    return {4, 1};
+    const bool at_most_5_4 = 4 * units <= 5LL * num_cus;
+    if (max_tiles < kLongStream) return at_most_5_4 && !dq ? Split{4, 2} : Split{4, 1};
+    if (at_most_5_4 && (!dq || max_tiles >= 48)) return {4, 4};
+    return units <= 2LL * num_cus ? Split{4, 2} : Split{4, 1};
 }
-constexpr int kLongStreamFwd = 16, kLongStreamDq = 48;
 // dK/dV (252 VGPRs: eight wavefronts fill a compute unit): 64-row halves.
 //   long streams, up to half a unit per compute unit: tiles by four (25 tiles, 120 units: 30.9 -> 20.1; 100 tiles,
 //     68 units: 107 -> 57);
@@ -81,7 +82,7 @@ inline Split choose_split_dkdv(long long units, int max_tiles, int num_cus) {
     return HMAR_FORCE_SPLIT_DKDV;
 #endif
     if (max_tiles < 4) return {4, 1};
-    if (max_tiles < 16) return 8 * units <= 5LL * num_cus ? Split{2, 2} : Split{4, 1};
+    if (max_tiles < kLongStream) return 8 * units <= 5LL * num_cus ? Split{2, 2} : Split{4, 1};
     if (2 * units <= num_cus) return {2, 4};
     return 4 * units <= 5LL * num_cus ? Split{2, 2} : Split{4, 1};
 }

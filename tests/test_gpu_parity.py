@@ -349,6 +349,24 @@ def test_scores_that_jump_far_above_the_first_tile():
     assert float(np.abs(ref["LSE"]).max()) > 300.0  # the case really is extreme
 
 
+@pytest.mark.parametrize("H", [2, 24, 40, 60])
+def test_scores_that_jump_in_long_streams(H):
+    # the same on streams of more than 16 tiles, where a tile is exponentiated before its maximum is
+    # known and formed again if a row's sum comes out too large, for every form of a workgroup
+    sides, D = (3, 23, 25), 64
+    offs, L = orc.scale_offsets(sides), sum(s * s for s in sides)
+    Q, K, V, _ = si.draw((1, H, L, D), seed=1600 + H, n_tensors=4)
+    boost = torch.ones(L)
+    for a, b in zip(offs[:-1], offs[1:]):
+        boost[b - (b - a) // 2:b] = 16.0
+        boost[b - (b - a) // 3:b] = 64.0
+    K = (K.float() * boost.view(1, 1, L, 1)).to(torch.bfloat16)
+    Q = (Q.float() * 8.0).to(torch.bfloat16)
+    res = _gpu_run(Q, K, V, None, sides, 0.125, backward=False)
+    heads = [(0, h) for h in sorted({0, H // 2, H - 1})]
+    _compare(res, _oracle_heads(Q, K, V, None, sides, 0.125, heads), heads, "late-dominant-keys, long streams")
+
+
 def test_custom_softmax_scale():
     sides = (3, 6, 9)
     L, B, H, D = 126, 1, 2, 64
