@@ -7,7 +7,7 @@ been built, importing the entry points fails with an error that says how to buil
 
 A plainly valid call of the entry points goes through the native module _launch, which does the same
 checks, allocations and library call in a fraction of the host time; whatever it does not accept
-(it returns None) takes the Python code below it, which decides and words the errors.  Measured per
+(it returns None) takes the Python code below it, which decides and words the errors.
 """
 from __future__ import annotations
 
