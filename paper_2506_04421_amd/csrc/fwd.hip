@@ -527,7 +527,10 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
                        dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
     with_split(split, [&](auto rw, auto ks) {
-        if (s.max_tiles[0] >= kLongStream)
+        // {4, 4} is for long streams only
+        if constexpr (rw() == 4 && ks() == 4)
+            hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
+        else if (s.max_tiles[0] >= kLongStream)
             hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
         else
             hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), false>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
@@ -592,7 +595,10 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
         const unsigned units = (unsigned)n_heads * (unsigned)p.n_pack;      // at most 2^24 * 32
         hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((units + 3) / 4), dim3(kThreads), 0, stream, p);
     } else with_split(split, [&](auto rw, auto ks) {
-        if (max_tiles >= kLongStream)
+        // {4, 4} is for long streams only
+        if constexpr (rw() == 4 && ks() == 4)
+            hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
+        else if (max_tiles >= kLongStream)
             hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
         else
             hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), false>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
