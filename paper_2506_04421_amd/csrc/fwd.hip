@@ -57,17 +57,15 @@ struct StepParams {
 };
 
 // Softmax reference.  Probabilities are formed against a row's reference maximum and are at most 2^8,
-// which fp32 sums and bf16 operands hold without loss (the final division by the row sum makes the
-// result independent of the reference).
-// Short streams: the reference is raised when a tile's maximum exceeds it by more than eight binades.
-// Long streams (LAZY): the reference is taken from the tile in which a row's keys begin; the tiles after it are
-// exponentiated against that reference at once, and only if a lane's sum over a tile comes out above
-// 2^8 are the tile's scores formed again, their maximum taken and the reference raised to it.  That
-// takes the 24 maximum instructions of a 64 x 32 tile step (of 140 vector instructions: a full chip is bound
-// by instruction issue) off the common path, but the second contraction waits for the sum: with 25 tiles
-// a refinement pass takes 46.7 -> 45.6 us, with 100 tiles the forward 2 % less; with 6 tiles and 1.5 workgroups per compute unit, where the chain of a tile counts, 10.5 -> 11.0 us.
+// which fp32 sums and bf16 operands hold without loss.  The reference is raised when a tile's maximum exceeds
+// it by more than eight binades.
+// Long streams (LAZY) do not take the maximum of every tile: past the tiles in which the rows' keys begin, a tile is
+// exponentiated at once, and only if a lane's sum over it comes out above 2^7 are its scores formed again
+// and put to that rule; from then on the wavefront takes every maximum first.  A score more than eight binades
+// above the reference makes a probability of 2^8 and more, which no rounding of the sum (below 2^27: 2^19 keys of at
+// most 2^8) can bring under 2^7, so the references, and with them all results, are bit for bit those of the plain form.
 constexpr float kRescaleThreshold = 8.0f;
-constexpr float kMaxTileSum = 256.0f;
+constexpr float kSuspectTileSum = 128.0f;
 
 #ifndef HMAR_FWD_MIN_WAVES
 #define HMAR_FWD_MIN_WAVES 4
@@ -296,6 +294,7 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
     float m_ref = kNegBig, lsum = 0.f;
+    bool suspect = false;             // LAZY: a tile had to be formed again
     bool o_empty = true;              // nothing accumulated yet: the first rescale has nothing to scale
 
     // The compiler does not see the DMA loads; without this use it would wait for the Q
@@ -350,8 +349,11 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                     for (int i = 0; i < 16; ++i) mt = fmaxf(mt, s[kb][i]);
                 return half_max(mt) * p.c;
             };
-            // the reference becomes the largest score so far; what was accumulated follows it
-            auto raise_reference = [&](float mt) {
+            // put the tile's scores to the rule: where it holds the reference becomes the largest score so far, and
+            // what was accumulated follows it
+            auto raise_reference = [&]() {
+                const float mt = largest();
+                if (__builtin_amdgcn_ballot_w64(mt > m_ref + kRescaleThreshold) == 0) return;
                 const float m_new = fmaxf(m_ref, mt);
                 if (!o_empty) {
                     const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
@@ -363,10 +365,10 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                 }
                 m_ref = m_new;
             };
-            // scores become probabilities; returns the lane's sum of them
+            // scores become probabilities; returns the lane's sum with them
             auto exponentials = [&]() {
                 const float neg_m = -m_ref;
-                float sum = 0.f;
+                float sum = lsum;
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -377,25 +379,24 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                     }
                 return sum;
             };
-            float tsum;
             if constexpr (LAZY) {
                 // in this share's first tile at or behind the one in which rows begin they have no reference yet
-                bool raise = kt - (KS - 1) * kTile <= full_lo;
+                bool check = suspect || kt - (KS - 1) * kTile <= full_lo;
+                float sum;
 #pragma nounroll
                 while (true) {                              // at most twice
                     scores();
-                    if (raise) raise_reference(largest());
-                    tsum = exponentials();
-                    if (raise || __builtin_amdgcn_ballot_w64(tsum > kMaxTileSum) == 0) break;
-                    raise = true;
+                    if (check) raise_reference();
+                    sum = exponentials();
+                    if (check || __builtin_amdgcn_ballot_w64(!(sum - lsum <= kSuspectTileSum)) == 0) break;
+                    check = suspect = true;
                 }
+                lsum = sum;
             } else {
                 scores();
-                const float mt = largest();
-                if (__builtin_amdgcn_ballot_w64(mt > m_ref + kRescaleThreshold) != 0) raise_reference(mt);
-                tsum = exponentials();
+                raise_reference();
+                lsum = exponentials();
             }
-            lsum += tsum;
             o_empty = false;
 #pragma unroll
             for (int tp = 0; tp < 4; ++tp) {

@@ -60,7 +60,10 @@ struct Split { int rw, ks; };
 //   tiles by two: long streams up to 2 (25 tiles, 480 units: 28.5 -> 25.7, dQ even; 100 tiles, 476 units: 102 ->
 //     81, 120 -> 103; a refinement pass of 576 equal units is 4 % slower), shorter ones up to 5/4 and not for dQ
 //     (7 tiles, 308 units: forward 11.6 -> 10.4, dQ 13.2 -> 13.0; 6 tiles, 384 units: 10.9 -> 11.3, dQ 9 % slower).
-constexpr int kLongStream = 16;            // tiles
+#ifndef HMAR_TUNE_LONG_STREAM
+#define HMAR_TUNE_LONG_STREAM 16           // measurement builds: where long streams begin
+#endif
+constexpr int kLongStream = HMAR_TUNE_LONG_STREAM;      // tiles
 inline Split choose_split(long long units, int max_tiles, int num_cus, bool dq) {
 #ifdef HMAR_FORCE_SPLIT
     return HMAR_FORCE_SPLIT;

@@ -739,3 +739,22 @@ def test_inference_steps_reproduce_the_training_forward():
         torch.cuda.synchronize()
         assert (Os.float() - O[:, :, q0:q1].float()).abs().max().item() <= 1e-2
         assert (LSEs - LSE[:, :, q0:q1]).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("p,c", [(100, 600), (700, 130), (0, 900)])
+@pytest.mark.parametrize("factor", [1.0, 2.0, 3.5, 6.0, 20.0])
+def test_maxima_left_out_on_long_streams_change_no_bits(p, c, factor):
+    # a step of 11 to 15 key tiles takes every tile's maximum when it is called alone; beside a step of 25 tiles it is
+    # exponentiated before its maximum is known.  Keys grow along the stream by `factor`, by steps below and above the
+    # eight binades at which the reference moves.
+    d, H = _dev(), 900
+    g = torch.Generator(device=d)
+    g.manual_seed(1900 + p)
+    draw = lambda h, n: torch.randn((1, h, n, 64), device=d, generator=g)
+    grow = 1.0 + (factor - 1.0) * torch.linspace(0.0, 1.0, p + c, device=d).pow(2).view(1, 1, -1, 1)
+    grow = torch.where(torch.rand((1, H, p + c, 1), device=d, generator=g) < 0.1, grow, torch.ones_like(grow))
+    q, k, v = draw(H, c).bfloat16(), (draw(H, p + c) * grow).bfloat16(), draw(H, p + c).bfloat16()
+    long = [draw(H, n).bfloat16() for n in (129, 1600, 1600)]
+    O, LSE = hm.hmar_attn_step_fwd(q, k, v, p)
+    Os, LSEs = hm.hmar_attn_steps_fwd([q, long[0]], [k, long[1]], [v, long[2]], [p, 1471])
+    assert torch.isfinite(O.float()).all() and torch.equal(O, Os[0]) and torch.equal(LSE, LSEs[0])
