@@ -56,41 +56,32 @@ __device__ __forceinline__ float neg_delta_of_row(const __bf16* o_row, const bf1
     return -half_sum(acc);
 }
 
-// The work of one dQ item.  smem: ring of 2 stages, each KS times a K tile followed by a V tile.
+// The work of one dQ item.  smem: ring of 2 stages, each a K tile followed by a V tile.
 // OWN_STATS: form the row statistics here and leave them in the workspace (the shipped kernel);
 // otherwise they are read from the workspace.
-// RW, KS: the split of the workgroup (see choose_split); `it` holds at most 32 RW rows.
-template <bool OWN_STATS, int RW = 4, int KS = 1>
+template <bool OWN_STATS>
 __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const int32_t* row_lo, const int32_t* row_hi,
                                         int head, int item_id, char* smem) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rw = KS > 1 ? wave % RW : wave, part = KS > 1 ? wave / RW : 0;      // the wavefront's 32 rows; its share of the tiles
-    constexpr int kSlot = 2 * kTileBytes;
     const int lr = lane & 31, h = lane >> 5;
     const size_t head_off = (size_t)head * p.L * kD;
     const size_t head_in = (size_t)HMAR_INPUT_HEAD(head) * p.L * kD;     // == head_off outside measurements
     const __bf16* Kh = p.K + head_in;
     const __bf16* Vh = p.V + head_in;
-    LaneOffsets lo_ = make_lane_offsets(lane, rw);
-    if constexpr (KS > 1) shift_lane_offsets(lo_, part * kSlot);     // reads of the share's tiles: the rest is immediate
+    const LaneOffsets lo_ = make_lane_offsets(lane, wave);
     const uint32_t smem_base = lds_address(smem);
 
     const int k_begin = it.other_begin, k_end = it.other_end, kmax = k_end - 1;
     const int ntiles = (k_end - k_begin + kTile - 1) / kTile;
 
-    const int nsteps = (ntiles + KS - 1) / KS;       // KS tiles per step, one per share
-    const uint32_t ring = smem_base + part * kSlot;  // stage st of this share: ring + st * KS * kSlot
-
-    auto issue = [&](int step, int st) {     // 4 DMA loads per lane and tile (8 where two wavefronts share a tile)
-        const int ti = step * KS + part;
-        if (KS > 1 && ti >= ntiles) return;
-        const uint32_t stage = ring + st * (KS * kSlot);
-        dma_tile_by<RW>(Kh, k_begin + ti * kTile, kmax, stage, lo_, lane, rw);
-        dma_tile_by<RW>(Vh, k_begin + ti * kTile, kmax, stage + kTileBytes, lo_, lane, rw);
+    auto issue = [&](int ti, int st) {       // 4 DMA loads per lane and tile
+        const uint32_t stage = smem_base + st * (2 * kTileBytes);
+        dma_tile(Kh, k_begin + ti * kTile, kmax, stage, lo_, lane, wave);
+        dma_tile(Vh, k_begin + ti * kTile, kmax, stage + kTileBytes, lo_, lane, wave);
     };
     issue(0, 0);
 
-    const int wq0 = it.own_begin + rw * kRowsPerWave;
+    const int wq0 = it.own_begin + wave * kRowsPerWave;
     const bool wave_active = wq0 < it.own_end;
     const int qrow = min(wq0 + lr, it.own_end - 1);
     const int lo = row_lo[qrow], hi = row_hi[qrow];
@@ -109,7 +100,7 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
     if constexpr (OWN_STATS) {
         nl2 = -p.LSE[(size_t)HMAR_INPUT_HEAD(head) * p.L + qrow] * kLog2e;
         ndelta = neg_delta_of_row(p.O + head_in + (size_t)qrow * kD, dob, h);
-        if (wq0 + lr < it.own_end && h == 0 && part == 0) {
+        if (wq0 + lr < it.own_end && h == 0) {
             p.neg_lse2[(size_t)head * p.L + qrow] = nl2;
             p.neg_delta[(size_t)head * p.L + qrow] = ndelta;
         }
@@ -132,16 +123,16 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
 
     // one tile: request the next one, compute, wait for the request; the stage is a template
     // constant so that every LDS address of the step is a per-lane register plus an immediate
-    auto tile_step = [&](const int step, auto stage_c) {
+    auto tile_step = [&](const int ti, auto stage_c) {
         constexpr int ST = decltype(stage_c)::value;
-        const int kt = k_begin + (step * KS + part) * kTile;
-        if (step + 1 < nsteps) issue(step + 1, ST ^ 1);
+        const int kt = k_begin + ti * kTile;
+        if (ti + 1 < ntiles) issue(ti + 1, ST ^ 1);
 #ifdef HMAR_TUNE_NO_COMPUTE_DQ
         if (false) {
 #else
         if (wave_active && kt < whi && kt + kTile > wlo) {
 #endif
-            const uint32_t Kt = smem_base + ST * (KS * kSlot);
+            const uint32_t Kt = smem_base + ST * (2 * kTileBytes);
             const uint32_t Vt = Kt + kTileBytes;
             const bool need_lo = kt < full_lo, need_hi = kt + kTile > full_hi;
             const int lim_lo = lo - kt - 4 * h, lim_hi = hi - kt - 4 * h;
@@ -176,38 +167,24 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
         }
         HMAR_WAIT_DMA_AND_BARRIER(0);     // the tile requested above has landed and this one is free
     };
-    for (int step = 0; step < nsteps; step += 2) {
-        tile_step(step, std::integral_constant<int, 0>{});
-        if (step + 1 >= nsteps) break;
-        tile_step(step + 1, std::integral_constant<int, 1>{});
+    for (int ti = 0; ti < ntiles; ti += 2) {
+        tile_step(ti, std::integral_constant<int, 0>{});
+        if (ti + 1 >= ntiles) break;
+        tile_step(ti + 1, std::integral_constant<int, 1>{});
     }
 
-    uint32_t patch = smem_base + rw * kPatchBytes;
-    if constexpr (KS > 1) {                  // the shares meet: the first adds up what the others bring
-        constexpr int kParts = (KS - 1) * RW;
-        static_assert(kParts * kPartBytes + RW * kPatchBytes <= 2 * KS * kSlot, "partial results and patches fit the ring");
-        patch += kParts * kPartBytes;
-        if (part > 0) part_store(smem_base + ((part - 1) * RW + rw) * kPartBytes, dq, lane);
-        HMAR_WAIT_DMA_AND_BARRIER(0);
-        if (part > 0) return;
-#pragma unroll
-        for (int g = 1; g < KS; ++g) part_add(smem_base + ((g - 1) * RW + rw) * kPartBytes, dq, lane, 1.0f, 1.0f);
-    }
     if (wave_active)
-        store_block_rows(patch, dq, p.sm_scale, p.dQ + head_off, wq0, it.own_end - wq0, lane, nullptr, HMAR_NT_GRADS != 0);
+        store_block_rows(smem_base + wave * kPatchBytes, dq, p.sm_scale, p.dQ + head_off, wq0, it.own_end - wq0, lane, nullptr, HMAR_NT_GRADS != 0);
 }
 
-template <int RW, int KS>
-__global__ __launch_bounds__(64 * RW * KS, HMAR_DQ_MIN_WAVES) void hmar_dq_kernel(BwdParams p) {
-    __shared__ __attribute__((aligned(1024))) char smem[2 * KS * 2 * kTileBytes];
+__global__ __launch_bounds__(kThreads, HMAR_DQ_MIN_WAVES) void hmar_dq_kernel(BwdParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[2 * 2 * kTileBytes];
 #ifdef HMAR_TUNE_LDS_PAD_DQ
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_DQ)
 #endif
     int head, item_id;
     if (!map_workgroup(p.n_items, p.n_heads, p.tail_groups, &head, &item_id, true)) return;
-    Item it;
-    if (!split_item<RW>(p.items, item_id, &it)) return;
-    dq_body<true, RW, KS>(p, it, p.row_lo, p.row_hi, head, item_id, smem);
+    dq_body<true>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem);
 }
 
 // ---------------------------------------------------------------------------------- dK, dV
@@ -296,15 +273,11 @@ __device__ __forceinline__ void dkdv_tile(uint32_t Qt, uint32_t Gt, uint32_t nl2
     }
 }
 
-// The work of one dK/dV item.  smem: ring of 2 stages, each KS times a Q tile followed by a dO tile;
-// nl2_s, delta_s: the per-row statistics of the tiles, laid out alike.
-// RW, KS: the split of the workgroup (see choose_split); `it` holds at most 32 RW rows.
-template <int RW = 4, int KS = 1>
+// The work of one dK/dV item.  smem: ring of 2 stages, each a Q tile followed by a dO tile;
+// nl2_s, delta_s: the per-row statistics of the two stages.
 __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, const int32_t* row_lo, const int32_t* row_hi,
                                           int head, int item_id, char* smem, float (*nl2_s)[kTile], float (*delta_s)[kTile]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rw = KS > 1 ? wave % RW : wave, part = KS > 1 ? wave / RW : 0;      // the wavefront's 32 keys; its share of the tiles
-    constexpr int kSlot = 2 * kTileBytes;
     const int lr = lane & 31, h = lane >> 5;
     const size_t head_off = (size_t)head * p.L * kD;
     const size_t head_in = (size_t)HMAR_INPUT_HEAD(head) * p.L * kD;     // == head_off outside measurements
@@ -312,32 +285,25 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
     const __bf16* Gh = p.dO + head_in;
     const float* NLh = p.neg_lse2 + (size_t)head * p.L;
     const float* Dh = p.neg_delta + (size_t)head * p.L;
-    LaneOffsets lo_ = make_lane_offsets(lane, rw);
-    if constexpr (KS > 1) shift_lane_offsets(lo_, part * kSlot);     // reads of the share's tiles: the rest is immediate
+    const LaneOffsets lo_ = make_lane_offsets(lane, wave);
     const uint32_t smem_base = lds_address(smem);
-    const uint32_t nl2_base = lds_address(nl2_s) + part * (kTile * 4), delta_base = lds_address(delta_s) + part * (kTile * 4);
+    const uint32_t nl2_base = lds_address(nl2_s), delta_base = lds_address(delta_s);
 
     const int q_begin = it.other_begin, q_end = it.other_end, qmax = q_end - 1;
     const int ntiles = (q_end - q_begin + kTile - 1) / kTile;
 
-    const int nsteps = (ntiles + KS - 1) / KS;       // KS tiles per step, one per share
-    const uint32_t ring = smem_base + part * kSlot;  // stage st of this share: ring + st * KS * kSlot
-
-    // per lane and tile: 4 DMA loads (8 where two wavefronts share a tile), plus one for wavefronts 0
-    // (-LSE*log2e) and 1 (Delta) of the share
-    auto issue = [&](int step, int st) {
-        const int ti = step * KS + part;
-        if (KS > 1 && ti >= ntiles) return;
-        const uint32_t stage = ring + st * (KS * kSlot);
+    // per lane and tile: 4 DMA loads, plus one for wavefronts 0 (-LSE*log2e) and 1 (Delta)
+    auto issue = [&](int ti, int st) {
+        const uint32_t stage = smem_base + st * (2 * kTileBytes);
         const int qt = q_begin + ti * kTile;
-        dma_tile_by<RW>(Qh, qt, qmax, stage, lo_, lane, rw);
-        dma_tile_by<RW>(Gh, qt, qmax, stage + kTileBytes, lo_, lane, rw);
-        if (rw == 0) dma_floats(NLh, qt, qmax, nl2_base + st * (KS * kTile * 4), lane);
-        else if (rw == 1) dma_floats(Dh, qt, qmax, delta_base + st * (KS * kTile * 4), lane);
+        dma_tile(Qh, qt, qmax, stage, lo_, lane, wave);
+        dma_tile(Gh, qt, qmax, stage + kTileBytes, lo_, lane, wave);
+        if (wave == 0) dma_floats(NLh, qt, qmax, nl2_base + st * (kTile * 4), lane);
+        else if (wave == 1) dma_floats(Dh, qt, qmax, delta_base + st * (kTile * 4), lane);
     };
     issue(0, 0);
 
-    const int wk0 = it.own_begin + rw * kRowsPerWave;
+    const int wk0 = it.own_begin + wave * kRowsPerWave;
     const bool wave_active = wk0 < it.own_end;
     const int krow = min(wk0 + lr, it.own_end - 1);
     const int lo = row_lo[krow], hi = row_hi[krow];       // queries that see this key
@@ -363,68 +329,46 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
                  "v"(vreg[2]), "v"(vreg[3]));
     HMAR_WAIT_DMA_AND_BARRIER(0);
 
-    auto tile_step = [&](const int step, auto stage_c) {     // see the dQ kernel
+    auto tile_step = [&](const int ti, auto stage_c) {     // see the dQ kernel
         constexpr int ST = decltype(stage_c)::value;
-        const int qt = q_begin + (step * KS + part) * kTile;
-        if (step + 1 < nsteps) issue(step + 1, ST ^ 1);
+        const int qt = q_begin + ti * kTile;
+        if (ti + 1 < ntiles) issue(ti + 1, ST ^ 1);
 #ifdef HMAR_TUNE_NO_COMPUTE_DKDV
         if (false) {
 #else
         if (wave_active && qt < whi && qt + kTile > wlo) {
 #endif
-            const uint32_t Qt = smem_base + ST * (KS * kSlot);
-            const uint32_t nl2_t = nl2_base + ST * (KS * kTile * 4) + 16 * h;
-            const uint32_t delta_t = delta_base + ST * (KS * kTile * 4) + 16 * h;
+            const uint32_t Qt = smem_base + ST * (2 * kTileBytes);
+            const uint32_t nl2_t = nl2_base + ST * (kTile * 4) + 16 * h;
+            const uint32_t delta_t = delta_base + ST * (kTile * 4) + 16 * h;
             dkdv_tile(Qt, Qt + kTileBytes, nl2_t, delta_t, kreg, vreg, dk, dv, lo - qt - 4 * h, hi - qt - 4 * h,
                       qt < full_lo, qt + kTile > full_hi, p.c, lo_);
         }
         HMAR_WAIT_DMA_AND_BARRIER(0);
     };
-    for (int step = 0; step < nsteps; step += 2) {
-        tile_step(step, std::integral_constant<int, 0>{});
-        if (step + 1 >= nsteps) break;
-        tile_step(step + 1, std::integral_constant<int, 1>{});
+    for (int ti = 0; ti < ntiles; ti += 2) {
+        tile_step(ti, std::integral_constant<int, 0>{});
+        if (ti + 1 >= ntiles) break;
+        tile_step(ti + 1, std::integral_constant<int, 1>{});
     }
 
-    uint32_t patch = smem_base + rw * kPatchBytes;
-    if constexpr (KS > 1) {                  // the shares meet: the first adds up what the others bring
-        // both pairs of accumulators at once; the patch reuses the wavefront's own first part once it is read
-        constexpr int kPair = 2 * kPartBytes;
-        static_assert((KS - 1) * RW * kPair <= 2 * KS * kSlot && kPatchBytes <= kPair, "partial results fit the ring");
-        if (part > 0) {
-            const uint32_t at = smem_base + ((part - 1) * RW + rw) * kPair;
-            part_store(at, dk, lane);
-            part_store(at + kPartBytes, dv, lane);
-        }
-        HMAR_WAIT_DMA_AND_BARRIER(0);
-        if (part > 0) return;
-#pragma unroll
-        for (int g = 1; g < KS; ++g) {
-            const uint32_t at = smem_base + ((g - 1) * RW + rw) * kPair;
-            part_add(at, dk, lane, 1.0f, 1.0f);
-            part_add(at + kPartBytes, dv, lane, 1.0f, 1.0f);
-        }
-        patch = smem_base + rw * kPair;
-    }
     if (wave_active) {
+        const uint32_t patch = smem_base + wave * kPatchBytes;
         store_block_rows(patch, dk, p.sm_scale, p.dK + head_off, wk0, it.own_end - wk0, lane, nullptr, HMAR_NT_GRADS != 0);
         store_block_rows(patch, dv, 1.0f, p.dV + head_off, wk0, it.own_end - wk0, lane, nullptr, HMAR_NT_GRADS != 0);
     }
 }
 
-template <int RW, int KS>
-__global__ __launch_bounds__(64 * RW * KS) __attribute__((amdgpu_waves_per_eu(HMAR_DKDV_MIN_WAVES, HMAR_DKDV_MIN_WAVES))) void hmar_dkdv_kernel(BwdParams p) {
-    __shared__ __attribute__((aligned(1024))) char smem[2 * KS * 2 * kTileBytes];
-    __shared__ __attribute__((aligned(256))) float nl2_s[2 * KS][kTile];
-    __shared__ __attribute__((aligned(256))) float delta_s[2 * KS][kTile];
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_DKDV_MIN_WAVES, HMAR_DKDV_MIN_WAVES))) void hmar_dkdv_kernel(BwdParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[2 * 2 * kTileBytes];
+    __shared__ __attribute__((aligned(256))) float nl2_s[2][kTile];
+    __shared__ __attribute__((aligned(256))) float delta_s[2][kTile];
 #ifdef HMAR_TUNE_LDS_PAD_DKDV
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_DKDV)
 #endif
     int head, item_id;
     if (!map_workgroup(p.n_items, p.n_heads, p.tail_groups, &head, &item_id)) return;
-    Item it;
-    if (!split_item<RW>(p.items, item_id, &it)) return;
-    dkdv_body<RW, KS>(p, it, p.row_lo, p.row_hi, head, item_id, smem, nl2_s, delta_s);
+    dkdv_body(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem, nl2_s, delta_s);
 }
 
 #if defined(HMAR_BWD_MERGED)
@@ -488,15 +432,9 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
         p.items = static_cast<const Item*>(s.items[dir]);
         p.row_lo = s.row_lo[dir];
         p.row_hi = s.row_hi[dir];
-        const long long units = (long long)n_heads * s.n_items[dir];
-        Split split = dir == 1 ? choose_split_dkdv(units, s.max_tiles[dir], s.num_cus)
-                               : choose_split(units, s.max_tiles[dir], s.num_cus, true);
-#if HMAR_DKDV_KEYS_PER_WAVE == 16 || defined(HMAR_DKDV_PIPE) || defined(HMAR_DKDV_PERSIST)
-        if (dir == 1) split = {4, 1};        // the study kernels take whole items
-#endif
-        p.n_items = s.n_items[dir] * (4 / split.rw);
-        p.tail_groups = tail_groups_for(s.num_cus, p.n_items);
-        const unsigned groups = launch_groups(p.n_items, n_heads);
+        p.n_items = s.n_items[dir];
+        p.tail_groups = tail_groups_for(s.num_cus, s.n_items[dir]);
+        const unsigned groups = launch_groups(s.n_items[dir], n_heads);
         if (groups == 0) return hipErrorInvalidValue;
         const int kid = dir == 1 ? kKernelDkDv : kKernelDq;
         profile_before(kid, stream);
@@ -511,13 +449,9 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
                                p, (int)groups);
         }
 #else
-        if (dir == 1) with_split_dkdv(split, [&](auto rw, auto ks) {
-            hipLaunchKernelGGL((hmar_dkdv_kernel<rw(), ks()>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-        });
+        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
-        if (dir == 0) with_split(split, [&](auto rw, auto ks) {
-            hipLaunchKernelGGL((hmar_dq_kernel<rw(), ks()>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-        });
+        else          hipLaunchKernelGGL(hmar_dq_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
         const hipError_t e = hipGetLastError();
         profile_after(kid, stream);
         if (e != hipSuccess) return e;

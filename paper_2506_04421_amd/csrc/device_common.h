@@ -159,18 +159,6 @@ __device__ __forceinline__ bool map_workgroup(int n_items, int n_heads, int tail
     return map_unit(blockIdx.x, n_items, n_heads, tail_groups, head, item, reverse);
 }
 
-// The rows of unit `id` of a table of items of up to 128 rows, cut into 4 / RW units of 32 RW rows;
-// false if the item has no rows there.
-template <int RW>
-__device__ __forceinline__ bool split_item(const Item* items, int id, Item* it) {
-    *it = items[id / (4 / RW)];
-    if constexpr (RW < 4) {
-        it->own_begin += id % (4 / RW) * (RW * kRowsPerWave);
-        it->own_end = min(it->own_end, it->own_begin + RW * kRowsPerWave);
-    }
-    return it->own_begin < it->own_end;
-}
-
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -242,12 +230,6 @@ __device__ __forceinline__ LaneOffsets make_lane_offsets(int lane, int wave) {
     return o;
 }
 
-// The offsets of the operand reads (not of the DMA loads), moved by `bytes`.
-__device__ __forceinline__ void shift_lane_offsets(LaneOffsets& o, int bytes) {
-    o.row0 += bytes; o.row1 += bytes; o.row2 += bytes; o.row3 += bytes;
-    o.trA0 += bytes; o.trA1 += bytes; o.trB0 += bytes; o.trB1 += bytes;
-}
-
 // One global->LDS DMA load: every lane moves 16 (or 4) bytes from global address
 // sbase + voff (sbase uniform over the wavefront, voff a per-lane byte offset) to LDS address
 // lds_base + lane * 16 (or 4); lds_base must be uniform too (it goes through M0).  Written
@@ -282,28 +264,6 @@ __device__ __forceinline__ void dma_tile(const __bf16* base, int row0, int row_m
         const int r = 8 * wave + (lane >> 3), last = row_max - row0;
         dma16(sbase, min(r, last) * kRowBytes + o.dma_src, lds0);
         dma16(sbase, min(r + 32, last) * kRowBytes + o.dma_src, lds0 + 4096);
-    }
-}
-
-// The same tile moved by RW wavefronts (4 or 2; `wave` is this one's index among them): wavefront w
-// takes the 8-row blocks w, w + RW, ... of the first 32 rows and of the second.  The chunk permutation
-// depends on the block's parity only, so the lane's offset serves all of them.
-template <int RW>
-__device__ __forceinline__ void dma_tile_by(const __bf16* base, int row0, int row_max, uint32_t tile,
-                                            const LaneOffsets& o, int lane, int wave) {
-    static_assert(RW == 4 || RW == 2, "wavefronts that share a tile");
-    if constexpr (RW == 4) {
-        dma_tile(base, row0, row_max, tile, o, lane, wave);
-    } else {
-        const char* sbase = reinterpret_cast<const char*>(base) + (size_t)row0 * kRowBytes;
-        const uint32_t lds0 = __builtin_amdgcn_readfirstlane(tile + wave * 1024);
-        const bool full = row0 + kTile - 1 <= row_max;
-        const int r = 8 * wave + (lane >> 3), last = row_max - row0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {            // rows 16 b + r
-            if (full) dma16(sbase + b * 16 * kRowBytes, o.dma_voff, lds0 + b * 2048);
-            else dma16(sbase, min(r + 16 * b, last) * kRowBytes + o.dma_src, lds0 + b * 2048);
-        }
     }
 }
 
@@ -402,34 +362,6 @@ __device__ __forceinline__ void store_block_rows(uint32_t patch, const f32x16 (&
             else *reinterpret_cast<u32x4*>(out + (size_t)r * kD + chunk * 8) = v;
         }
     }
-}
-
-// ---- partial results of a split workgroup -------------------------------------------------
-// Where a workgroup's wavefronts share rows but not streamed tiles, the ones beyond the first group
-// leave their accumulators in LDS for the first to add up: 16-byte pieces, lane-contiguous, so that
-// both directions are free of bank conflicts.  kPartBytes per pair of accumulators.
-constexpr int kPartBytes = 32 * 64 * 4;
-typedef __attribute__((address_space(3))) f32x4 lds_f32x4_rw;
-typedef __attribute__((address_space(3))) float lds_float_rw;
-__device__ __forceinline__ void part_store(uint32_t at, const f32x16 (&acc)[2], int lane) {
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const f32x4 v = {acc[mb][4 * j], acc[mb][4 * j + 1], acc[mb][4 * j + 2], acc[mb][4 * j + 3]};
-            *(lds_f32x4_rw*)(at + (4 * mb + j) * 1024 + lane * 16) = v;
-        }
-}
-// acc = acc * own + part * other
-__device__ __forceinline__ void part_add(uint32_t at, f32x16 (&acc)[2], int lane, float own, float other) {
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const f32x4 v = *(lds_f32x4_rw*)(at + (4 * mb + j) * 1024 + lane * 16);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[mb][4 * j + r] = __builtin_fmaf(v[r], other, acc[mb][4 * j + r] * own);
-        }
 }
 
 }  // namespace hmar

@@ -1,8 +1,7 @@
 // Forward kernel of the Markovian next-scale attention (paper Sec. "Efficient Markovian
 // Next-Scale Prediction"; appendix "Efficient Attention Performance") for gfx950.
 //
-// One workgroup (4 wavefronts) owns up to 128 consecutive query rows, 32 per wavefront (launches too
-// small for that divide the key tiles among more wavefronts: choose_split in kernels.h),
+// One workgroup (4 wavefronts) owns up to 128 consecutive query rows, 32 per wavefront,
 // and streams the key/value rows of their two-scale windows through a two-stage ring of LDS
 // tiles (64 rows each) filled by global->LDS DMA loads that run one tile ahead.
 // Scores are computed transposed (S^T = K Q^T) so that a lane holds one query column:
@@ -170,14 +169,13 @@ __device__ __forceinline__ void small_step_unit(const StepParams& p, int head, i
     if (row0 + lr < n_q && h == 0) sd.LSE[(size_t)head * n_q + qrow] = (m_ref + log2f(l)) * kLn2;
 }
 
-// The pack item of a steps launch that has larger steps too: wavefront w takes the units w, w + WAVES, ...
-// of the workgroup's head.
-template <int WAVES>
+// The pack item of a steps launch that has larger steps too: wavefront w takes the units w, w + 4, ... of the
+// workgroup's head.
 __device__ __forceinline__ void small_steps_pack(const StepParams& p, int head, char* smem) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LaneOffsets lo_ = make_lane_offsets(threadIdx.x & 63, 0);
     const uint32_t Vt = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kTileBytes);
-    for (int u = wave; u < p.n_pack; u += WAVES) small_step_unit(p, head, p.pack_unit[u], Vt, lo_);
+    for (int u = wave; u < p.n_pack; u += 4) small_step_unit(p, head, p.pack_unit[u], Vt, lo_);
 }
 
 // A launch of small steps alone: every wavefront takes one unit of one head, the units of a head side by
@@ -197,11 +195,8 @@ __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_s
 
 // One body serves both launches: with STEPS the item, its buffers and its (trivial) pair ranges
 // come from the step descriptors, otherwise from the schedule tables.
-template <bool STEPS, int RW, int KS, bool LAZY, typename Params>
+template <bool STEPS, bool LAZY, typename Params>
 __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
-    constexpr int kRows = RW * kRowsPerWave;      // rows of the workgroup
-    constexpr int kStages = RW == 4 && KS == 1 ? kFwdStages : 2;
-    constexpr int kSlot = 2 * kTileBytes;         // a K tile followed by a V tile
     int head, item_id;
     if (!map_workgroup(p.n_items, p.n_heads, p.tail_groups, &head, &item_id)) return;
     Item it;
@@ -212,15 +207,15 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     const int32_t* row_lo = nullptr; const int32_t* row_hi = nullptr;
     if constexpr (STEPS) {
         if (p.n_pack > 0 && item_id == p.n_items - 1) {
-            small_steps_pack<RW * KS>(p, head, smem);
+            small_steps_pack(p, head, smem);
             return;
         }
         int si = 0;
         while (si + 1 < p.n_tiled && item_id >= p.step[si + 1].first_item) ++si;
         const StepDesc& sd = p.step[si];
         const int li = item_id - sd.first_item;
-        it.own_begin = li * kRows;
-        it.own_end = min(sd.n_q, it.own_begin + kRows);
+        it.own_begin = li * 128;
+        it.own_end = min(sd.n_q, it.own_begin + 128);
         it.other_begin = 0;
         it.other_end = sd.Lk;
         const size_t q_off = (size_t)head * sd.q_stride, q_in = (size_t)HMAR_INPUT_HEAD(head) * sd.q_stride;
@@ -230,7 +225,7 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
         rows = sd.rows;
         q_stride_rows = sd.q_stride;
     } else {
-        if (!split_item<RW>(p.items, item_id, &it)) return;
+        it = p.items[item_id];
         const size_t q_off = (size_t)head * p.L, q_in = (size_t)HMAR_INPUT_HEAD(head) * p.L;
         Qh = p.Q + q_in * kD; Oh = p.O + q_off * kD; LSEh = p.LSE + q_off;
         Kh = p.K + (size_t)HMAR_INPUT_HEAD(head) * p.Lk * kD;
@@ -238,32 +233,26 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
         row_lo = p.row_lo; row_hi = p.row_hi;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rw = KS > 1 ? wave % RW : wave, part = KS > 1 ? wave / RW : 0;      // the wavefront's 32 rows; its share of the tiles
     const int lr = lane & 31, h = lane >> 5;
-    LaneOffsets lo_ = make_lane_offsets(lane, rw);
-    if constexpr (KS > 1) shift_lane_offsets(lo_, part * kSlot);     // reads of the share's tiles: the rest is immediate
+    const LaneOffsets lo_ = make_lane_offsets(lane, wave);
     const uint32_t smem_base = lds_address(smem);
-    const uint32_t ring = smem_base + part * kSlot;  // stage st of this share: ring + st * KS * kSlot
 
     const int k_begin = it.other_begin, k_end = it.other_end, kmax = k_end - 1;
     const int ntiles = (k_end - k_begin + kTile - 1) / kTile;
-    const int nsteps = (ntiles + KS - 1) / KS;       // KS tiles per step, one per share
 
-    // 4 DMA loads per lane and tile (2 for K, 2 for V; 8 where two wavefronts share a tile); the first
-    // tile is requested before anything else so that its latency overlaps the rest of the prologue
-    auto issue = [&](int step, int st) {
-        const int ti = step * KS + part;
-        if (KS > 1 && ti >= ntiles) return;
-        const uint32_t stage = ring + st * (KS * kSlot);
-        dma_tile_by<RW>(Kh, k_begin + ti * kTile, kmax, stage, lo_, lane, rw);
-        dma_tile_by<RW>(Vh, k_begin + ti * kTile, kmax, stage + kTileBytes, lo_, lane, rw);
+    // 4 DMA loads per lane and tile (2 for K, 2 for V); the first tile is requested before
+    // anything else so that its latency overlaps the rest of the prologue
+    auto issue = [&](int ti, int st) {
+        const uint32_t stage = smem_base + st * (2 * kTileBytes);
+        dma_tile(Kh, k_begin + ti * kTile, kmax, stage, lo_, lane, wave);
+        dma_tile(Vh, k_begin + ti * kTile, kmax, stage + kTileBytes, lo_, lane, wave);
     };
     issue(0, 0);
 #pragma unroll
-    for (int d = 1; d < kStages - 1; ++d)
-        if (d < nsteps) issue(d, d);
+    for (int d = 1; d < kFwdStages - 1; ++d)
+        if (d < ntiles) issue(d, d);
 
-    const int wq0 = it.own_begin + rw * kRowsPerWave;
+    const int wq0 = it.own_begin + wave * kRowsPerWave;
     const bool wave_active = wq0 < it.own_end;               // uniform over the wavefront
     const bool row_valid = wq0 + lr < it.own_end;
     const int qrow = min(wq0 + lr, it.own_end - 1);
@@ -306,18 +295,18 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     // One tile: request the next one, compute, wait for the request.  The stage is a template
     // constant (the loop below alternates the two instantiations) so that every LDS address of
     // the step is a per-lane register plus an immediate offset.
-    auto tile_step = [&](const int step, auto stage_c) {
+    auto tile_step = [&](const int ti, auto stage_c) {
         constexpr int ST = decltype(stage_c)::value;
-        const int kt = k_begin + (step * KS + part) * kTile;
+        const int kt = k_begin + ti * kTile;
         // the tile requested now goes into the stage that every wavefront left at the last barrier
-        const bool ahead = step + kStages - 1 < nsteps;
-        if (ahead) issue(step + kStages - 1, (ST + kStages - 1) % kStages);
+        const bool ahead = ti + kFwdStages - 1 < ntiles;
+        if (ahead) issue(ti + kFwdStages - 1, (ST + kFwdStages - 1) % kFwdStages);
 #ifdef HMAR_TUNE_NO_COMPUTE_FWD
         if (false) {
 #else
-        if (wave_active && kt < whi && kt + kTile > wlo) {      // (whi <= k_end: a tile past the last is never entered)
+        if (wave_active && kt < whi && kt + kTile > wlo) {
 #endif
-            const uint32_t Kt = smem_base + ST * (KS * kSlot);
+            const uint32_t Kt = smem_base + ST * (2 * kTileBytes);
             const uint32_t Vt = Kt + kTileBytes;
             f32x16 s[2];
             auto scores = [&]() {
@@ -380,8 +369,7 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                 return sum;
             };
             if constexpr (LAZY) {
-                // in this share's first tile at or behind the one in which rows begin they have no reference yet
-                bool check = suspect || kt - (KS - 1) * kTile <= full_lo;
+                bool check = suspect || kt <= full_lo;      // up to the tile in which the last row begins
                 float sum;
 #pragma nounroll
                 while (true) {                              // at most twice
@@ -410,75 +398,47 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
         }
         // the next tile has landed (4 loads per lane and tile: the younger tiles may still be in
         // flight) and this one is free
-        if (kStages > 2 && ahead) { HMAR_WAIT_DMA_AND_BARRIER(4 * (kStages - 2)); }
-        else                      { HMAR_WAIT_DMA_AND_BARRIER(0); }
+        if (kFwdStages > 2 && ahead) { HMAR_WAIT_DMA_AND_BARRIER(4 * (kFwdStages - 2)); }
+        else                         { HMAR_WAIT_DMA_AND_BARRIER(0); }
     };
-    for (int step = 0; step < nsteps; step += kStages) {
-        tile_step(step, std::integral_constant<int, 0>{});
-        if (step + 1 >= nsteps) break;
-        tile_step(step + 1, std::integral_constant<int, 1>{});
-        if constexpr (kStages > 2) {
-            if (step + 2 >= nsteps) break;
-            tile_step(step + 2, std::integral_constant<int, 2>{});
+    for (int ti = 0; ti < ntiles; ti += kFwdStages) {
+        tile_step(ti, std::integral_constant<int, 0>{});
+        if (ti + 1 >= ntiles) break;
+        tile_step(ti + 1, std::integral_constant<int, 1>{});
+        if constexpr (kFwdStages > 2) {
+            if (ti + 2 >= ntiles) break;
+            tile_step(ti + 2, std::integral_constant<int, 2>{});
         }
-        if constexpr (kStages > 3) {
-            if (step + 3 >= nsteps) break;
-            tile_step(step + 3, std::integral_constant<int, 3>{});
+        if constexpr (kFwdStages > 3) {
+            if (ti + 3 >= ntiles) break;
+            tile_step(ti + 3, std::integral_constant<int, 3>{});
         }
     }
 
     // every wavefront has passed the last barrier: the ring is free and serves as the patch
     // through which the output block is turned into full rows
-    float l = half_sum(lsum);
-    uint32_t patch = smem_base + rw * kPatchBytes;
-    if constexpr (KS > 1) {
-        // The shares meet: each brings its accumulator, row sum and reference; the first one adds them up
-        // relative to the largest reference (a share that met no key of a row brings 0 and kNegBig).
-        constexpr int kParts = (KS - 1) * RW;
-        static_assert(kParts * (kPartBytes + 512) + RW * kPatchBytes <= 2 * KS * kSlot, "partial results and patches fit the ring");
-        const uint32_t stats = smem_base + kParts * kPartBytes;
-        patch = stats + kParts * 512 + rw * kPatchBytes;
-        if (part > 0) {
-            const int u = (part - 1) * RW + rw;
-            part_store(smem_base + u * kPartBytes, o, lane);
-            *(lds_float_rw*)(stats + u * 512 + lane * 4) = m_ref;
-            *(lds_float_rw*)(stats + u * 512 + 256 + lane * 4) = l;
-        }
-        HMAR_WAIT_DMA_AND_BARRIER(0);
-        if (part > 0) return;
-#pragma unroll
-        for (int g = 1; g < KS; ++g) {
-            const int u = (g - 1) * RW + rw;
-            const float m_g = *(lds_float_rw*)(stats + u * 512 + lane * 4), l_g = *(lds_float_rw*)(stats + u * 512 + 256 + lane * 4);
-            const float m_new = fmaxf(m_ref, m_g);
-            const float own = __builtin_amdgcn_exp2f(m_ref - m_new), other = __builtin_amdgcn_exp2f(m_g - m_new);
-            part_add(smem_base + u * kPartBytes, o, lane, own, other);
-            l = __builtin_fmaf(l_g, other, l * own);
-            m_ref = m_new;
-        }
-    }
     if (wave_active) {
-        store_block_rows(patch, o, 1.0f / l, Oh, wq0, it.own_end - wq0, lane, rows, HMAR_NT_O != 0,
+        const float l = half_sum(lsum);
+        store_block_rows(smem_base + wave * kPatchBytes, o, 1.0f / l, Oh, wq0, it.own_end - wq0, lane, rows, HMAR_NT_O != 0,
                          q_rows_per_head);
         if (row_valid && h == 0) LSEh[qrow_mem] = (m_ref + log2f(l)) * kLn2;
     }
 }
 
-// RW wavefronts own 32 rows each, KS sets of them share the tiles (see choose_split)
-template <int RW, int KS, bool LAZY>
-__global__ __launch_bounds__(64 * RW * KS, HMAR_FWD_MIN_WAVES) void hmar_fwd_kernel(FwdParams p) {
-    // ring of stages, each KS times a K tile followed by a V tile
-    __shared__ __attribute__((aligned(1024))) char smem[(RW == 4 && KS == 1 ? kFwdStages : 2) * KS * 2 * kTileBytes];
+template <bool LAZY>
+__global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_kernel(FwdParams p) {
+    // ring of stages, each a K tile followed by a V tile
+    __shared__ __attribute__((aligned(1024))) char smem[kFwdStages * 2 * kTileBytes];
 #ifdef HMAR_TUNE_LDS_PAD_FWD
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_FWD)
 #endif
-    fwd_body<false, RW, KS, LAZY>(p, smem);
+    fwd_body<false, LAZY>(p, smem);
 }
 
-template <int RW, int KS, bool LAZY>
-__global__ __launch_bounds__(64 * RW * KS, HMAR_FWD_MIN_WAVES) void hmar_fwd_steps_kernel(StepParams p) {
-    __shared__ __attribute__((aligned(1024))) char smem[(RW == 4 && KS == 1 ? kFwdStages : 2) * KS * 2 * kTileBytes];
-    fwd_body<true, RW, KS, LAZY>(p, smem);
+template <bool LAZY>
+__global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_steps_kernel(StepParams p) {
+    __shared__ __attribute__((aligned(1024))) char smem[kFwdStages * 2 * kTileBytes];
+    fwd_body<true, LAZY>(p, smem);
 }
 
 #ifdef HMAR_TUNE_FWD_STUDY
@@ -509,12 +469,7 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     p.items = static_cast<const Item*>(s.items[0]);
     p.row_lo = s.row_lo[0];
     p.row_hi = s.row_hi[0];
-#ifdef HMAR_TUNE_FWD_STUDY
-    const Split split = {4, 1};              // the study kernel takes whole items
-#else
-    const Split split = choose_split((long long)n_heads * s.n_items[0], s.max_tiles[0], s.num_cus, false);
-#endif
-    p.n_items = s.n_items[0] * (4 / split.rw);
+    p.n_items = s.n_items[0];
     p.n_heads = n_heads;
     p.tail_groups = tail_groups_for(s.num_cus, p.n_items);
     p.L = s.L;
@@ -527,15 +482,8 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
                        dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
-    with_split(split, [&](auto rw, auto ks) {
-        // {4, 4} is for long streams only
-        if constexpr (rw() == 4 && ks() == 4)
-            hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-        else if (s.max_tiles[0] >= kLongStream)
-            hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-        else
-            hipLaunchKernelGGL((hmar_fwd_kernel<rw(), ks(), false>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-    });
+    const auto kernel = s.max_tiles[0] >= kLongStream ? hmar_fwd_kernel<true> : hmar_fwd_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
     const hipError_t e = hipGetLastError();
     profile_after(kKernelFwd, stream);
@@ -551,15 +499,7 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     for (int i = 0; i < L.n_steps; ++i) if (!packed(L.step[i])) order[n++] = i;
     p.n_tiled = n;
     for (int i = 0; i < L.n_steps; ++i) if (packed(L.step[i])) order[n++] = i;
-    long long blocks128 = 0;             // 128-row items of the launch, the pack among them
-    int max_tiles = 1;
-    for (int i = 0; i < p.n_tiled; ++i) {
-        blocks128 += (L.step[order[i]].n_q + 127) / 128;
-        max_tiles = std::max(max_tiles, (L.step[order[i]].Lk + kTile - 1) / kTile);
-    }
-    const Split split = choose_split((blocks128 + (p.n_tiled < L.n_steps)) * n_heads, max_tiles, num_cus, false);
-    const int rows_per_item = split.rw * kRowsPerWave;
-    int items = 0;
+    int items = 0, max_tiles = 0;
     p.n_pack = 0;
     for (int i = 0; i < L.n_steps; ++i) {
         const StepLaunch::Step& a = L.step[order[i]];
@@ -576,7 +516,8 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
         d.Lk = a.Lk;
         d.first_item = items;
         if (i < p.n_tiled) {
-            items += (a.n_q + rows_per_item - 1) / rows_per_item;
+            items += (a.n_q + 127) / 128;
+            max_tiles = std::max(max_tiles, (a.Lk + kTile - 1) / kTile);
         } else {
             for (int blk = 0; 32 * blk < a.n_q; ++blk)         // at most two: n_q <= Lk <= 64
                 p.pack_unit[p.n_pack++] = 2 * i + blk;
@@ -595,15 +536,10 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     if (p.n_tiled == 0) {
         const unsigned units = (unsigned)n_heads * (unsigned)p.n_pack;      // at most 2^24 * 32
         hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((units + 3) / 4), dim3(kThreads), 0, stream, p);
-    } else with_split(split, [&](auto rw, auto ks) {
-        // {4, 4} is for long streams only
-        if constexpr (rw() == 4 && ks() == 4)
-            hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-        else if (max_tiles >= kLongStream)
-            hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), true>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-        else
-            hipLaunchKernelGGL((hmar_fwd_steps_kernel<rw(), ks(), false>), dim3(groups), dim3(64 * rw() * ks()), 0, stream, p);
-    });
+    } else {
+        const auto kernel = max_tiles >= kLongStream ? hmar_fwd_steps_kernel<true> : hmar_fwd_steps_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
+    }
     const hipError_t e = hipGetLastError();
     profile_after(kKernelFwd, stream);
     return e;

@@ -758,3 +758,56 @@ def test_maxima_left_out_on_long_streams_change_no_bits(p, c, factor):
     O, LSE = hm.hmar_attn_step_fwd(q, k, v, p)
     Os, LSEs = hm.hmar_attn_steps_fwd([q, long[0]], [k, long[1]], [v, long[2]], [p, 1471])
     assert torch.isfinite(O.float()).all() and torch.equal(O, Os[0]) and torch.equal(LSE, LSEs[0])
+
+
+def _whole_call(q, k, v, g, sides):
+    O, LSE = hm.hmar_attn_fwd(q, k, v, sides)
+    return (O, LSE) + tuple(hm.hmar_attn_bwd(q, k, v, O, g, LSE, sides))
+
+
+@pytest.mark.parametrize("sides,B,few", [
+    (si.SIDES_256, 80, (1, 17, 35, 55)),       # 7 items a head, 9 tiles: launches of 7 to 385 units
+    ((17, 20), 80, (1, 6, 30)),                # 7 items, 11 tiles
+    ((3, 23, 25), 60, (1, 11, 25, 45)),        # 11 items, 19 tiles
+    (si.SIDES_512, 30, (1, 7, 15, 25)),        # 20 items, 25 tiles
+    ((39, 41), 24, (1, 5, 10, 18))])           # 27 items, 51 tiles
+def test_results_do_not_depend_on_the_batch(sides, B, few):
+    # a fixed summation order per schedule: the first images of a batch that fills the chip give, computed by
+    # themselves, the bits they have in the batch
+    d, L = _dev(), sum(s * s for s in sides)
+    q, k, v, g = (t.to(d) for t in si.draw((B, 1, L, 64), seed=1700 + L, n_tensors=4))
+    whole = _whole_call(q, k, v, g, sides)
+    for n in few:
+        for name, a, b in zip(("O", "LSE", "dQ", "dK", "dV"), _whole_call(q[:n], k[:n], v[:n], g[:n], sides), whole):
+            assert torch.equal(a, b[:n]), (name, n)
+        if n * L <= 1 << 20:
+            out = [torch.full_like(q[:n], float("nan")) for _ in range(3)]
+            hm.hmar_attn_bwd_noalloc(q[:n], k[:n], v[:n], whole[0][:n], g[:n], whole[1][:n], sides, *out)
+            for name, a, b in zip(("dQ", "dK", "dV"), out, whole[2:]):
+                assert torch.equal(a, b[:n]), (name, n, "noalloc")
+
+
+@pytest.mark.parametrize("B", [1, 2, 5, 12])
+def test_steps_do_not_depend_on_the_batch_or_on_the_steps_beside_them(B):
+    # every step of a call has the bits it has alone, and each image those it has in a batch that fills the chip
+    d, H = _dev(), 24
+    shapes = [(4, 9), (100, 169), (169, 256), (324, 576), (576, 1024), (900, 150)]
+    g = torch.Generator(device="cpu")
+    g.manual_seed(1800)
+    draw = lambda n: torch.randn((24, H, n, 64), generator=g).to(torch.bfloat16).to(d)
+    q = [draw(c) for _, c in shapes]
+    k, v = ([draw(p + c) for p, c in shapes] for _ in range(2))
+    n_prev = [p for p, _ in shapes]
+    whole = hm.hmar_attn_steps_fwd(q, k, v, n_prev)
+    first = lambda ts: [t[:B] for t in ts]
+    some = hm.hmar_attn_steps_fwd(first(q), first(k), first(v), n_prev)
+    for i, p in enumerate(n_prev):
+        O, LSE = hm.hmar_attn_step_fwd(q[i][:B], k[i][:B], v[i][:B], p)
+        for o, lse in ((some[0][i], some[1][i]), (whole[0][i][:B], whole[1][i][:B])):
+            assert torch.equal(O, o) and torch.equal(LSE, lse), shapes[i]
+        rows = torch.arange(0, shapes[i][1], 3, dtype=torch.int32, device=d)
+        listed = []
+        for n in (B, 24):
+            O, LSE = torch.zeros_like(q[i][:n]), torch.zeros_like(whole[1][i][:n])
+            listed.append(hm.hmar_attn_step_fwd_rows(q[i][:n], k[i][:n], v[i][:n], p, rows, O, LSE))
+        assert torch.equal(listed[0][0], listed[1][0][:B]) and torch.equal(listed[0][1], listed[1][1][:B]), shapes[i]
