@@ -30,8 +30,8 @@ struct BwdParams {
     float* neg_delta;        // -Delta: likewise
     __bf16* dQ; __bf16* dK; __bf16* dV;
     const Item* items; const int32_t* row_lo; const int32_t* row_hi;
-    int n_items, n_heads, L;
-    int tail_groups;  // see map_workgroup
+    UnitMap map;
+    int L;
     float c;          // sm_scale * log2(e)
     float sm_scale;
 };
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kThreads, HMAR_DQ_MIN_WAVES) void hmar_dq_kernel(Bw
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_DQ)
 #endif
     int head, item_id;
-    if (!map_workgroup(p.n_items, p.n_heads, p.tail_groups, &head, &item_id, true)) return;
+    map_workgroup(p.map, &head, &item_id, true);
     dq_body<true>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem);
 }
 
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_D
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_DKDV)
 #endif
     int head, item_id;
-    if (!map_workgroup(p.n_items, p.n_heads, p.tail_groups, &head, &item_id)) return;
+    map_workgroup(p.map, &head, &item_id);
     dkdv_body(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem, nl2_s, delta_s);
 }
 
@@ -419,7 +419,6 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
     p.dQ = static_cast<__bf16*>(dQ);
     p.dK = static_cast<__bf16*>(dK);
     p.dV = static_cast<__bf16*>(dV);
-    p.n_heads = n_heads;
     p.L = s.L;
     p.c = sm_scale * kLog2e;
     p.sm_scale = sm_scale;
@@ -432,10 +431,9 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
         p.items = static_cast<const Item*>(s.items[dir]);
         p.row_lo = s.row_lo[dir];
         p.row_hi = s.row_hi[dir];
-        p.n_items = s.n_items[dir];
-        p.tail_groups = tail_groups_for(s.num_cus, s.n_items[dir]);
         const unsigned groups = launch_groups(s.n_items[dir], n_heads);
         if (groups == 0) return hipErrorInvalidValue;
+        p.map = unit_map_for(s.num_cus, s.n_items[dir], n_heads);
         const int kid = dir == 1 ? kKernelDkDv : kKernelDq;
         profile_before(kid, stream);
 #if HMAR_DKDV_KEYS_PER_WAVE == 16

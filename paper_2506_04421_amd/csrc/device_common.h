@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels.h"
+
 namespace hmar {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -118,45 +120,44 @@ typedef const __attribute__((address_space(1))) void global_void;
 //    heaviest items, then the next, ...): the launch then ends on the lightest items, and the
 //    period in which the device drains is as short as those.  The batch is sized to about one
 //    round of resident workgroups, small enough for its heads' K and V to share the L2.
-//  - The n_heads % 8 heads that fill no group are walked with that batch, their items dealt out to
-//    all XCDs: unit u = item * rest + head goes to XCD u % 8, behind the batch's units of that item.
-//    Their rows are fetched by several L2s, but no XCD works on a head while others have none:
-//    12 heads of the 8640-token schedule take 140 / 182 / 241 us (forward / dQ / dK,dV), with one XCD
-//    for each of the last four heads 159 / 214 / 278; one head 100 / 107 / 111 against 101 / 118 / 127; at
-//    2240 tokens and below, where launches are short, +-2 %.
+//  - The n_heads % 8 heads that fill no group are walked with that batch, the units of an item behind those of the
+//    batch's groups, so that they are dealt out to all XCDs: their rows are fetched by several L2s, but no XCD
+//    works on a head while others have none.  Against an XCD for each of them (forward / dK,dV / dQ in us): 12 heads
+//    of 8640 tokens 169 / 277 / 213 -> 140 / 239 / 177, 100 heads of 680 tokens 14.6 / 22.4 / 18.1 -> 14.4 / 21.5 / 17.3,
+//    12 heads of 2240 tokens 26.7 / 34.6 / 33.7 -> 26.2 / 32.8 / 29.7; the worst seen is one kernel of 3090 tokens, 12
+//    heads: dK,dV 62.8 -> 66.
 //  - With `reverse` the groups are walked from the last to the first: a kernel that follows
 //    another one over the same tensors then starts on the heads that kernel touched last,
 //    which are the ones still in the last-level cache.
-// The launch holds launch_groups(n_items, n_heads) workgroups (csrc/kernels.h); false: no work.
-__device__ __forceinline__ bool map_unit(int wg, int n_items, int n_heads, int tail_groups, int* head, int* item,
-                                         bool reverse = false) {
-    const int xcd = wg & 7, slot = wg >> 3;
-    const int n_groups = n_heads >> 3, rest = n_heads & 7;
-    const int tail = min(max(tail_groups, 1), n_groups);
-    const int head_major = (n_groups - tail) * n_items;       // slots before the tail batch
-    int group = -1, it;
-    if (slot < head_major) {
-        group = slot / n_items;
-        it = slot % n_items;
-    } else {
-        const int s2 = slot - head_major;
-        // slots of this XCD before item i of the batch: its groups' and its share of the other heads'
-        auto before = [&](int i) { return i * tail + ((i * rest + 7 - xcd) >> 3); };
-        if (s2 >= before(n_items)) return false;
-        it = min(8 * s2 / (8 * tail + rest), n_items - 1);
-        while (before(it) > s2) --it;
-        while (before(it + 1) <= s2) ++it;
-        const int at = s2 - before(it);
-        if (at < tail) group = n_groups - tail + at;
-        else *head = 8 * n_groups + ((xcd - it * rest) & 7);
-    }
-    *item = it;
-    if (group >= 0) *head = (reverse ? n_groups - 1 - group : group) * 8 + xcd;
-    return true;
+// The launch holds exactly launch_groups(...) workgroups (csrc/kernels.h).  All of this precedes a workgroup's first
+// load, and the code is fetched anew by every launch: the host hands over what does not depend on the workgroup and
+// inverses of the two divisors, which took the three kernels of a 4-head launch of 680 tokens from 11.97 / 13.80 /
+// 14.04 us with integer divisions to 11.50 / 13.34 / 13.15.
+__device__ __forceinline__ int divide(int n, int d, uint32_t inverse) {       // n / d, 0 <= n; see inverse_of
+    const int q = (int)__umulhi((uint32_t)n, inverse);
+    return q + (n - q * d >= d ? 1 : 0);
 }
-__device__ __forceinline__ bool map_workgroup(int n_items, int n_heads, int tail_groups, int* head, int* item,
-                                              bool reverse = false) {
-    return map_unit(blockIdx.x, n_items, n_heads, tail_groups, head, item, reverse);
+__device__ __forceinline__ void map_unit(int wg, const UnitMap& m, int* head, int* item, bool reverse = false) {
+    const int xcd = wg & 7;
+    bool grouped = true;
+    int h, it;
+    if (wg < m.head_major) {
+        const int slot = wg >> 3, group = divide(slot, m.n_items, m.inv_items);
+        it = slot - group * m.n_items;
+        h = 8 * group + xcd;
+    } else {
+        const int u = wg - m.head_major;
+        it = divide(u, m.batch, m.inv_batch);
+        const int r = u - it * m.batch;
+        grouped = r < m.batch_grouped;
+        h = m.batch_head + (grouped ? (r & ~7) + xcd : r);
+    }
+    if (reverse && grouped) h = m.last_group_head - (h & ~7) + xcd;
+    *head = h;
+    *item = it;
+}
+__device__ __forceinline__ void map_workgroup(const UnitMap& m, int* head, int* item, bool reverse = false) {
+    map_unit(blockIdx.x, m, head, item, reverse);
 }
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {

@@ -22,8 +22,7 @@ struct FwdParams {
     const __bf16* Q; const __bf16* K; const __bf16* V;
     __bf16* O; float* LSE;
     const Item* items; const int32_t* row_lo; const int32_t* row_hi;
-    int n_items, n_heads;
-    int tail_groups;   // see map_workgroup
+    UnitMap map;
     int L, Lk;   // rows per head of Q/O/LSE and of K/V
     float c;   // sm_scale * log2(e): scores are exponentiated in base 2
 };
@@ -49,7 +48,8 @@ struct StepDesc {
 constexpr int kMaxPackUnits = 2 * kMaxSteps;
 struct StepParams {
     StepDesc step[kMaxSteps];   // the n_tiled steps that get items of their own, then the packed ones
-    int n_tiled, n_items, n_heads, tail_groups;
+    UnitMap map;
+    int n_tiled, n_heads;
     int n_pack;                 // units of the pack (0: the launch has no pack item)
     int pack_unit[kMaxPackUnits];
     float c;
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_s
 template <bool STEPS, bool LAZY, typename Params>
 __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     int head, item_id;
-    if (!map_workgroup(p.n_items, p.n_heads, p.tail_groups, &head, &item_id)) return;
+    map_workgroup(p.map, &head, &item_id);
     Item it;
     const __bf16* Qh; const __bf16* Kh; const __bf16* Vh;
     __bf16* Oh; float* LSEh;
@@ -206,7 +206,7 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     int q_stride_rows = 0;            // rows per head of those buffers (steps)
     const int32_t* row_lo = nullptr; const int32_t* row_hi = nullptr;
     if constexpr (STEPS) {
-        if (p.n_pack > 0 && item_id == p.n_items - 1) {
+        if (p.n_pack > 0 && item_id == p.map.n_items - 1) {
             small_steps_pack(p, head, smem);
             return;
         }
@@ -469,14 +469,12 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     p.items = static_cast<const Item*>(s.items[0]);
     p.row_lo = s.row_lo[0];
     p.row_hi = s.row_hi[0];
-    p.n_items = s.n_items[0];
-    p.n_heads = n_heads;
-    p.tail_groups = tail_groups_for(s.num_cus, p.n_items);
     p.L = s.L;
     p.Lk = s.Lk;
     p.c = sm_scale * kLog2e;
-    const unsigned groups = launch_groups(p.n_items, n_heads);
+    const unsigned groups = launch_groups(s.n_items[0], n_heads);
     if (groups == 0) return hipErrorInvalidValue;
+    p.map = unit_map_for(s.num_cus, s.n_items[0], n_heads);
     profile_before(kKernelFwd, stream);
 #ifdef HMAR_TUNE_FWD_STUDY
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
@@ -526,12 +524,11 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     if (p.n_pack > 0) ++items;                                  // the pack is the launch's last item
     for (int i = L.n_steps; i < kMaxSteps; ++i) p.step[i] = p.step[0];
     for (int u = p.n_pack; u < kMaxPackUnits; ++u) p.pack_unit[u] = 0;
-    p.n_items = items;
     p.n_heads = n_heads;
-    p.tail_groups = tail_groups_for(num_cus, items);
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(items, n_heads);
     if (groups == 0) return hipErrorInvalidValue;
+    p.map = unit_map_for(num_cus, items, n_heads);
     profile_before(kKernelFwd, stream);
     if (p.n_tiled == 0) {
         const unsigned units = (unsigned)n_heads * (unsigned)p.n_pack;      // at most 2^24 * 32

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace hmar {
 
 // Device copy of the tile schedule of one (device, scale schedule) pair.
@@ -31,11 +33,30 @@ inline int tail_groups_for(int num_cus, int n_items) {
     return g < 1 ? 1 : g;
 }
 
-// Workgroups of a launch over n_items items of each head (see map_unit), or 0 if they would be too many
-// for a grid.
+// The inverse by which divide() (csrc/device_common.h) divides by d: the quotient from the high half of a product is
+// at most one too small for every n below 2^31.
+inline uint32_t inverse_of(int d) { return d > 1 ? (uint32_t)((1ull << 32) / (unsigned)d) : 0xffffffffu; }
+
+// The order in which the workgroups of a launch take its (head, item) units (see map_unit).
+struct UnitMap {
+    int n_items;
+    int head_major;            // workgroups before the batch that ends the launch
+    int batch_head;            // first head of the batch
+    int batch, batch_grouped;  // its heads, and those of them that fill groups of eight
+    int last_group_head;       // first head of the last group
+    uint32_t inv_items, inv_batch;
+};
+inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads) {
+    const int n_groups = n_heads / 8, tail = std::min(tail_groups_for(num_cus, n_items), n_groups);
+    const int batch = 8 * tail + n_heads % 8;
+    return {n_items, 8 * (n_groups - tail) * n_items, 8 * (n_groups - tail), batch, 8 * tail, 8 * (n_groups - 1),
+            inverse_of(n_items), inverse_of(batch)};
+}
+
+// Workgroups of a launch over n_items items of each head, or 0 if they would be too many for a grid.
 inline unsigned launch_groups(int n_items, int n_heads) {
     if (n_items < 1 || n_heads < 1 || 8LL * ((n_heads + 7LL) / 8) * n_items > 0x7fffffffLL) return 0;
-    return 8u * ((unsigned)(n_heads / 8) * (unsigned)n_items + ((unsigned)(n_heads % 8) * (unsigned)n_items + 7) / 8);
+    return (unsigned)n_items * (unsigned)n_heads;
 }
 
 // Streams of this many tiles and more leave the maxima of most tiles out (csrc/fwd.hip).

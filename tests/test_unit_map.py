@@ -1,0 +1,85 @@
+"""The order in which a launch's workgroups take its (head, item) units: map_unit of csrc/device_common.h with the
+host's table, compiled for the CPU as it stands in the sources."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_04421_amd", "csrc")
+CUS = 256
+
+PROGRAM = """
+#include "kernels.h"
+#define __device__
+#define __forceinline__ inline
+static inline uint32_t __umulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
+namespace hmar {
+%s
+}
+extern "C" unsigned units(int n_items, int n_heads, int cus, int reverse, int* head, int* item) {
+    const unsigned n = hmar::launch_groups(n_items, n_heads);
+    if (!head) return n;
+    const hmar::UnitMap m = hmar::unit_map_for(cus, n_items, n_heads);
+    for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
+    return n;
+}
+extern "C" int quotient(int n, int d) { return hmar::divide(n, d, hmar::inverse_of(d)); }
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("unit_map")
+    text = open(os.path.join(CSRC, "device_common.h")).read()
+    begin = text.index("__device__ __forceinline__ int divide(")
+    (d / "hip").mkdir()
+    (d / "hip" / "hip_runtime.h").write_text("#pragma once\n#include <cstddef>\ntypedef int hipError_t; typedef void* hipStream_t;\n")
+    (d / "map.cpp").write_text(PROGRAM % text[begin:text.index("__device__ __forceinline__ void map_workgroup(")])
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", str(d), "-I", CSRC, str(d / "map.cpp"),
+           "-o", str(d / "map.so")]
+    subprocess.run(cmd, check=True)
+    return ctypes.CDLL(str(d / "map.so"))
+
+
+def _units(lib, n_items, n_heads, reverse=False):
+    n = lib.units(n_items, n_heads, CUS, 0, None, None)
+    head, item = np.zeros(n, np.int32), np.zeros(n, np.int32)
+    p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
+    lib.units(n_items, n_heads, CUS, int(reverse), p(head), p(item))
+    return head, item
+
+
+@pytest.mark.parametrize("reverse", [False, True])
+@pytest.mark.parametrize("n_items", [1, 2, 3, 5, 7, 8, 20, 70, 255, 256, 257, 1000])
+def test_every_unit_has_one_workgroup(lib, n_items, reverse):
+    for n_heads in list(range(1, 42)) + [48, 63, 100, 104, 107, 768, 1023, 1536]:
+        head, item = _units(lib, n_items, n_heads, reverse)
+        assert len(head) == n_items * n_heads
+        assert head.min() >= 0 and head.max() < n_heads and item.min() >= 0 and item.max() < n_items
+        assert np.bincount(head.astype(np.int64) * n_items + item, minlength=n_items * n_heads).max() == 1
+        # a head of a whole group keeps to the XCD of its number
+        xcd, grouped = np.arange(len(head)) % 8, head < n_heads // 8 * 8
+        assert (head[grouped] % 8 == xcd[grouped]).all()
+
+
+@pytest.mark.parametrize("n_items,n_heads", [(7, 768), (20, 192), (7, 256), (1, 1536), (70, 48), (300, 16)])
+def test_whole_groups_are_walked_head_by_head_and_the_last_batch_item_by_item(lib, n_items, n_heads):
+    groups = n_heads // 8
+    tail = min(max(CUS // n_items, 1), groups)
+    for reverse in (False, True):
+        head, item = _units(lib, n_items, n_heads, reverse)
+        slot, xcd = np.arange(len(head)) // 8, np.arange(len(head)) % 8
+        first = (groups - tail) * n_items
+        group = np.where(slot < first, slot // n_items, groups - tail + (slot - first) % tail)
+        assert (item == np.where(slot < first, slot % n_items, (slot - first) // tail)).all()
+        assert (head == (groups - 1 - group if reverse else group) * 8 + xcd).all()
+
+
+def test_quotients_by_the_inverse(lib):
+    rng = np.random.default_rng(1)
+    for d in [1, 2, 3, 7, 8, 255, 256, 641, 16384] + rng.integers(1, 1 << 20, 50).tolist():
+        for n in [0, 1, d - 1, d, d + 1, 5 * d - 1, 5 * d, (1 << 31) - 1, (1 << 31) - 1 - (1 << 31) % d] + rng.integers(0, 1 << 31, 50).tolist():
+            assert lib.quotient(int(n), int(d)) == n // d, (n, d)
