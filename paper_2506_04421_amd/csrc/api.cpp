@@ -81,9 +81,6 @@ void pack_tables(const Schedule& s, unsigned char* staging, unsigned char* base,
         std::memcpy(staging + o, s.items[d].data(), bytes);
         dev->items[d] = base + o;
         dev->n_items[d] = (int32_t)s.items[d].size();
-        dev->max_tiles[d] = 0;
-        for (const TileItem& it : s.items[d])
-            dev->max_tiles[d] = std::max(dev->max_tiles[d], (it.other_end - it.other_begin + 63) / 64);
         o += bytes;
     }
     for (int d = 0; d < 2; ++d) {
@@ -93,6 +90,13 @@ void pack_tables(const Schedule& s, unsigned char* staging, unsigned char* base,
         std::memcpy(staging + o, s.row_hi[d].data(), L * 4);
         dev->row_hi[d] = reinterpret_cast<const int32_t*>(base + o);
         o += L * 4;
+    }
+    dev->max_tiles = 0;
+    dev->total_tiles = 0;
+    for (const TileItem& it : s.items[0]) {
+        const int32_t tiles = (it.other_end - it.other_begin + 63) / 64;
+        dev->max_tiles = std::max(dev->max_tiles, tiles);
+        dev->total_tiles += tiles;
     }
     dev->L = s.L;
     dev->Lk = s.Lk;

@@ -58,11 +58,12 @@ struct StepParams {
 // Softmax reference.  Probabilities are formed against a row's reference maximum and are at most 2^8,
 // which fp32 sums and bf16 operands hold without loss.  The reference is raised when a tile's maximum exceeds
 // it by more than eight binades.
-// Long streams (LAZY) do not take the maximum of every tile: past the tiles in which the rows' keys begin, a tile is
-// exponentiated at once, and only if a lane's sum over it comes out above 2^7 are its scores formed again
-// and put to that rule; from then on the wavefront takes every maximum first.  A score more than eight binades
-// above the reference makes a probability of 2^8 and more, which no rounding of the sum (below 2^27: 2^19 keys of at
-// most 2^8) can bring under 2^7, so the references, and with them all results, are bit for bit those of the plain form.
+// Launches of long streams (LAZY; see leaves_maxima_out) do not take the maximum of every tile: past the tiles in
+// which the rows' keys begin, a tile is exponentiated at once, and only if a lane's sum over it comes out above 2^7 are
+// its scores formed again and put to that rule; from then on the wavefront takes every maximum first.  A score more
+// than eight binades above the reference makes a probability of 2^8 and more, which no rounding of the sum (below
+// 2^27: 2^19 keys of at most 2^8) can bring under 2^7, so the references, and with them all results, are bit for bit
+// those of the plain form.
 constexpr float kRescaleThreshold = 8.0f;
 constexpr float kSuspectTileSum = 128.0f;
 
@@ -480,7 +481,8 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
                        dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
-    const auto kernel = s.max_tiles[0] >= kLongStream ? hmar_fwd_kernel<true> : hmar_fwd_kernel<false>;
+    const auto kernel = leaves_maxima_out(s.max_tiles, s.total_tiles, n_heads, s.num_cus) ? hmar_fwd_kernel<true>
+                                                                                          : hmar_fwd_kernel<false>;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
     const hipError_t e = hipGetLastError();
@@ -498,6 +500,7 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     p.n_tiled = n;
     for (int i = 0; i < L.n_steps; ++i) if (packed(L.step[i])) order[n++] = i;
     int items = 0, max_tiles = 0;
+    long long total_tiles = 0;
     p.n_pack = 0;
     for (int i = 0; i < L.n_steps; ++i) {
         const StepLaunch::Step& a = L.step[order[i]];
@@ -514,8 +517,10 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
         d.Lk = a.Lk;
         d.first_item = items;
         if (i < p.n_tiled) {
-            items += (a.n_q + 127) / 128;
-            max_tiles = std::max(max_tiles, (a.Lk + kTile - 1) / kTile);
+            const int step_items = (a.n_q + 127) / 128, tiles = (a.Lk + kTile - 1) / kTile;
+            items += step_items;
+            max_tiles = std::max(max_tiles, tiles);
+            total_tiles += (long long)step_items * tiles;
         } else {
             for (int blk = 0; 32 * blk < a.n_q; ++blk)         // at most two: n_q <= Lk <= 64
                 p.pack_unit[p.n_pack++] = 2 * i + blk;
@@ -534,7 +539,8 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
         const unsigned units = (unsigned)n_heads * (unsigned)p.n_pack;      // at most 2^24 * 32
         hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((units + 3) / 4), dim3(kThreads), 0, stream, p);
     } else {
-        const auto kernel = max_tiles >= kLongStream ? hmar_fwd_steps_kernel<true> : hmar_fwd_steps_kernel<false>;
+        const auto kernel = leaves_maxima_out(max_tiles, total_tiles, n_heads, num_cus) ? hmar_fwd_steps_kernel<true>
+                                                                                        : hmar_fwd_steps_kernel<false>;
         hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
     }
     const hipError_t e = hipGetLastError();

@@ -11,7 +11,8 @@ namespace hmar {
 struct DeviceSchedule {
     const void* items[2];      // Item[n_items[dir]]
     int32_t n_items[2];
-    int32_t max_tiles[2];      // streamed 64-row tiles of the longest item
+    int32_t max_tiles;         // streamed 64-row tiles of the forward's longest item
+    int64_t total_tiles;       // and of all its items
     const int32_t* row_lo[2];  // L entries
     const int32_t* row_hi[2];
     int32_t L;                 // rows of Q, O, LSE per head
@@ -59,11 +60,19 @@ inline unsigned launch_groups(int n_items, int n_heads) {
     return (unsigned)n_items * (unsigned)n_heads;
 }
 
-// Streams of this many tiles and more leave the maxima of most tiles out (csrc/fwd.hip).
+// Whether a forward launch leaves the maxima of most tiles out (csrc/fwd.hip; no bits depend on it): streams of 16 tiles
+// and more, and work for 7/4 of its longest items on every compute unit.  Time against taking every maximum, at
+// `fill` = tiles of the launch / (tiles of the longest item * compute units), 256 compute units:
+//   19 to 100 tiles: fill 0.2 to 1.0 +9..12 %, 1.1 to 1.4 -2..+11 %, 1.5 to 1.7 -4..+5 %, 1.8 to 2.6 -5..+1.5 %, beyond
+//     -1..-8 % (25 tiles, fill 9.3: 141 -> 139 us; 100 tiles, fill 8.3: 480 -> 464; equal items of 25 tiles, 2.25: 49.5 ->
+//     48.3): on few wavefronts the second contraction waits for the sum, on many the vector instructions count;
+//   7 to 13 tiles: up to +11 % below 1.5, then -2..+2 %, on full chips -2 %: they keep the plain form.
 #ifndef HMAR_TUNE_LONG_STREAM
 #define HMAR_TUNE_LONG_STREAM 16           // measurement builds: where long streams begin
 #endif
-constexpr int kLongStream = HMAR_TUNE_LONG_STREAM;      // tiles
+inline bool leaves_maxima_out(int max_tiles, long long total_tiles, int n_heads, int num_cus) {
+    return max_tiles >= HMAR_TUNE_LONG_STREAM && 4 * total_tiles * n_heads >= 7LL * num_cus * max_tiles;
+}
 
 // Per-kernel event bracketing for hmar_profile_begin/end (no-ops unless profiling is on).
 enum KernelId { kKernelFwd = 0, kKernelDkDv = 1, kKernelDq = 2, kNumKernels = 3 };
