@@ -32,7 +32,7 @@ def variant_path(name: str) -> str:
     return os.path.join(HERE, f"libhmar_attn_{name}.so")
 
 
-def _launch_command(out: str) -> list:
+def launch_command(out: str, defines=()) -> list:
     """g++ command of the Python module _launch: host code against torch's C++ interface, no device code."""
     import torch
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
@@ -41,7 +41,7 @@ def _launch_command(out: str) -> list:
     return [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
             "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"), "-I", os.path.join(rocm, "include"),
-            "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "py_launch.cpp"),
+            "-I", sysconfig.get_paths()["include"], *[f"-D{d}" for d in defines], os.path.join(CSRC, "py_launch.cpp"),
             "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python", "-lc10_hip", "-o", out]
 
 
@@ -54,7 +54,7 @@ def build_library(verbose: bool = False, variant: str = "", defines=()) -> str:
                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, *[f"-D{d}" for d in defines],
                    *[os.path.join(CSRC, s) for s in SOURCES], "-o", out + ".tmp"])]
     if not variant:
-        jobs.append((LAUNCH_PATH, _launch_command(LAUNCH_PATH + ".tmp")))
+        jobs.append((LAUNCH_PATH, launch_command(LAUNCH_PATH + ".tmp")))
     procs = []
     for target, cmd in jobs:
         if verbose:

@@ -33,11 +33,26 @@ decltype(&hmar_attn_bwd_workspace_bytes_masked) g_ws_bytes = nullptr;
 decltype(&hmar_attn_steps_fwd) g_steps = nullptr;
 decltype(&hmar_attn_step_fwd_rows) g_rows = nullptr;
 
+// A build for tests on hosts without a GPU (-DHMAR_LAUNCH_HOST) takes host tensors and the null stream.
+#ifdef HMAR_LAUNCH_HOST
+bool on_gpu(const at::Tensor&) { return true; }
+bool current(const at::Device&) { return true; }
+void* stream_of(const at::Tensor&) { return nullptr; }
+#else
+bool on_gpu(const at::Tensor& t) { return t.is_cuda(); }
+bool current(const at::Device& d) { return d.index() == c10::hip::current_device(); }
+void* stream_of(const at::Tensor& q) { return c10::hip::getCurrentHIPStream(q.device().index()).stream(); }
+#endif
+
+// Under a function transform (torch.func.grad and its like) an operation gives a wrapper without memory of its own,
+// whatever it was given.
+bool has_memory(const at::Tensor& t) { return t.unsafeGetTensorImpl()->has_storage(); }
+
 // A plain tensor with memory of its own (no subclass, no wrapper of a function transform), or null.
 const at::Tensor* plain(PyObject* o) {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.defined() || !t.is_cuda() || t.layout() != at::kStrided || !t.unsafeGetTensorImpl()->has_storage()) return nullptr;
+    if (!t.defined() || !on_gpu(t) || t.layout() != at::kStrided || !has_memory(t)) return nullptr;
     return &t;
 }
 
@@ -55,10 +70,8 @@ const at::Tensor* checked_q(PyObject* o) {
 // The outputs and the launch below are what the caller sees only if no mode wants to see the calls.
 bool ready(const at::Tensor& q) {
     return !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
-           q.device().index() == c10::hip::current_device();
+           current(q.device());
 }
-
-void* stream_of(const at::Tensor& q) { return c10::hip::getCurrentHIPStream(q.device().index()).stream(); }
 
 bool to_int(PyObject* o, int64_t* out) {
     if (!PyLong_CheckExact(o)) return false;
@@ -86,7 +99,10 @@ bool to_sizes(PyObject* address, PyObject* count, PyObject* L, Sizes* out) {
 
 // an output tensor the caller gave (checked), or a new one
 bool output(PyObject* given, at::ScalarType type, at::IntArrayRef shape, const at::Tensor& q, at::Tensor* out) {
-    if (given == Py_None) { *out = at::empty(shape, q.options().dtype(type)); return true; }
+    if (given == Py_None) {
+        *out = at::empty(shape, q.options().dtype(type));
+        return has_memory(*out);
+    }
     const at::Tensor* t = checked(given, type, shape, q.device());
     if (!t) return false;
     *out = *t;
@@ -112,17 +128,27 @@ PyObject* guarded(F&& body) {
     try {
         return body();
     } catch (const std::exception&) {
+        PyErr_Clear();
         Py_RETURN_NONE;
     }
 }
 
+// The GIL is free while this lives.  Everything that can throw or needs Python (pointers and sizes of tensors, the
+// stream) is fetched before; should the call throw all the same, the GIL is taken again on the way out.
+struct GilReleased {
+    PyThreadState* state = PyEval_SaveThread();
+    GilReleased() = default;
+    GilReleased(const GilReleased&) = delete;
+    GilReleased& operator=(const GilReleased&) = delete;
+    ~GilReleased() { PyEval_RestoreThread(state); }
+};
 template <typename F>
 hmar_status without_gil(F&& call) {
-    PyThreadState* state = PyEval_SaveThread();
-    const hmar_status code = call();
-    PyEval_RestoreThread(state);
-    return code;
+    const GilReleased released;
+    return call();
 }
+
+float* floats(const at::Tensor& t) { return static_cast<float*>(t.data_ptr()); }
 
 // bind(addresses of the library's functions)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -158,9 +184,12 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
             !output(a[4], at::kFloat, q->sizes().slice(0, 3), *q, &lse))
             Py_RETURN_NONE;
         void* stream = stream_of(*q);
+        const void *Q = q->data_ptr(), *K = k->data_ptr(), *V = v->data_ptr();
+        void* O = o.data_ptr();
+        float* LSE = floats(lse);
+        const int32_t B = (int32_t)q->size(0), H = (int32_t)q->size(1), D = (int32_t)q->size(3);
         const hmar_status code = without_gil([&] {
-            return g_fwd(q->data_ptr(), k->data_ptr(), v->data_ptr(), o.data_ptr(), static_cast<float*>(lse.data_ptr()), s.array,
-                         s.count, (int32_t)kind, (int32_t)q->size(0), (int32_t)q->size(1), (int32_t)q->size(3), scale, stream);
+            return g_fwd(Q, K, V, O, LSE, s.array, s.count, (int32_t)kind, B, H, D, scale, stream);
         });
         return result(code, {o, lse});
     });
@@ -185,17 +214,19 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (a[9] == Py_None) {
             const int64_t need = (int64_t)g_ws_bytes(s.array, s.count, (int32_t)kind, B, H, D);
             ws = at::empty({need < 16 ? 16 : need}, q->options().dtype(at::kByte));
+            if (!has_memory(ws)) Py_RETURN_NONE;
         } else {
             const at::Tensor* t = plain(a[9]);
             if (!t || t->device() != q->device()) Py_RETURN_NONE;
             ws = *t;
         }
         void* stream = stream_of(*q);
+        const void *Q = q->data_ptr(), *K = in[0]->data_ptr(), *V = in[1]->data_ptr(), *O = in[2]->data_ptr(), *dO = in[3]->data_ptr();
+        const float* LSE = floats(*lse);
+        void *dQ = out[0].data_ptr(), *dK = out[1].data_ptr(), *dV = out[2].data_ptr(), *workspace = ws.data_ptr();
+        const size_t ws_bytes = (size_t)ws.numel() * ws.element_size();
         const hmar_status code = without_gil([&] {
-            return g_bwd(q->data_ptr(), in[0]->data_ptr(), in[1]->data_ptr(), in[2]->data_ptr(), in[3]->data_ptr(),
-                         static_cast<const float*>(lse->data_ptr()), out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(),
-                         s.array, s.count, (int32_t)kind, B, H, D, scale, ws.data_ptr(),
-                         (size_t)ws.numel() * ws.element_size(), stream);
+            return g_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, s.array, s.count, (int32_t)kind, B, H, D, scale, workspace, ws_bytes, stream);
         });
         return result(code, {out[0], out[1], out[2]});
     });
@@ -215,10 +246,12 @@ PyObject* bwd_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (!t[i]) Py_RETURN_NONE;
         }
         void* stream = stream_of(*q);
+        void* p[9];
+        for (int i = 0; i < 9; ++i) p[i] = t[i]->data_ptr();
+        const int32_t B = (int32_t)q->size(0), H = (int32_t)q->size(1), D = (int32_t)q->size(3);
         const hmar_status code = without_gil([&] {
-            return g_bwd_noalloc(q->data_ptr(), t[1]->data_ptr(), t[2]->data_ptr(), t[3]->data_ptr(), t[4]->data_ptr(),
-                                 static_cast<const float*>(t[5]->data_ptr()), t[6]->data_ptr(), t[7]->data_ptr(), t[8]->data_ptr(),
-                                 s.array, s.count, (int32_t)q->size(0), (int32_t)q->size(1), (int32_t)q->size(3), scale, stream);
+            return g_bwd_noalloc(p[0], p[1], p[2], p[3], p[4], static_cast<const float*>(p[5]), p[6], p[7], p[8], s.array, s.count,
+                                 B, H, D, scale, stream);
         });
         if (code != HMAR_OK) return PyLong_FromLong(code);
         return PyTuple_Pack(3, a[6], a[7], a[8]);
@@ -252,11 +285,11 @@ PyObject* step(PyObject*, PyObject* const* a, Py_ssize_t n) {
         void* stream = stream_of(*q);
         const void *Q = q->data_ptr(), *K = s.k.data_ptr(), *V = s.v.data_ptr();
         void* O = s.o.data_ptr();
-        float* LSE = static_cast<float*>(s.lse.data_ptr());
+        float* LSE = floats(s.lse);
         const int32_t n_prev = (int32_t)s.n_prev, n_cur = (int32_t)q->size(2);
+        const int32_t B = (int32_t)q->size(0), H = (int32_t)q->size(1), D = (int32_t)q->size(3);
         const hmar_status code = without_gil([&] {
-            return g_steps(&Q, &K, &V, &O, &LSE, &n_prev, &n_cur, 1, (int32_t)q->size(0), (int32_t)q->size(1), (int32_t)q->size(3),
-                           scale, stream);
+            return g_steps(&Q, &K, &V, &O, &LSE, &n_prev, &n_cur, 1, B, H, D, scale, stream);
         });
         return result(code, {s.o, s.lse});
     });
@@ -274,10 +307,14 @@ PyObject* rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
             r->numel() < 1 || r->numel() > q->size(2))
             Py_RETURN_NONE;
         void* stream = stream_of(*q);
+        const void *Q = q->data_ptr(), *K = s.k.data_ptr(), *V = s.v.data_ptr();
+        void* O = s.o.data_ptr();
+        float* LSE = floats(s.lse);
+        const int32_t* list = static_cast<const int32_t*>(r->data_ptr());
+        const int32_t n_rows = (int32_t)r->numel(), n_cur = (int32_t)q->size(2);
+        const int32_t B = (int32_t)q->size(0), H = (int32_t)q->size(1), D = (int32_t)q->size(3);
         const hmar_status code = without_gil([&] {
-            return g_rows(q->data_ptr(), s.k.data_ptr(), s.v.data_ptr(), s.o.data_ptr(), static_cast<float*>(s.lse.data_ptr()),
-                          static_cast<const int32_t*>(r->data_ptr()), (int32_t)r->numel(), (int32_t)s.n_prev, (int32_t)q->size(2),
-                          (int32_t)q->size(0), (int32_t)q->size(1), (int32_t)q->size(3), scale, stream);
+            return g_rows(Q, K, V, O, LSE, list, n_rows, (int32_t)s.n_prev, n_cur, B, H, D, scale, stream);
         });
         return result(code, {s.o, s.lse});
     });
@@ -310,13 +347,14 @@ PyObject* steps(PyObject*, PyObject* const* a, Py_ssize_t n) {
                 x.q.device() != q0.device())
                 Py_RETURN_NONE;
             Q[(size_t)i] = x.q.data_ptr(); K[(size_t)i] = x.k.data_ptr(); V[(size_t)i] = x.v.data_ptr();
-            O[(size_t)i] = x.o.data_ptr(); LSE[(size_t)i] = static_cast<float*>(x.lse.data_ptr());
+            O[(size_t)i] = x.o.data_ptr(); LSE[(size_t)i] = floats(x.lse);
             n_prev[(size_t)i] = (int32_t)x.n_prev; n_cur[(size_t)i] = (int32_t)x.q.size(2);
         }
         void* stream = stream_of(q0);
+        const int32_t B = (int32_t)q0.size(0), H = (int32_t)q0.size(1), D = (int32_t)q0.size(3);
         const hmar_status code = without_gil([&] {
-            return g_steps(Q.data(), K.data(), V.data(), O.data(), LSE.data(), n_prev.data(), n_cur.data(), (int32_t)count,
-                           (int32_t)q0.size(0), (int32_t)q0.size(1), (int32_t)q0.size(3), scale, stream);
+            return g_steps(Q.data(), K.data(), V.data(), O.data(), LSE.data(), n_prev.data(), n_cur.data(), (int32_t)count, B, H, D,
+                           scale, stream);
         });
         if (code != HMAR_OK) return PyLong_FromLong(code);
         PyObject *os = PyList_New(count), *lses = PyList_New(count);

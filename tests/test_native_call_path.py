@@ -1,12 +1,18 @@
 """The binding's native call path (_launch) against its Python path, which takes over whenever an argument is
 not exactly of the plain type (here: the softmax scale as numpy.float64).  Both reach the same kernels, so
 results are compared bit for bit; errors must be the Python path's."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2506_04421_amd as hm
-from paper_2506_04421_amd import binding
+from paper_2506_04421_amd import binding, build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 D = 64
 MARKOV_COUNTS = hm.HMAR_MASK_MARKOV | hm.HMAR_SCALE_COUNTS
@@ -37,6 +43,101 @@ def test_host_tensors_and_other_types_are_left_to_the_python_path():
     assert native.rows(q, q, q, 0, torch.zeros(1, dtype=torch.int32), q, lse, 0.0) is None
     assert native.steps([q], [q], [q], [0], None, None, 0.0) is None
     assert native.steps([], [], [], [], None, None, 0.0) is None
+
+
+TRANSFORMS = """
+import ctypes, importlib.util, sys, threading
+import torch
+spec = importlib.util.spec_from_file_location("_launch", sys.argv[1])
+native = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(native)
+calls = []
+def stand_in(name, code):
+    def f(*args):
+        calls.append(name)
+        return code
+    return ctypes.CFUNCTYPE(ctypes.c_int64)(f)          # reads no argument
+names = ("fwd", "bwd", "bwd_noalloc", "ws_bytes", "steps", "rows")
+keep = [stand_in(n, 4096 if n == "ws_bytes" else 0) for n in names]
+native.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in keep])
+q, k, v, o, g = (torch.randn(1, 2, 5, 64).bfloat16() for _ in range(5))
+dq, dk, dv = (torch.empty_like(q) for _ in range(3))
+lse, rows, ws = torch.zeros(1, 2, 5), torch.zeros(3, dtype=torch.int32), torch.zeros(4096, dtype=torch.uint8)
+sides = (ctypes.c_int32 * 2)(1, 2)
+s = (ctypes.addressof(sides), 2, 5)
+new = {                                                  # these allocate: under a transform they are left to Python
+    "fwd": lambda: native.fwd(q, k, v, None, None, *s, 0, 0.0),
+    "fwd, O given": lambda: native.fwd(q, k, v, o, None, *s, 0, 0.0),
+    "bwd": lambda: native.bwd(q, k, v, o, g, lse, None, None, None, ws, *s, 0, 0.0),
+    "bwd, workspace": lambda: native.bwd(q, k, v, o, g, lse, dq, dk, dv, None, *s, 0, 0.0),
+    "step": lambda: native.step(q, k, v, 0, None, None, 0.0),
+    "steps": lambda: native.steps([q], [k], [v], [0], None, None, 0.0)}
+given = {
+    "fwd": lambda: native.fwd(q, k, v, o, lse, *s, 0, 0.0),
+    "bwd": lambda: native.bwd(q, k, v, o, g, lse, dq, dk, dv, ws, *s, 0, 0.0),
+    "bwd_noalloc": lambda: native.bwd_noalloc(q, k, v, o, g, lse, dq, dk, dv, *s, 0.0),
+    "step": lambda: native.step(q, k, v, 0, o, lse, 0.0),
+    "steps": lambda: native.steps([q], [k], [v], [0], [o], [lse], 0.0),
+    "rows": lambda: native.rows(q, k, v, 0, rows, o, lse, 0.0)}
+def transforms(f):
+    res = []
+    def body(x):
+        res.append(f())
+        return (x * x).sum()
+    x = torch.ones(3)
+    torch.func.grad(body)(x)
+    torch.func.vjp(body, x)
+    torch.func.jvp(body, (x,), (x,))
+    torch.func.vmap(lambda y: body(y))(torch.ones(2, 3))
+    return res
+for name, f in new.items():
+    assert f() is not None, name
+    calls.clear()
+    res = transforms(f)
+    launched = [c for c in calls if c != "ws_bytes"]
+    assert res[:3] == [None] * 3 and len(launched) == sum(n is not None for n in res), (name, res, calls)
+    assert f() is not None, name
+for name, f in given.items():
+    calls.clear()
+    assert all(r is not None for r in transforms(f)) and len(calls) == 4, (name, calls)
+t = threading.Thread(target=lambda: transforms(new["fwd"]))
+t.start(); t.join()
+print("done")
+"""
+
+
+def test_function_transforms_around_a_call_are_left_to_the_python_path(tmp_path):
+    # inside torch.func.grad and its like a new tensor is a wrapper without memory, also where every input is a plain
+    # constant of the closure; met with the GIL released that ended the process, hence one of its own here
+    path = str(tmp_path / "_launch.so")
+    subprocess.run(build.launch_command(path, ["HMAR_LAUNCH_HOST"]), check=True, timeout=300)
+    res = subprocess.run([sys.executable, "-c", TRANSFORMS, path], capture_output=True, text=True, timeout=300, cwd=ROOT)
+    assert res.returncode == 0 and res.stdout.strip().endswith("done"), res.stdout + res.stderr
+
+
+@pytest.mark.gpu
+def test_a_call_on_constants_inside_a_function_transform_raises_the_python_paths_error():
+    dev = torch.device("cuda:0")
+    q, k, v, g = _tensors(4, (1, 2, 14, D), dev)
+    sizes = (1, 2, 3)
+    O, LSE = hm.hmar_attn_fwd(q, k, v, sizes)
+    dQ, dK, dV = hm.hmar_attn_bwd(q, k, v, O, g, LSE, sizes)
+    ws = torch.empty(8 * 2 * 14 + 16, dtype=torch.uint8, device=dev)
+    x = torch.ones(3, device=dev)
+    for scale in (np.float64(0.0), 0.0):
+        for call in (lambda: hm.hmar_attn_fwd(q, k, v, sizes, scale), lambda: hm.hmar_attn_bwd(q, k, v, O, g, LSE, sizes, scale),
+                     lambda: hm.hmar_attn_step_fwd(q, k, v, 0, scale), lambda: hm.hmar_attn_steps_fwd([q], [k], [v], [0], scale)):
+            with pytest.raises(RuntimeError, match="storage"):
+                torch.func.grad(lambda y: (call(), y.sum())[1])(x)
+        o, lse, gq, gk, gv = (torch.full_like(t, float("nan")) for t in (O, LSE, dQ, dK, dV))
+
+        def given(y):
+            hm.hmar_attn_fwd(q, k, v, sizes, scale, O=o, LSE=lse)
+            hm.hmar_attn_bwd(q, k, v, o, g, lse, sizes, scale, dQ=gq, dK=gk, dV=gv, workspace=ws)
+            return (y * y).sum()
+        assert torch.equal(torch.func.grad(given)(x), 2 * x)
+        for a, b in zip((o, lse, gq, gk, gv), (O, LSE, dQ, dK, dV)):
+            assert torch.equal(a, b)
 
 
 @pytest.mark.gpu
