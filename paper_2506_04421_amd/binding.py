@@ -97,8 +97,7 @@ def _check(code: int, what: str) -> None:
         raise HmarError(f"{what} failed: {status_string(code)}")
 
 
-_SIDES_CACHE = {}
-_SIDES_NATIVE = {}      # the same entries as the native path takes them; the arrays live in _SIDES_CACHE
+_SIDES_CACHE = {}       # key -> (ctypes array, count, L, (address of the array, count, L)); entries stay
 
 
 def _sides_array(side_lens: Sequence[int], counts: bool = False):
@@ -108,10 +107,10 @@ def _sides_array(side_lens: Sequence[int], counts: bool = False):
     hit = _SIDES_CACHE.get(key)
     if hit is None:
         sides = [int(s) for s in key[0]]
-        hit = ((ctypes.c_int32 * len(sides))(*sides), len(sides), sum(s if counts else s * s for s in sides))
-        _SIDES_CACHE[key] = hit
-        _SIDES_NATIVE[key] = (ctypes.addressof(hit[0]),) + hit[1:]
-    return hit
+        arr, n, L = (ctypes.c_int32 * len(sides))(*sides), len(sides), sum(s if counts else s * s for s in sides)
+        # threads that meet a schedule at the same time share the entry that is stored first
+        hit = _SIDES_CACHE.setdefault(key, (arr, n, L, (ctypes.addressof(arr), n, L)))
+    return hit[:3]
 
 
 def _known_sides(side_lens, mask_kind):
@@ -121,9 +120,10 @@ def _known_sides(side_lens, mask_kind):
             return None
         side_lens = tuple(side_lens)
     try:
-        return _SIDES_NATIVE.get((side_lens, mask_kind & HMAR_SCALE_COUNTS != 0))
+        hit = _SIDES_CACHE.get((side_lens, mask_kind & HMAR_SCALE_COUNTS != 0))
     except TypeError:            # an unhashable entry, or a mask kind that is no integer
         return None
+    return None if hit is None else hit[3]
 
 
 def _done(res, what: str):

@@ -1,9 +1,11 @@
 """The binding's native call path (_launch) against its Python path, which takes over whenever an argument is
 not exactly of the plain type (here: the softmax scale as numpy.float64).  Both reach the same kernels, so
 results are compared bit for bit; errors must be the Python path's."""
+import ctypes
 import os
 import subprocess
 import sys
+import threading
 
 import numpy as np
 import pytest
@@ -43,6 +45,43 @@ def test_host_tensors_and_other_types_are_left_to_the_python_path():
     assert native.rows(q, q, q, 0, torch.zeros(1, dtype=torch.int32), q, lse, 0.0) is None
     assert native.steps([q], [q], [q], [0], None, None, 0.0) is None
     assert native.steps([], [], [], [], None, None, 0.0) is None
+
+
+@pytest.mark.parametrize("moment", ["before", "after"])
+def test_two_threads_that_meet_a_schedule_first_share_one_array(monkeypatch, moment):
+    # both have found nothing; the second stores its entry just before or just after the first one does.  The address
+    # the native path is given must be that of the array that is kept
+    class Cache(dict):
+        met = blind = False
+
+        def get(self, *a):
+            return None if self.blind else super().get(*a)
+
+        def meet(self):
+            if not self.met:
+                self.met = self.blind = True
+                second = threading.Thread(target=binding._sides_array, args=((23, 29),))
+                second.start()
+                second.join()
+                self.blind = False
+
+        def setdefault(self, *a):
+            if moment == "before":
+                self.meet()
+            res = super().setdefault(*a)
+            self.meet()
+            return res
+
+        def __setitem__(self, *a):
+            if moment == "before":
+                self.meet()
+            super().__setitem__(*a)
+            self.meet()
+    monkeypatch.setattr(binding, "_SIDES_CACHE", Cache())
+    array, count, L = binding._sides_array((23, 29))
+    assert binding._SIDES_CACHE.met and list(array) == [23, 29] and (count, L) == (2, 1370)
+    kept = binding._sides_array((23, 29))[0]
+    assert binding._known_sides((23, 29), 0) == (ctypes.addressof(kept), 2, 1370)
 
 
 TRANSFORMS = """
