@@ -535,9 +535,10 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     if (groups == 0) return hipErrorInvalidValue;
     p.map = unit_map_for(num_cus, items, n_heads);
     profile_before(kKernelFwd, stream);
-    if (p.n_tiled == 0) {
-        const unsigned units = (unsigned)n_heads * (unsigned)p.n_pack;      // at most 2^24 * 32
-        hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((units + 3) / 4), dim3(kThreads), 0, stream, p);
+    // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
+    const long long small_groups = ((long long)n_heads * p.n_pack + 3) / 4;
+    if (p.n_tiled == 0 && small_groups * kThreads < 1LL << 32) {
+        hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((unsigned)small_groups), dim3(kThreads), 0, stream, p);
     } else {
         const auto kernel = leaves_maxima_out(max_tiles, total_tiles, n_heads, num_cus) ? hmar_fwd_steps_kernel<true>
                                                                                         : hmar_fwd_steps_kernel<false>;

@@ -721,6 +721,22 @@ def test_refinement_pass_over_a_subset_of_rows(n_prev, n_cur, n_rows):
     # blocks in order; in general only the oracle bar holds, which is what is asserted above
 
 
+@pytest.mark.parametrize("heads", [(1 << 22) - 16, 1 << 22])
+def test_steps_of_more_units_than_a_launch_has_room_for(heads):
+    # 16 steps of one token: a launch of four units per workgroup would need 2^32 threads at 2^22 heads, one that a
+    # launch cannot have.  One key: O is V, and LSE the only score.
+    d = _dev()
+    g = torch.Generator(device=d)
+    g.manual_seed(7)
+    q, k, v = (torch.randn((1, heads, 1, 64), device=d, generator=g, dtype=torch.bfloat16) for _ in range(3))
+    Os, LSEs = hm.hmar_attn_steps_fwd([q] * 16, [k] * 16, [v] * 16, [0] * 16, Os=[_nan_like(q) for _ in range(16)],
+                                      LSEs=[_nan_stats((1, heads, 1), d) for _ in range(16)])
+    score = (q.float() * k.float()).sum(-1) / 8.0
+    for O, LSE in zip(Os, LSEs):
+        assert torch.equal(O, v)
+        assert ((LSE - score).abs() <= TOL_LSE_REL * score.abs().clamp(min=1.0)).all()
+
+
 def test_inference_steps_reproduce_the_training_forward():
     # all 10 steps of the 256px schedule, each fed the slices the training layout holds,
     # give the rows of the full Markovian forward (same kernels, same tiles => bit equal
