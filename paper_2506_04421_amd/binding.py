@@ -7,12 +7,14 @@ been built, importing the entry points fails with an error that says how to buil
 
 A plainly valid call of the entry points goes through the native module _launch, which does the same
 checks, allocations and library call in a fraction of the host time; whatever it does not accept
-(it returns None) takes the Python code below it, which decides and words the errors.
+(it returns None) takes the Python code below it, which decides and words the errors.  Both call the same
+library; where _launch is not built, every call takes the Python code, after one warning.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Sequence, Tuple
 
 import torch
@@ -22,11 +24,16 @@ LIB_PATH = os.path.join(_HERE, "libhmar_attn.so")
 
 HMAR_OK = 0
 _lib = None
-_launch = None      # the native module, bound to the library's functions
+_launch = None      # the native module, bound to the library's functions, or _NoLaunch
 
 
 class HmarError(RuntimeError):
     pass
+
+
+class _NoLaunch:
+    """In the place of the native module where that was not built: leaves every call to the Python path."""
+    fwd = bwd = bwd_noalloc = step = rows = steps = staticmethod(lambda *args: None)
 
 
 def load_library() -> ctypes.CDLL:
@@ -78,11 +85,13 @@ def load_library() -> ctypes.CDLL:
     try:
         from . import _launch as launch
     except ImportError as e:
-        raise HmarError(f"the native call path of the binding is missing or does not load ({e}): build it with "
-                        "`python -m paper_2506_04421_amd.build`") from e
-    launch.bind(*[ctypes.cast(f, vp).value for f in
-                  (lib.hmar_attn_fwd_masked, lib.hmar_attn_bwd_masked, lib.hmar_attn_bwd_noalloc,
-                   lib.hmar_attn_bwd_workspace_bytes_masked, lib.hmar_attn_steps_fwd, lib.hmar_attn_step_fwd_rows)])
+        warnings.warn(f"the native call path is missing or does not load ({e}); calls take the Python path, which costs "
+                      "host time: build it with `python -m paper_2506_04421_amd.build`", RuntimeWarning, stacklevel=2)
+        launch = _NoLaunch
+    else:
+        launch.bind(*[ctypes.cast(f, vp).value for f in
+                      (lib.hmar_attn_fwd_masked, lib.hmar_attn_bwd_masked, lib.hmar_attn_bwd_noalloc,
+                       lib.hmar_attn_bwd_workspace_bytes_masked, lib.hmar_attn_steps_fwd, lib.hmar_attn_step_fwd_rows)])
     _launch = launch
     _lib = lib
     return lib

@@ -59,14 +59,19 @@ def build_library(verbose: bool = False, variant: str = "", defines=()) -> str:
     for target, cmd in jobs:
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((target, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    results = [(target, proc.communicate()[0], proc.returncode) for target, proc in procs]
+        try:
+            procs.append((target, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+        except OSError as e:                        # no such compiler
+            procs.append((target, e))
+    results = [(target, *((str(proc) + "\n", 1) if isinstance(proc, OSError) else (proc.communicate()[0], proc.returncode)))
+               for target, proc in procs]
+    for target, _, code in results:                 # the library is of use without the module
+        if code == 0:
+            os.replace(target + ".tmp", target)
     for target, log, code in results:
         if code != 0:
             sys.stderr.write(log)
             raise RuntimeError(f"the compiler failed building {os.path.basename(target)}")
-    for target, _, _ in results:
-        os.replace(target + ".tmp", target)
     return out
 
 

@@ -47,6 +47,34 @@ def test_host_tensors_and_other_types_are_left_to_the_python_path():
     assert native.steps([], [], [], [], None, None, 0.0) is None
 
 
+def test_the_library_works_without_the_native_path(monkeypatch):
+    # the module needs torch's C++ interface and Python's headers where it is built; the library never did
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_launch", None)
+    monkeypatch.delattr(hm, "_launch", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2506_04421_amd._launch", None)          # importing it fails
+    with pytest.warns(RuntimeWarning, match="native call path"):
+        assert hm.hmar_schedule_describe((1, 2, 3, 4)) == ([0, 1, 5, 14, 30], 538)
+    q = torch.zeros((1, 1, 5, D), dtype=torch.bfloat16)
+    binding._sides_array((1, 2))
+    for call in (lambda: hm.hmar_attn_fwd(q, q, q, (1, 2)), lambda: hm.hmar_attn_step_fwd(q, q, q, 0),
+                 lambda: hm.hmar_attn_bwd(q, q, q, q, q, q, (1, 2))):
+        with pytest.raises(hm.HmarError, match="^Q must be a device tensor"):
+            call()
+
+
+def test_the_library_is_built_where_the_native_path_is_not(monkeypatch, tmp_path):
+    monkeypatch.setattr(build, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "LAUNCH_PATH", str(tmp_path / "_launch.so"))
+    monkeypatch.setattr(build, "SOURCES", ["schedule.cpp"])
+    for command in (["false"], [str(tmp_path / "no_such_compiler")]):
+        monkeypatch.setattr(build, "launch_command", lambda out, c=command: c)
+        (tmp_path / "lib.so").unlink(missing_ok=True)
+        with pytest.raises(RuntimeError, match="_launch.so"):
+            build.build_library()
+        assert (tmp_path / "lib.so").exists() and not (tmp_path / "_launch.so").exists()
+
+
 @pytest.mark.parametrize("moment", ["before", "after"])
 def test_two_threads_that_meet_a_schedule_first_share_one_array(monkeypatch, moment):
     # both have found nothing; the second stores its entry just before or just after the first one does.  The address
