@@ -204,23 +204,24 @@ def test_heads_that_fill_no_group_of_eight(sides, H, heads):
 
 @pytest.mark.parametrize("sides,H", [((17, 20), 3), ((17, 20), 40), ((17, 20), 60),      # 7 items, 11 tiles each
                                      ((3, 23, 25), 2), ((3, 23, 25), 24), ((3, 23, 25), 48), ((3, 23, 25), 90),  # 11, 19
-                                     ((39, 41), 5)])                                          # 27, 51
-def test_small_launches_divide_the_streamed_tiles(sides, H):
-    # every form a workgroup can take: the launches hold from a few to two units per compute unit,
-    # with streams of fewer and of more than 16 and 48 tiles, ragged last items and tiles
+                                     ((39, 41), 5), ((39, 41), 26)])                          # 27, 51
+def test_launches_of_a_few_units_to_several_per_compute_unit(sides, H):
+    # short and long streams, ragged last items and tiles; (3, 23, 25) at 90 heads and (39, 41) at 26 fill the chip
+    # with streams long enough to leave tile maxima out
     L = sum(s * s for s in sides)
     Q, K, V, dO = si.draw((1, H, L, 64), seed=1400 + H, n_tensors=4)
     res = _gpu_run(Q, K, V, dO, sides, 0.125)
     heads = [(0, h) for h in sorted({0, H // 2, H - 1})]
     ref = _oracle_heads(Q, K, V, dO, sides, 0.125, heads)
     bounds = _operand_rounding_bounds(Q, K, V, dO, sides, 0.125, heads, ref)      # see the full-size test
-    _compare(res, ref, heads, "divided tiles", grad_bounds={t: np.maximum(x, TOL_ABS) for t, x in bounds.items()})
+    _compare(res, ref, heads, "few to several units per CU", grad_bounds={t: np.maximum(x, TOL_ABS) for t, x in bounds.items()})
 
 
-@pytest.mark.parametrize("n_prev,n_cur,H", [(150, 200, 5), (150, 200, 100), (600, 500, 4), (600, 500, 50), (600, 500, 90)])
-def test_small_steps_divide_the_keys(n_prev, n_cur, H):
-    # the same forms for inference steps, alone, with a step small enough to share the last item, and
-    # over a row list
+@pytest.mark.parametrize("n_prev,n_cur,H", [(150, 200, 5), (150, 200, 100), (600, 500, 4), (600, 500, 50), (600, 500, 90),
+                                            (600, 500, 230)])
+def test_steps_of_a_few_units_to_several_per_compute_unit(n_prev, n_cur, H):
+    # the same for inference steps, alone, with a step small enough to share the last item, and over a row list: at 230
+    # heads all three launches, of 4, 5 and 2 items a head, leave tile maxima out
     d = _dev()
     p, c = [n_prev, 3], [n_cur, 9]
     Qs = [si.draw((1, H, n, 64), seed=1500 + n, n_tensors=1)[0] for n in c]
@@ -242,11 +243,11 @@ def test_small_steps_divide_the_keys(n_prev, n_cur, H):
             rO, rL = orc.attn_step_fwd(*[si.to_f64(t[:, h:h + 1]) for t in (Qs[i], KVs[i][0], KVs[i][1])], p[i])
             ref["O"].append(rO[0, 0]); ref["LSE"].append(rL[0, 0])
         ref = {n: np.stack(t) for n, t in ref.items()}
-        _compare(dict(O=Os[i], LSE=LSEs[i]), ref, heads, "divided keys")
+        _compare(dict(O=Os[i], LSE=LSEs[i]), ref, heads, "few to several units per CU, steps")
         if i == 0:
-            _compare(dict(O=one[0], LSE=one[1]), ref, heads, "divided keys")
+            _compare(dict(O=one[0], LSE=one[1]), ref, heads, "few to several units per CU, steps")
             _compare(dict(O=O[:, :, rows.long()], LSE=LSE[:, :, rows.long()]), {n: t[:, idx] for n, t in ref.items()},
-                     heads, "divided keys, listed rows")
+                     heads, "few to several units per CU, listed rows")
             keep = np.setdiff1d(np.arange(n_cur), idx)
             assert (si.to_f64(O)[:, :, keep] == 7.0).all() and (si.to_f64(LSE)[:, :, keep] == -3.0).all()
 
@@ -349,10 +350,10 @@ def test_scores_that_jump_far_above_the_first_tile():
     assert float(np.abs(ref["LSE"]).max()) > 300.0  # the case really is extreme
 
 
-@pytest.mark.parametrize("H", [2, 24, 40, 60])
+@pytest.mark.parametrize("H", [2, 24, 40, 60, 80])
 def test_scores_that_jump_in_long_streams(H):
-    # the same on streams of more than 16 tiles, where a tile is exponentiated before its maximum is
-    # known and formed again if a row's sum comes out too large, for every form of a workgroup
+    # the same on streams of more than 16 tiles, where (at 80 heads) a tile is exponentiated before its maximum is
+    # known and formed again if a row's sum comes out too large
     sides, D = (3, 23, 25), 64
     offs, L = orc.scale_offsets(sides), sum(s * s for s in sides)
     Q, K, V, _ = si.draw((1, H, L, D), seed=1600 + H, n_tensors=4)
@@ -365,6 +366,34 @@ def test_scores_that_jump_in_long_streams(H):
     res = _gpu_run(Q, K, V, None, sides, 0.125, backward=False)
     heads = [(0, h) for h in sorted({0, H // 2, H - 1})]
     _compare(res, _oracle_heads(Q, K, V, None, sides, 0.125, heads), heads, "late-dominant-keys, long streams")
+
+
+@pytest.mark.parametrize("factor", [2.0, 8.0, 64.0])
+def test_scores_that_jump_in_long_steps(factor):
+    # the same for a step and for a row list: 18 key tiles, more than 7/4 workgroups per compute unit, keys that grow late
+    # in the stream by little (tiles formed again, the reference stays) and by much (it moves)
+    d, H, n_prev, n_cur = _dev(), 230, 600, 500
+    Q = si.draw((1, H, n_cur, 64), seed=1650, n_tensors=1)[0]
+    K, V = si.draw((1, H, n_prev + n_cur, 64), seed=1651, n_tensors=2)
+    boost = torch.ones(n_prev + n_cur)
+    boost[700:] = factor
+    boost[1000:] = 1.5 * factor
+    K = (K.float() * boost.view(1, 1, -1, 1)).to(torch.bfloat16)
+    q, k, v = Q.to(d), K.to(d), V.to(d)
+    O, LSE = hm.hmar_attn_step_fwd(q, k, v, n_prev, O=_nan_like(q), LSE=_nan_stats((1, H, n_cur), d))
+    rows = torch.arange(1, n_cur, 3, dtype=torch.int32, device=d)
+    Or, LSEr = _nan_like(q), _nan_stats((1, H, n_cur), d)
+    hm.hmar_attn_step_fwd_rows(q, k, v, n_prev, rows, Or, LSEr)
+    torch.cuda.synchronize()
+    assert torch.isfinite(O.float()).all() and torch.isfinite(Or[:, :, rows.long()].float()).all()
+    idx, heads, ref = rows.cpu().numpy(), [(0, 0), (0, 114), (0, 229)], {"O": [], "LSE": []}
+    for _, h in heads:
+        rO, rL = orc.attn_step_fwd(*[si.to_f64(t[:, h:h + 1]) for t in (Q, K, V)], n_prev)
+        ref["O"].append(rO[0, 0]); ref["LSE"].append(rL[0, 0])
+    ref = {n: np.stack(t) for n, t in ref.items()}
+    _compare(dict(O=O, LSE=LSE), ref, heads, "late-dominant keys, long steps")
+    _compare(dict(O=Or[:, :, rows.long()], LSE=LSEr[:, :, rows.long()]), {n: t[:, idx] for n, t in ref.items()}, heads,
+             "late-dominant keys, long steps, listed rows")
 
 
 def test_custom_softmax_scale():
