@@ -204,7 +204,7 @@ hmar_status hmar_schedule_tiles(const int32_t* side_lens, int32_t num_scales, in
  * hmar_profile_end() every kernel the library launches is bracketed by a pair of HIP events
  * recorded on the launch stream.  hmar_profile_end() waits for those events and adds up, per
  * kernel, the elapsed milliseconds and the number of launches.  Kernel ids: 0 forward (and
- * inference steps), 1 dK/dV, 2 dQ.  total_ms_out and launches_out are HOST arrays of
+ * inference steps), 1 dK/dV (also a small backward, which is one launch), 2 dQ.  total_ms_out and launches_out are HOST arrays of
  * HMAR_NUM_KERNELS entries (either may be null).  One stream at a time: the first launch
  * after hmar_profile_begin() fixes the stream; launches on any other stream are not
  * recorded and make hmar_profile_end() return HMAR_ERR_INVALID_ARG.  Launches must not be

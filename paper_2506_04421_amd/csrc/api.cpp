@@ -91,12 +91,14 @@ void pack_tables(const Schedule& s, unsigned char* staging, unsigned char* base,
         dev->row_hi[d] = reinterpret_cast<const int32_t*>(base + o);
         o += L * 4;
     }
-    dev->max_tiles = 0;
-    dev->total_tiles = 0;
-    for (const TileItem& it : s.items[0]) {
-        const int32_t tiles = (it.other_end - it.other_begin + 63) / 64;
-        dev->max_tiles = std::max(dev->max_tiles, tiles);
-        dev->total_tiles += tiles;
+    for (int d = 0; d < 2; ++d) {
+        dev->max_tiles[d] = 0;
+        dev->total_tiles[d] = 0;
+        for (const TileItem& it : s.items[d]) {
+            const int32_t tiles = (it.other_end - it.other_begin + 63) / 64;
+            dev->max_tiles[d] = std::max(dev->max_tiles[d], tiles);
+            dev->total_tiles[d] += tiles;
+        }
     }
     dev->L = s.L;
     dev->Lk = s.Lk;

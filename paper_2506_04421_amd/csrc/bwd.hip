@@ -40,26 +40,66 @@ struct BwdParams {
 #ifndef HMAR_DQ_MIN_WAVES
 #define HMAR_DQ_MIN_WAVES 4
 #endif
-// -Delta of a row from the lane's half of it: each half-wave holds 32 of the row's 64 dO values
+// acc + the dot product of eight elements of an O row with those of the dO row: two products per instruction
+// (v_dot2c_f32_bf16), fp32 accumulation
+__device__ __forceinline__ float delta_of_chunk(bf16x8 o, bf16x8 g, float acc) {
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(o, o, 0, 1), __builtin_shufflevector(g, g, 0, 1), acc, false);
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(o, o, 2, 3), __builtin_shufflevector(g, g, 2, 3), acc, false);
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(o, o, 4, 5), __builtin_shufflevector(g, g, 4, 5), acc, false);
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(o, o, 6, 7), __builtin_shufflevector(g, g, 6, 7), acc, false);
+}
+// -Delta of a row from the lane's half of it: chunks h, 2 + h, 4 + h, 6 + h of the row's eight
 __device__ __forceinline__ float neg_delta_of_row(const __bf16* o_row, const bf16x8 (&dob)[4], int h) {
     float acc = 0.f;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const bf16x8 ov = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(o_row + 16 * t + 8 * h));
-        const bf16x8 gv = dob[t];
-        // two products per instruction (v_dot2c_f32_bf16), fp32 accumulation
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(ov, ov, 0, 1), __builtin_shufflevector(gv, gv, 0, 1), acc, false);
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(ov, ov, 2, 3), __builtin_shufflevector(gv, gv, 2, 3), acc, false);
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(ov, ov, 4, 5), __builtin_shufflevector(gv, gv, 4, 5), acc, false);
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(ov, ov, 6, 7), __builtin_shufflevector(gv, gv, 6, 7), acc, false);
-    }
+    for (int t = 0; t < 4; ++t)
+        acc = delta_of_chunk(HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(o_row + 16 * t + 8 * h)), dob[t], acc);
     return -half_sum(acc);
 }
 
+// The statistics of a tile of 64 rows, formed by the four wavefronts of a workgroup, 16 rows each, 8 rows per load with a
+// chunk of a row per lane: whole cache lines (two lanes per row, as above, make a load touch 32 of them: 3.0 us for the
+// 425 rows that an item of the 680-token schedule visits, against 1.5).  The sum of a row is handed from lane to lane in
+// the order of neg_delta_of_row, so that the bits are the same.
+struct TileStats {
+    bf16x8 o[2], g[2];
+    float lse[2];
+    __device__ __forceinline__ void request(const __bf16* O, const __bf16* dO, const float* LSE, int row0, int row_max, int lane, int wave) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const size_t row = min(row0 + 16 * wave + 8 * j + (lane >> 3), row_max);
+            o[j] = *reinterpret_cast<const bf16x8*>(O + row * kD + 8 * (lane & 7));
+            g[j] = *reinterpret_cast<const bf16x8*>(dO + row * kD + 8 * (lane & 7));
+            lse[j] = LSE[row];
+        }
+    }
+    __device__ __forceinline__ void form(float* nl2, float* delta, int lane, int wave) const {
+        float acc[2] = {0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                // from the lane two to the left (row_shr:2); after step t the lanes of chunks 2t, 2t + 1 hold theirs
+                if (t > 0) acc[j] = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, acc[j]), 0x112, 0xf, 0xf, true));
+                acc[j] = delta_of_chunk(o[j], g[j], acc[j]);
+            }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const float other = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, acc[j]), 0xB1, 0xf, 0xf, true));
+            if ((lane & 7) == 7) {
+                const int r = 16 * wave + 8 * j + (lane >> 3);
+                delta[r] = -(acc[j] + other);
+                nl2[r] = -lse[j] * kLog2e;
+            }
+        }
+    }
+};
+
 // The work of one dQ item.  smem: ring of 2 stages, each a K tile followed by a V tile.
-// OWN_STATS: form the row statistics here and leave them in the workspace (the shipped kernel);
-// otherwise they are read from the workspace.
-template <bool OWN_STATS>
+// Where the row statistics come from: formed here and left in the workspace for the dK/dV kernel, formed here
+// for this item alone, or read from the workspace.
+enum class Stats { kFormAndLeave, kForm, kRead };
+template <Stats STATS>
 __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const int32_t* row_lo, const int32_t* row_hi,
                                         int head, int item_id, char* smem) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -97,10 +137,10 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
         dob[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(p.dO + head_in + (size_t)qrow * kD + 16 * t + 8 * h));
     }
     float nl2, ndelta;
-    if constexpr (OWN_STATS) {
+    if constexpr (STATS != Stats::kRead) {
         nl2 = -p.LSE[(size_t)HMAR_INPUT_HEAD(head) * p.L + qrow] * kLog2e;
         ndelta = neg_delta_of_row(p.O + head_in + (size_t)qrow * kD, dob, h);
-        if (wq0 + lr < it.own_end && h == 0) {
+        if (STATS == Stats::kFormAndLeave && wq0 + lr < it.own_end && h == 0) {
             p.neg_lse2[(size_t)head * p.L + qrow] = nl2;
             p.neg_delta[(size_t)head * p.L + qrow] = ndelta;
         }
@@ -184,7 +224,7 @@ __global__ __launch_bounds__(kThreads, HMAR_DQ_MIN_WAVES) void hmar_dq_kernel(Bw
 #endif
     int head, item_id;
     map_workgroup(p.map, &head, &item_id, true);
-    dq_body<true>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem);
+    dq_body<Stats::kFormAndLeave>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem);
 }
 
 // ---------------------------------------------------------------------------------- dK, dV
@@ -274,9 +314,12 @@ __device__ __forceinline__ void dkdv_tile(uint32_t Qt, uint32_t Gt, uint32_t nl2
 }
 
 // The work of one dK/dV item.  smem: ring of 2 stages, each a Q tile followed by a dO tile;
-// nl2_s, delta_s: the per-row statistics of the two stages.
+// nl2_s, delta_s: the statistics of the tiles' rows: of the two stages, streamed with them from the workspace, or
+// (STATS == kForm) of all tiles, formed here before the first step.
+template <Stats STATS>
 __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, const int32_t* row_lo, const int32_t* row_hi,
                                           int head, int item_id, char* smem, float (*nl2_s)[kTile], float (*delta_s)[kTile]) {
+    static_assert(STATS != Stats::kFormAndLeave, "the dQ kernel leaves them");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 31, h = lane >> 5;
     const size_t head_off = (size_t)head * p.L * kD;
@@ -298,8 +341,10 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
         const int qt = q_begin + ti * kTile;
         dma_tile(Qh, qt, qmax, stage, lo_, lane, wave);
         dma_tile(Gh, qt, qmax, stage + kTileBytes, lo_, lane, wave);
-        if (wave == 0) dma_floats(NLh, qt, qmax, nl2_base + st * (kTile * 4), lane);
-        else if (wave == 1) dma_floats(Dh, qt, qmax, delta_base + st * (kTile * 4), lane);
+        if constexpr (STATS == Stats::kRead) {
+            if (wave == 0) dma_floats(NLh, qt, qmax, nl2_base + st * (kTile * 4), lane);
+            else if (wave == 1) dma_floats(Dh, qt, qmax, delta_base + st * (kTile * 4), lane);
+        }
     };
     issue(0, 0);
 
@@ -317,6 +362,21 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
     for (int t = 0; t < 4; ++t) {
         kreg[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(p.K + head_in + (size_t)krow * kD + 16 * t + 8 * h));
         vreg[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(p.V + head_in + (size_t)krow * kD + 16 * t + 8 * h));
+    }
+
+    if constexpr (STATS == Stats::kForm) {
+        constexpr int kStatsAhead = 4;      // tiles whose rows are requested together; 2: +0.2 us, 7: the same
+        // rows past the last one get the last one's statistics, as they get its row (finite: their probabilities are 0)
+        for (int t0 = 0; t0 < ntiles; t0 += kStatsAhead) {
+            TileStats stats[kStatsAhead];
+#pragma unroll
+            for (int j = 0; j < kStatsAhead; ++j)
+                stats[j].request(p.O + head_in, Gh, p.LSE + (size_t)HMAR_INPUT_HEAD(head) * p.L, q_begin + (t0 + j) * kTile, qmax, lane, wave);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < kStatsAhead; ++j)
+                if (t0 + j < ntiles) stats[j].form(nl2_s[t0 + j], delta_s[t0 + j], lane, wave);
+        }
     }
 
     f32x16 dk[2], dv[2];
@@ -339,8 +399,8 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
         if (wave_active && qt < whi && qt + kTile > wlo) {
 #endif
             const uint32_t Qt = smem_base + ST * (2 * kTileBytes);
-            const uint32_t nl2_t = nl2_base + ST * (kTile * 4) + 16 * h;
-            const uint32_t delta_t = delta_base + ST * (kTile * 4) + 16 * h;
+            const uint32_t stats = (STATS == Stats::kForm ? ti : ST) * (kTile * 4) + 16 * h;
+            const uint32_t nl2_t = nl2_base + stats, delta_t = delta_base + stats;
             dkdv_tile(Qt, Qt + kTileBytes, nl2_t, delta_t, kreg, vreg, dk, dv, lo - qt - 4 * h, hi - qt - 4 * h,
                       qt < full_lo, qt + kTile > full_hi, p.c, lo_);
         }
@@ -368,7 +428,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_D
 #endif
     int head, item_id;
     map_workgroup(p.map, &head, &item_id);
-    dkdv_body(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem, nl2_s, delta_s);
+    dkdv_body<Stats::kRead>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem, nl2_s, delta_s);
+}
+
+// Both kernels' items in one launch, for launches too small to fill the chip, which are bound by the latency of one
+// item's chain of tiles (about 1 us a tile) and of the launch itself.  What puts the dK/dV kernel behind the dQ
+// kernel are the two row statistics; here every dK/dV item forms those of the rows it visits by itself, before its first
+// step (in the step ahead of their use they cost registers: spills, 0.7 us a tile).  Both work lists hold the same number of
+// items, heaviest first: the units of a head alternate between them.  32 heads of 680 tokens: 11.5 + 11.6 us in two
+// launches, 16.2 in one; 4 heads 11.1 + 11.1 -> 12.7.  Where the line lies: one_backward_launch (csrc/kernels.h).
+struct BwdBothParams {
+    BwdParams p;                                    // items, row_lo, row_hi: of the dQ list; map: of both lists
+    const Item* k_items; const int32_t* k_row_lo; const int32_t* k_row_hi;
+};
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_DKDV_MIN_WAVES, HMAR_DKDV_MIN_WAVES))) void hmar_bwd_both_kernel(BwdBothParams b) {
+    __shared__ __attribute__((aligned(1024))) char smem[2 * 2 * kTileBytes];
+    __shared__ __attribute__((aligned(256))) float nl2_s[kBothMaxTiles][kTile];
+    __shared__ __attribute__((aligned(256))) float delta_s[kBothMaxTiles][kTile];
+    int head, unit;
+    map_workgroup(b.p.map, &head, &unit);
+    const int item_id = unit >> 1;
+    if (unit & 1) dq_body<Stats::kForm>(b.p, b.p.items[item_id], b.p.row_lo, b.p.row_hi, head, item_id, smem);
+    else          dkdv_body<Stats::kForm>(b.p, b.k_items[item_id], b.k_row_lo, b.k_row_hi, head, item_id, smem, nl2_s, delta_s);
 }
 
 #if defined(HMAR_BWD_MERGED)
@@ -426,6 +507,23 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
 #if defined(HMAR_BWD_MERGED)
     return launch_bwd_merged(p, s, n_heads, stream);
 #endif
+    if (one_backward_launch(s, n_heads)) {
+        BwdBothParams b;
+        b.k_items = static_cast<const Item*>(s.items[1]);
+        b.k_row_lo = s.row_lo[1];
+        b.k_row_hi = s.row_hi[1];
+        p.items = static_cast<const Item*>(s.items[0]);
+        p.row_lo = s.row_lo[0];
+        p.row_hi = s.row_hi[0];
+        const int units = s.n_items[0] + s.n_items[1];
+        p.map = unit_map_for(s.num_cus, units, n_heads);
+        b.p = p;
+        profile_before(kKernelDkDv, stream);
+        hipLaunchKernelGGL(hmar_bwd_both_kernel, dim3(launch_groups(units, n_heads)), dim3(kThreads), 0, stream, b);
+        const hipError_t e = hipGetLastError();
+        profile_after(kKernelDkDv, stream);
+        return e;
+    }
     // dQ first: it also produces the per-row statistics the dK/dV kernel streams
     for (int dir = 0; dir < 2; ++dir) {
         p.items = static_cast<const Item*>(s.items[dir]);

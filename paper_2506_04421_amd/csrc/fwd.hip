@@ -481,7 +481,7 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
                        dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
-    const auto kernel = leaves_maxima_out(s.max_tiles, s.total_tiles, n_heads, s.num_cus) ? hmar_fwd_kernel<true>
+    const auto kernel = leaves_maxima_out(s.max_tiles[0], s.total_tiles[0], n_heads, s.num_cus) ? hmar_fwd_kernel<true>
                                                                                           : hmar_fwd_kernel<false>;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif

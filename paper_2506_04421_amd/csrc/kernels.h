@@ -11,8 +11,8 @@ namespace hmar {
 struct DeviceSchedule {
     const void* items[2];      // Item[n_items[dir]]
     int32_t n_items[2];
-    int32_t max_tiles;         // streamed 64-row tiles of the forward's longest item
-    int64_t total_tiles;       // and of all its items
+    int32_t max_tiles[2];      // streamed 64-row tiles of a list's longest item
+    int64_t total_tiles[2];    // and of all its items
     const int32_t* row_lo[2];  // L entries
     const int32_t* row_hi[2];
     int32_t L;                 // rows of Q, O, LSE per head
@@ -72,6 +72,24 @@ inline unsigned launch_groups(int n_items, int n_heads) {
 #endif
 inline bool leaves_maxima_out(int max_tiles, long long total_tiles, int n_heads, int num_cus) {
     return max_tiles >= HMAR_TUNE_LONG_STREAM && 4 * total_tiles * n_heads >= 7LL * num_cus * max_tiles;
+}
+
+// Whether a backward is one launch of both kernels' items (hmar_bwd_both_kernel; no bits depend on it): work for at
+// most two of the longest items on every compute unit, and windows whose statistics fit the LDS of two workgroups per
+// compute unit.  Forward and backward in us, two launches -> one, by `fill` = tiles of both lists / (tiles of the
+// longest item * compute units), 256 compute units:
+//   680 tokens (7 tiles):   4 heads, 0.1  31.0 -> 21.8;  32, 1.1  31.7 -> 25.6;  48, 1.7  33.9 -> 30.4;  64, 2.3  36.4 -> 33.1;
+//                           80, 2.9  42.0 -> 39.4;  100, 3.6  48.0 -> 48.2
+//   2240 tokens (25 tiles): 4 heads, 0.4  80.8 -> 59.3;  13, 1.3  83.3 -> 72.9;  20, 2.0  96.5 -> 96.1;  26, 2.6  101 -> 112
+//   466 tokens (6 tiles):   48 heads, 1.1  29.3 -> 23.4;  75, 1.7  33.2 -> 29.8;  100, 2.3  34.5 -> 35.0
+constexpr int kBothMaxTiles = 64;          // tiles a dK/dV item may visit
+#ifndef HMAR_TUNE_BOTH_FILL
+#define HMAR_TUNE_BOTH_FILL 2              // measurement builds: the line (0: always two launches)
+#endif
+inline bool one_backward_launch(const DeviceSchedule& s, int n_heads) {
+    const long long total = (s.total_tiles[0] + s.total_tiles[1]) * n_heads;
+    return s.n_items[0] == s.n_items[1] && s.max_tiles[1] <= kBothMaxTiles &&
+           total <= (long long)HMAR_TUNE_BOTH_FILL * std::max(s.max_tiles[0], s.max_tiles[1]) * s.num_cus;
 }
 
 // Per-kernel event bracketing for hmar_profile_begin/end (no-ops unless profiling is on).
