@@ -49,11 +49,10 @@ __device__ __forceinline__ float delta_of_chunk(bf16x8 o, bf16x8 g, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(o, o, 6, 7), __builtin_shufflevector(g, g, 6, 7), acc, false);
 }
 // -Delta of a row from the lane's half of it: chunks h, 2 + h, 4 + h, 6 + h of the row's eight
-__device__ __forceinline__ float neg_delta_of_row(const __bf16* o_row, const bf16x8 (&dob)[4], int h) {
+__device__ __forceinline__ float neg_delta_of_row(const bf16x8 (&o)[4], const bf16x8 (&dob)[4]) {
     float acc = 0.f;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-        acc = delta_of_chunk(HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(o_row + 16 * t + 8 * h)), dob[t], acc);
+    for (int t = 0; t < 4; ++t) acc = delta_of_chunk(o[t], dob[t], acc);
     return -half_sum(acc);
 }
 
@@ -130,21 +129,26 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
     const int wlo = row_lo[rfirst], whi = row_hi[rlast];        // union of the wavefront's ranges
     const int full_lo = row_lo[rlast], full_hi = row_hi[rfirst];  // what every one of its rows pairs with
 
+    auto own_row = [&](int r) { return min(wq0 + r, it.own_end - 1); };
+    const uint32_t patch = smem_base + 2 * kTileBytes + wave * 4096;      // in the stage that no load runs into before the barrier
+    const RawRows raw_q = request_rows(p.Q + head_in, own_row, lane), raw_do = request_rows(p.dO + head_in, own_row, lane);
     bf16x8 q[4], dob[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        q[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(p.Q + head_in + (size_t)qrow * kD + 16 * t + 8 * h));
-        dob[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(p.dO + head_in + (size_t)qrow * kD + 16 * t + 8 * h));
-    }
     float nl2, ndelta;
     if constexpr (STATS != Stats::kRead) {
+        const RawRows raw_o = request_rows(p.O + head_in, own_row, lane);
         nl2 = -p.LSE[(size_t)HMAR_INPUT_HEAD(head) * p.L + qrow] * kLog2e;
-        ndelta = neg_delta_of_row(p.O + head_in + (size_t)qrow * kD, dob, h);
+        bf16x8 o[4];
+        rows_to_operand(patch, raw_q, lo_, lane, q);
+        rows_to_operand(patch, raw_do, lo_, lane, dob);
+        rows_to_operand(patch, raw_o, lo_, lane, o);
+        ndelta = neg_delta_of_row(o, dob);
         if (STATS == Stats::kFormAndLeave && wq0 + lr < it.own_end && h == 0) {
             p.neg_lse2[(size_t)head * p.L + qrow] = nl2;
             p.neg_delta[(size_t)head * p.L + qrow] = ndelta;
         }
     } else {
+        rows_to_operand(patch, raw_q, lo_, lane, q);
+        rows_to_operand(patch, raw_do, lo_, lane, dob);
         nl2 = p.neg_lse2[(size_t)head * p.L + qrow];
         ndelta = p.neg_delta[(size_t)head * p.L + qrow];
     }
@@ -357,12 +361,8 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
     const int wlo = row_lo[rfirst], whi = row_hi[rlast];        // union of the wavefront's ranges
     const int full_lo = row_lo[rlast], full_hi = row_hi[rfirst];  // what every one of its rows pairs with
 
-    bf16x8 kreg[4], vreg[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        kreg[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(p.K + head_in + (size_t)krow * kD + 16 * t + 8 * h));
-        vreg[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(p.V + head_in + (size_t)krow * kD + 16 * t + 8 * h));
-    }
+    auto own_row = [&](int r) { return min(wk0 + r, it.own_end - 1); };
+    const RawRows raw_k = request_rows(p.K + head_in, own_row, lane), raw_v = request_rows(p.V + head_in, own_row, lane);
 
     if constexpr (STATS == Stats::kForm) {
         constexpr int kStatsAhead = 4;      // tiles whose rows are requested together; 2: +0.2 us, 7: the same
@@ -385,6 +385,10 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
 #pragma unroll
         for (int i = 0; i < 16; ++i) { dk[mb][i] = 0.f; dv[mb][i] = 0.f; }
 
+    bf16x8 kreg[4], vreg[4];
+    const uint32_t patch = smem_base + 2 * kTileBytes + wave * 4096;      // in the stage that no load runs into before the barrier
+    rows_to_operand(patch, raw_k, lo_, lane, kreg);
+    rows_to_operand(patch, raw_v, lo_, lane, vreg);
     asm volatile("" :: "v"(kreg[0]), "v"(kreg[1]), "v"(kreg[2]), "v"(kreg[3]), "v"(vreg[0]), "v"(vreg[1]),
                  "v"(vreg[2]), "v"(vreg[3]));
     HMAR_WAIT_DMA_AND_BARRIER(0);
@@ -413,9 +417,9 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
     }
 
     if (wave_active) {
-        const uint32_t patch = smem_base + wave * kPatchBytes;
-        store_block_rows(patch, dk, p.sm_scale, p.dK + head_off, wk0, it.own_end - wk0, lane, nullptr, HMAR_NT_GRADS != 0);
-        store_block_rows(patch, dv, 1.0f, p.dV + head_off, wk0, it.own_end - wk0, lane, nullptr, HMAR_NT_GRADS != 0);
+        const uint32_t out = smem_base + wave * kPatchBytes;
+        store_block_rows(out, dk, p.sm_scale, p.dK + head_off, wk0, it.own_end - wk0, lane, nullptr, HMAR_NT_GRADS != 0);
+        store_block_rows(out, dv, 1.0f, p.dV + head_off, wk0, it.own_end - wk0, lane, nullptr, HMAR_NT_GRADS != 0);
     }
 }
 

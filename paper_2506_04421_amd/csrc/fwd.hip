@@ -273,10 +273,7 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     int q_rows_per_head = 0;
     if constexpr (STEPS) q_rows_per_head = q_stride_rows;
     const int qrow_mem = rows ? min(max(rows[qrow], 0), q_rows_per_head - 1) : qrow;
-    bf16x8 q[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        q[t] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(Qh + (size_t)qrow_mem * kD + 16 * t + 8 * h));
+    const RawRows raw = request_rows(Qh, [&](int r) { return rows ? __shfl(qrow_mem, r) : min(wq0 + r, it.own_end - 1); }, lane);
 
     f32x16 o[2];
 #pragma unroll
@@ -287,10 +284,11 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     bool suspect = false;             // LAZY: a tile had to be formed again
     bool o_empty = true;              // nothing accumulated yet: the first rescale has nothing to scale
 
-    // The compiler does not see the DMA loads; without this use it would wait for the Q
-    // registers inside the loop, where its count would also drain the loads running ahead.
+    bf16x8 q[4];                      // through the ring's last stage, which no load runs into before the barrier
+    rows_to_operand(smem_base + (kFwdStages - 1) * (2 * kTileBytes) + wave * 4096, raw, lo_, lane, q);
+    // Loads complete in order: the rows above were requested after tile 0.  The operands are read here and not in
+    // the loop, whose first loads overwrite the patch.
     asm volatile("" :: "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]));
-    // Loads complete in order: the registers above were requested after tile 0.
     HMAR_WAIT_DMA_AND_BARRIER(0);
 
     // One tile: request the next one, compute, wait for the request.  The stage is a template
