@@ -49,10 +49,10 @@ __device__ __forceinline__ float delta_of_chunk(bf16x8 o, bf16x8 g, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(o, o, 6, 7), __builtin_shufflevector(g, g, 6, 7), acc, false);
 }
 // -Delta of a row from the lane's half of it: chunks h, 2 + h, 4 + h, 6 + h of the row's eight
-__device__ __forceinline__ float neg_delta_of_row(const bf16x8 (&o)[4], const bf16x8 (&dob)[4]) {
+__device__ __forceinline__ float neg_delta_of_row(const OwnRows& o, const OwnRows& dob) {
     float acc = 0.f;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc = delta_of_chunk(o[t], dob[t], acc);
+    for (int t = 0; t < 4; ++t) acc = delta_of_chunk(o.chunk[t], dob.chunk[t], acc);
     return -half_sum(acc);
 }
 
@@ -98,7 +98,7 @@ struct TileStats {
 // Where the row statistics come from: formed here and left in the workspace for the dK/dV kernel, formed here
 // for this item alone, or read from the workspace.
 enum class Stats { kFormAndLeave, kForm, kRead };
-template <Stats STATS>
+template <Stats STATS, bool WHOLE>
 __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const int32_t* row_lo, const int32_t* row_hi,
                                         int head, int item_id, char* smem) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -129,28 +129,26 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
     const int wlo = row_lo[rfirst], whi = row_hi[rlast];        // union of the wavefront's ranges
     const int full_lo = row_lo[rlast], full_hi = row_hi[rfirst];  // what every one of its rows pairs with
 
-    auto own_row = [&](int r) { return min(wq0 + r, it.own_end - 1); };
     const uint32_t patch = smem_base + 2 * kTileBytes + wave * 4096;      // in the stage that no load runs into before the barrier
-    const RawRows raw_q = request_rows(p.Q + head_in, own_row, lane), raw_do = request_rows(p.dO + head_in, own_row, lane);
-    bf16x8 q[4], dob[4];
+    auto own = [&](int r) { return min(wq0 + r, it.own_end - 1); };
+    OwnRows q = request_rows<WHOLE>(p.Q + head_in, qrow, own, lane), dob = request_rows<WHOLE>(p.dO + head_in, qrow, own, lane);
     float nl2, ndelta;
     if constexpr (STATS != Stats::kRead) {
-        const RawRows raw_o = request_rows(p.O + head_in, own_row, lane);
+        OwnRows o = request_rows<WHOLE>(p.O + head_in, qrow, own, lane);
         nl2 = -p.LSE[(size_t)HMAR_INPUT_HEAD(head) * p.L + qrow] * kLog2e;
-        bf16x8 o[4];
-        rows_to_operand(patch, raw_q, lo_, lane, q);
-        rows_to_operand(patch, raw_do, lo_, lane, dob);
-        rows_to_operand(patch, raw_o, lo_, lane, o);
+        turn_rows<WHOLE>(patch, q, lo_, lane);
+        turn_rows<WHOLE>(patch, dob, lo_, lane);
+        turn_rows<WHOLE>(patch, o, lo_, lane);
         ndelta = neg_delta_of_row(o, dob);
         if (STATS == Stats::kFormAndLeave && wq0 + lr < it.own_end && h == 0) {
             p.neg_lse2[(size_t)head * p.L + qrow] = nl2;
             p.neg_delta[(size_t)head * p.L + qrow] = ndelta;
         }
     } else {
-        rows_to_operand(patch, raw_q, lo_, lane, q);
-        rows_to_operand(patch, raw_do, lo_, lane, dob);
         nl2 = p.neg_lse2[(size_t)head * p.L + qrow];
         ndelta = p.neg_delta[(size_t)head * p.L + qrow];
+        turn_rows<WHOLE>(patch, q, lo_, lane);
+        turn_rows<WHOLE>(patch, dob, lo_, lane);
     }
 
     f32x16 dq[2];
@@ -161,8 +159,8 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
 
     // make the compiler wait for these registers here, not inside the loop (see the forward);
     // loads complete in order, so tile 0 has landed as well
-    asm volatile("" :: "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]), "v"(dob[0]), "v"(dob[1]), "v"(dob[2]),
-                 "v"(dob[3]), "v"(nl2), "v"(ndelta));
+    asm volatile("" :: "v"(q.chunk[0]), "v"(q.chunk[1]), "v"(q.chunk[2]), "v"(q.chunk[3]), "v"(dob.chunk[0]), "v"(dob.chunk[1]),
+                 "v"(dob.chunk[2]), "v"(dob.chunk[3]), "v"(nl2), "v"(ndelta));
     HMAR_WAIT_DMA_AND_BARRIER(0);
 
     // one tile: request the next one, compute, wait for the request; the stage is a template
@@ -189,8 +187,8 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
                 for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    s = mfma32(lds_a_row(Kt, lo_, kb, t), q[t], s);
-                    dp = mfma32(lds_a_row(Vt, lo_, kb, t), dob[t], dp);
+                    s = mfma32(lds_a_row(Kt, lo_, kb, t), q.chunk[t], s);
+                    dp = mfma32(lds_a_row(Vt, lo_, kb, t), dob.chunk[t], dp);
                 }
                 mask_block(s, 32 * kb, lim_lo, lim_hi, need_lo, need_hi);     // exp2(-inf) = 0
 #pragma unroll
@@ -221,6 +219,7 @@ __device__ __forceinline__ void dq_body(const BwdParams& p, const Item it, const
         store_block_rows(smem_base + wave * kPatchBytes, dq, p.sm_scale, p.dQ + head_off, wq0, it.own_end - wq0, lane, nullptr, HMAR_NT_GRADS != 0);
 }
 
+template <bool WHOLE>
 __global__ __launch_bounds__(kThreads, HMAR_DQ_MIN_WAVES) void hmar_dq_kernel(BwdParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[2 * 2 * kTileBytes];
 #ifdef HMAR_TUNE_LDS_PAD_DQ
@@ -228,7 +227,7 @@ __global__ __launch_bounds__(kThreads, HMAR_DQ_MIN_WAVES) void hmar_dq_kernel(Bw
 #endif
     int head, item_id;
     map_workgroup(p.map, &head, &item_id, true);
-    dq_body<Stats::kFormAndLeave>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem);
+    dq_body<Stats::kFormAndLeave, WHOLE>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem);
 }
 
 // ---------------------------------------------------------------------------------- dK, dV
@@ -320,7 +319,7 @@ __device__ __forceinline__ void dkdv_tile(uint32_t Qt, uint32_t Gt, uint32_t nl2
 // The work of one dK/dV item.  smem: ring of 2 stages, each a Q tile followed by a dO tile;
 // nl2_s, delta_s: the statistics of the tiles' rows: of the two stages, streamed with them from the workspace, or
 // (STATS == kForm) of all tiles, formed here before the first step.
-template <Stats STATS>
+template <Stats STATS, bool WHOLE>
 __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, const int32_t* row_lo, const int32_t* row_hi,
                                           int head, int item_id, char* smem, float (*nl2_s)[kTile], float (*delta_s)[kTile]) {
     static_assert(STATS != Stats::kFormAndLeave, "the dQ kernel leaves them");
@@ -361,8 +360,8 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
     const int wlo = row_lo[rfirst], whi = row_hi[rlast];        // union of the wavefront's ranges
     const int full_lo = row_lo[rlast], full_hi = row_hi[rfirst];  // what every one of its rows pairs with
 
-    auto own_row = [&](int r) { return min(wk0 + r, it.own_end - 1); };
-    const RawRows raw_k = request_rows(p.K + head_in, own_row, lane), raw_v = request_rows(p.V + head_in, own_row, lane);
+    auto own = [&](int r) { return min(wk0 + r, it.own_end - 1); };
+    OwnRows krows = request_rows<WHOLE>(p.K + head_in, krow, own, lane), vrows = request_rows<WHOLE>(p.V + head_in, krow, own, lane);
 
     if constexpr (STATS == Stats::kForm) {
         constexpr int kStatsAhead = 4;      // tiles whose rows are requested together; 2: +0.2 us, 7: the same
@@ -385,10 +384,10 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
 #pragma unroll
         for (int i = 0; i < 16; ++i) { dk[mb][i] = 0.f; dv[mb][i] = 0.f; }
 
-    bf16x8 kreg[4], vreg[4];
     const uint32_t patch = smem_base + 2 * kTileBytes + wave * 4096;      // in the stage that no load runs into before the barrier
-    rows_to_operand(patch, raw_k, lo_, lane, kreg);
-    rows_to_operand(patch, raw_v, lo_, lane, vreg);
+    turn_rows<WHOLE>(patch, krows, lo_, lane);
+    turn_rows<WHOLE>(patch, vrows, lo_, lane);
+    const bf16x8 (&kreg)[4] = krows.chunk, (&vreg)[4] = vrows.chunk;
     asm volatile("" :: "v"(kreg[0]), "v"(kreg[1]), "v"(kreg[2]), "v"(kreg[3]), "v"(vreg[0]), "v"(vreg[1]),
                  "v"(vreg[2]), "v"(vreg[3]));
     HMAR_WAIT_DMA_AND_BARRIER(0);
@@ -423,6 +422,7 @@ __device__ __forceinline__ void dkdv_body(const BwdParams& p, const Item it, con
     }
 }
 
+template <bool WHOLE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_DKDV_MIN_WAVES, HMAR_DKDV_MIN_WAVES))) void hmar_dkdv_kernel(BwdParams p) {
     __shared__ __attribute__((aligned(1024))) char smem[2 * 2 * kTileBytes];
     __shared__ __attribute__((aligned(256))) float nl2_s[2][kTile];
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_D
 #endif
     int head, item_id;
     map_workgroup(p.map, &head, &item_id);
-    dkdv_body<Stats::kRead>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem, nl2_s, delta_s);
+    dkdv_body<Stats::kRead, WHOLE>(p, p.items[item_id], p.row_lo, p.row_hi, head, item_id, smem, nl2_s, delta_s);
 }
 
 // Both kernels' items in one launch, for launches too small to fill the chip, which are bound by the latency of one
@@ -452,8 +452,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_D
     int head, unit;
     map_workgroup(b.p.map, &head, &unit);
     const int item_id = unit >> 1;
-    if (unit & 1) dq_body<Stats::kForm>(b.p, b.p.items[item_id], b.p.row_lo, b.p.row_hi, head, item_id, smem);
-    else          dkdv_body<Stats::kForm>(b.p, b.k_items[item_id], b.k_row_lo, b.k_row_hi, head, item_id, smem, nl2_s, delta_s);
+    if (unit & 1) dq_body<Stats::kForm, true>(b.p, b.p.items[item_id], b.p.row_lo, b.p.row_hi, head, item_id, smem);
+    else          dkdv_body<Stats::kForm, true>(b.p, b.k_items[item_id], b.k_row_lo, b.k_row_hi, head, item_id, smem, nl2_s, delta_s);
 }
 
 #if defined(HMAR_BWD_MERGED)
@@ -536,6 +536,7 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
         const unsigned groups = launch_groups(s.n_items[dir], n_heads);
         if (groups == 0) return hipErrorInvalidValue;
         p.map = unit_map_for(s.num_cus, s.n_items[dir], n_heads);
+        const bool whole = dir == 1 ? whole_rows_dkdv(groups, s.max_tiles[dir], s.num_cus) : whole_rows_dq(groups, s.max_tiles[dir], s.num_cus);
         const int kid = dir == 1 ? kKernelDkDv : kKernelDq;
         profile_before(kid, stream);
 #if HMAR_DKDV_KEYS_PER_WAVE == 16
@@ -549,9 +550,9 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
                                p, (int)groups);
         }
 #else
-        if (dir == 1) hipLaunchKernelGGL(hmar_dkdv_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
+        if (dir == 1) hipLaunchKernelGGL(whole ? hmar_dkdv_kernel<true> : hmar_dkdv_kernel<false>, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
-        else          hipLaunchKernelGGL(hmar_dq_kernel, dim3(groups), dim3(kThreads), 0, stream, p);
+        else          hipLaunchKernelGGL(whole ? hmar_dq_kernel<true> : hmar_dq_kernel<false>, dim3(groups), dim3(kThreads), 0, stream, p);
         const hipError_t e = hipGetLastError();
         profile_after(kid, stream);
         if (e != hipSuccess) return e;

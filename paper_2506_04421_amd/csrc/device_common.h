@@ -309,29 +309,33 @@ __device__ __forceinline__ bf16x8 lds_a_tr(uint32_t tile, const LaneOffsets& o, 
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// A wavefront's own 32 rows as operands (lane: row lr, columns 16t + 8h .. +7 in out[t]).  Asking for them in that
-// layout makes every load touch all 32 rows, 16 bytes at a time; asked for as they lie in memory a load is eight
-// whole rows (row_of(r): row r of the wavefront; lane l gets chunk l % 8 of rows 8j + l / 8), and a detour through
-// 4 KB of LDS that belong to the wavefront (`patch`) turns them round.  LDS operations of one wavefront execute in
-// order: no barrier, and the patch can be used again at once.  What it saves is address work ahead of the first tile
-// (dQ asks for three operands, 48 loads a workgroup): backward of 64 heads of 680 tokens 16.3 + 14.9 -> 15.4 + 13.7 us,
-// of 100 heads of 466 tokens 15.5 + 13.9 -> 14.6 + 12.8; launches that fill the chip are bound elsewhere (0..-1 %).
-struct RawRows { bf16x8 chunk[4]; };
-template <typename RowOf>
-__device__ __forceinline__ RawRows request_rows(const __bf16* base, RowOf row_of, int lane) {
-    RawRows raw;
+// A wavefront's own 32 rows as operands (lane: row lr, columns 16t + 8h .. +7 in chunk[t]).  Asked for in that layout,
+// every load touches all 32 rows, 16 bytes at a time; asked for as they lie in memory (WHOLE) a load is eight whole rows
+// (lane l gets chunk l % 8 of rows 8j + l / 8), and a detour through 4 KB of LDS that belong to the wavefront
+// (`patch`) turns them round.  LDS operations of one wavefront execute in order: no barrier, and the patch can be used
+// again at once.  Which is better: whole_rows_* (csrc/kernels.h).
+struct OwnRows { bf16x8 chunk[4]; };
+template <bool WHOLE, typename RowOf>          // own: row lr of the wavefront; row_of(r): its row r
+__device__ __forceinline__ OwnRows request_rows(const __bf16* head, int own, RowOf row_of, int lane) {
+    OwnRows rows;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        raw.chunk[j] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(base + (size_t)row_of(8 * j + (lane >> 3)) * kD + 8 * (lane & 7)));
-    return raw;
+    for (int j = 0; j < 4; ++j) {
+        const __bf16* at = WHOLE ? head + (size_t)row_of(8 * j + (lane >> 3)) * kD + 8 * (lane & 7)
+                                 : head + (size_t)own * kD + 16 * j + 8 * (lane >> 5);
+        rows.chunk[j] = HMAR_ROW_LOAD(reinterpret_cast<const bf16x8*>(at));
+    }
+    return rows;
 }
-__device__ __forceinline__ void rows_to_operand(uint32_t patch, const RawRows& raw, const LaneOffsets& o, int lane, bf16x8 (&out)[4]) {
-    typedef __attribute__((address_space(3))) bf16x8 lds_out;
-    const uint32_t even = patch + (lane >> 3) * kRowBytes + (((lane & 7) ^ swz(lane >> 3)) << 4);
+template <bool WHOLE>
+__device__ __forceinline__ void turn_rows(uint32_t patch, OwnRows& rows, const LaneOffsets& o, int lane) {
+    if constexpr (WHOLE) {
+        typedef __attribute__((address_space(3))) bf16x8 lds_out;
+        const uint32_t even = patch + (lane >> 3) * kRowBytes + (((lane & 7) ^ swz(lane >> 3)) << 4);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) *(lds_out*)((j & 1 ? even ^ 32 : even) + j * 1024) = raw.chunk[j];   // swz(r + 8) = swz(r) ^ 2
+        for (int j = 0; j < 4; ++j) *(lds_out*)((j & 1 ? even ^ 32 : even) + j * 1024) = rows.chunk[j];   // swz(r + 8) = swz(r) ^ 2
 #pragma unroll
-    for (int t = 0; t < 4; ++t) out[t] = lds_a_row(patch, o, 0, t);
+        for (int t = 0; t < 4; ++t) rows.chunk[t] = lds_a_row(patch, o, 0, t);
+    }
 }
 
 // Mask one 32 x 32 score block held in the C layout.  Register i of the lane is the

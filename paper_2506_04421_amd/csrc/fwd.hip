@@ -45,14 +45,17 @@ struct StepDesc {
 // workgroup: they come last in `step` and share ONE item per head, the launch's last, in which
 // every wavefront works on its own: unit u of the pack is the 32-row block pack_unit[u] % 2 of step
 // pack_unit[u] / 2, taken by wavefront u % 4 (see small_steps_pack).
-constexpr int kMaxPackUnits = 2 * kMaxSteps;
+// N: steps there is room for, kMaxSteps or 1.  A call of one step, as a sampling loop makes them, hands over 120 bytes
+// instead of 1.2 KB: they fill two cache lines, and the host does not write the rest.
+template <int N>
 struct StepParams {
-    StepDesc step[kMaxSteps];   // the n_tiled steps that get items of their own, then the packed ones
+    static constexpr int kRoom = N;
     UnitMap map;
     int n_tiled, n_heads;
     int n_pack;                 // units of the pack (0: the launch has no pack item)
-    int pack_unit[kMaxPackUnits];
     float c;
+    StepDesc step[N];           // the n_tiled steps that get items of their own, then the packed ones
+    int pack_unit[2 * N];
 };
 
 // Softmax reference.  Probabilities are formed against a row's reference maximum and are at most 2^8,
@@ -84,10 +87,11 @@ static_assert(kFwdStages >= 2 && kFwdStages <= 4, "ring depth");
 // LDS (one tile, at Vt), from where the transpose load feeds the second contraction; the same LDS
 // then serves as the patch of the result.  One tile holds all keys, so the softmax is the plain
 // one: row maximum, exponentials, row sum.  No barrier: nothing is shared between wavefronts.
-__device__ __forceinline__ void small_step_unit(const StepParams& p, int head, int unit, uint32_t Vt, const LaneOffsets& lo_) {
+template <int N>
+__device__ __forceinline__ void small_step_unit(const StepParams<N>& p, int head, int unit, uint32_t Vt, const LaneOffsets& lo_) {
     const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
     static_assert(kPatchBytes <= kTileBytes, "the result patch reuses the value tile");
-    const StepDesc& sd = p.step[unit >> 1];
+    const StepDesc& sd = p.step[N == 1 ? 0 : unit >> 1];
     const int n_q = sd.n_q, Lk = sd.Lk;                 // Lk <= 64, no row map
     const int row0 = 32 * (unit & 1);                   // < n_q
     const size_t in_head = (size_t)HMAR_INPUT_HEAD(head);
@@ -172,7 +176,8 @@ __device__ __forceinline__ void small_step_unit(const StepParams& p, int head, i
 
 // The pack item of a steps launch that has larger steps too: wavefront w takes the units w, w + 4, ... of the
 // workgroup's head.
-__device__ __forceinline__ void small_steps_pack(const StepParams& p, int head, char* smem) {
+template <int N>
+__device__ __forceinline__ void small_steps_pack(const StepParams<N>& p, int head, char* smem) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LaneOffsets lo_ = make_lane_offsets(threadIdx.x & 63, 0);
     const uint32_t Vt = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kTileBytes);
@@ -183,7 +188,8 @@ __device__ __forceinline__ void small_steps_pack(const StepParams& p, int head, 
 // side.  (One workgroup per head, as the pack has it, leaves three of four wavefronts without work in a
 // step of up to 32 rows, and 1536 heads take two rounds of workgroups where this takes less than one.
 // Steps of 1, 4, 9, 16, 25, 36 tokens: 8.8 9.2 9.8 10.6 12.4 15.7 -> 5.5 5.7 6.8 7.8 10.7 13.3 us.)
-__global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_steps_kernel(StepParams p) {
+template <int N>
+__global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_steps_kernel(StepParams<N> p) {
     __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned u = blockIdx.x * 4 + wave;
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_s
 
 // One body serves both launches: with STEPS the item, its buffers and its (trivial) pair ranges
 // come from the step descriptors, otherwise from the schedule tables.
-template <bool STEPS, bool LAZY, typename Params>
+template <bool STEPS, bool LAZY, bool WHOLE, typename Params>
 __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     int head, item_id;
     map_workgroup(p.map, &head, &item_id);
@@ -211,8 +217,8 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
             small_steps_pack(p, head, smem);
             return;
         }
-        int si = 0;
-        while (si + 1 < p.n_tiled && item_id >= p.step[si + 1].first_item) ++si;
+        int si = 0;                        // n_tiled is 1 where there is room for one
+        while (Params::kRoom > 1 && si + 1 < p.n_tiled && item_id >= p.step[si + 1].first_item) ++si;
         const StepDesc& sd = p.step[si];
         const int li = item_id - sd.first_item;
         it.own_begin = li * 128;
@@ -273,7 +279,7 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     int q_rows_per_head = 0;
     if constexpr (STEPS) q_rows_per_head = q_stride_rows;
     const int qrow_mem = rows ? min(max(rows[qrow], 0), q_rows_per_head - 1) : qrow;
-    const RawRows raw = request_rows(Qh, [&](int r) { return rows ? __shfl(qrow_mem, r) : min(wq0 + r, it.own_end - 1); }, lane);
+    OwnRows q = request_rows<WHOLE>(Qh, qrow_mem, [&](int r) { return rows ? __shfl(qrow_mem, r) : min(wq0 + r, it.own_end - 1); }, lane);
 
     f32x16 o[2];
 #pragma unroll
@@ -284,11 +290,11 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     bool suspect = false;             // LAZY: a tile had to be formed again
     bool o_empty = true;              // nothing accumulated yet: the first rescale has nothing to scale
 
-    bf16x8 q[4];                      // through the ring's last stage, which no load runs into before the barrier
-    rows_to_operand(smem_base + (kFwdStages - 1) * (2 * kTileBytes) + wave * 4096, raw, lo_, lane, q);
+    // through the ring's last stage, which no load runs into before the barrier
+    turn_rows<WHOLE>(smem_base + (kFwdStages - 1) * (2 * kTileBytes) + wave * 4096, q, lo_, lane);
     // Loads complete in order: the rows above were requested after tile 0.  The operands are read here and not in
     // the loop, whose first loads overwrite the patch.
-    asm volatile("" :: "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]));
+    asm volatile("" :: "v"(q.chunk[0]), "v"(q.chunk[1]), "v"(q.chunk[2]), "v"(q.chunk[3]));
     HMAR_WAIT_DMA_AND_BARRIER(0);
 
     // One tile: request the next one, compute, wait for the request.  The stage is a template
@@ -316,22 +322,31 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                     asm volatile("" ::: "memory");
                     asm volatile("" : "+v"(lim_lo), "+v"(lim_hi));
                 }
-                // The training launches request all eight operands ahead of the first contraction; left to itself the
-                // compiler reads each next to its use and waits for it there: 4 heads of 2240 tokens 25.6 -> 24.1 us, 32
-                // of 680 tokens 11.6 -> 11.2, -0.6 % on full launches.  Steps, which have no edges to mask inside their
-                // stream, are scheduled better without it (a row list of 25 tiles 46.2 -> 46.9 us with it).
-                bf16x8 a[2][4];
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) a[kb][t] = lds_a_row(Kt, lo_, kb, t);
-                if constexpr (!STEPS) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
                     for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+                if constexpr (!STEPS && !LAZY) {
+                    // all eight operands are requested ahead of the first contraction; left to itself the compiler
+                    // reads each next to its use and waits for it there: 4 heads of 2240 tokens 25.6 -> 24.1 us, 32 of
+                    // 680 tokens 11.6 -> 11.2, -0.6 % on full launches.  The other forms do without: there is no
+                    // room for it where maxima are left out (2240 tokens, 192 heads: +2 %), and steps, without
+                    // edges to mask inside their stream, come out better scheduled (25 tiles of a row list: 46.2 us, with it 46.9)
+                    bf16x8 a[2][4];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) s[kb] = mfma32(a[kb][t], q[t], s[kb]);
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) a[kb][t] = lds_a_row(Kt, lo_, kb, t);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) s[kb] = mfma32(a[kb][t], q.chunk[t], s[kb]);
+                } else {
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) s[kb] = mfma32(lds_a_row(Kt, lo_, kb, t), q.chunk[t], s[kb]);
                 }
                 // element i of block kb is key kt + 4h + 32kb + 8(i/4) + i%4; allowed iff lo <= key < hi
 #pragma unroll
@@ -433,20 +448,20 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     }
 }
 
-template <bool LAZY>
+template <bool LAZY, bool WHOLE>
 __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_kernel(FwdParams p) {
     // ring of stages, each a K tile followed by a V tile
     __shared__ __attribute__((aligned(1024))) char smem[kFwdStages * 2 * kTileBytes];
 #ifdef HMAR_TUNE_LDS_PAD_FWD
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_FWD)
 #endif
-    fwd_body<false, LAZY>(p, smem);
+    fwd_body<false, LAZY, WHOLE>(p, smem);
 }
 
-template <bool LAZY>
-__global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_steps_kernel(StepParams p) {
+template <bool LAZY, bool WHOLE, int N>
+__global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_steps_kernel(StepParams<N> p) {
     __shared__ __attribute__((aligned(1024))) char smem[kFwdStages * 2 * kTileBytes];
-    fwd_body<true, LAZY>(p, smem);
+    fwd_body<true, LAZY, WHOLE>(p, smem);
 }
 
 #ifdef HMAR_TUNE_FWD_STUDY
@@ -488,8 +503,9 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
                        dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
-    const auto kernel = leaves_maxima_out(s.max_tiles[0], s.total_tiles[0], n_heads, s.num_cus) ? hmar_fwd_kernel<true>
-                                                                                          : hmar_fwd_kernel<false>;
+    const auto kernel = leaves_maxima_out(s.max_tiles[0], s.total_tiles[0], n_heads, s.num_cus) ? hmar_fwd_kernel<true, false>
+                        : whole_rows_fwd(groups, s.num_cus)                                     ? hmar_fwd_kernel<false, true>
+                                                                                                : hmar_fwd_kernel<false, false>;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
     const hipError_t e = hipGetLastError();
@@ -497,12 +513,12 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     return e;
 }
 
-hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, int num_cus, hipStream_t stream) {
-    if (L.n_steps < 1 || L.n_steps > kMaxSteps) return hipErrorInvalidValue;
-    StepParams p;
+template <int N>
+static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_scale, int num_cus, hipStream_t stream) {
+    StepParams<N> p;
     // steps with items of their own first (in the given order), then the ones that share the pack
     auto packed = [](const StepLaunch::Step& a) { return a.Lk <= kTile && a.rows == nullptr; };
-    int order[kMaxSteps], n = 0;
+    int order[N], n = 0;
     for (int i = 0; i < L.n_steps; ++i) if (!packed(L.step[i])) order[n++] = i;
     p.n_tiled = n;
     for (int i = 0; i < L.n_steps; ++i) if (packed(L.step[i])) order[n++] = i;
@@ -534,8 +550,8 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
         }
     }
     if (p.n_pack > 0) ++items;                                  // the pack is the launch's last item
-    for (int i = L.n_steps; i < kMaxSteps; ++i) p.step[i] = p.step[0];
-    for (int u = p.n_pack; u < kMaxPackUnits; ++u) p.pack_unit[u] = 0;
+    for (int i = L.n_steps; i < N; ++i) p.step[i] = p.step[0];
+    for (int u = p.n_pack; u < 2 * N; ++u) p.pack_unit[u] = 0;
     p.n_heads = n_heads;
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(items, n_heads);
@@ -545,15 +561,22 @@ hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, in
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
     const long long small_groups = ((long long)n_heads * p.n_pack + 3) / 4;
     if (p.n_tiled == 0 && small_groups * kThreads < 1LL << 32) {
-        hipLaunchKernelGGL(hmar_fwd_small_steps_kernel, dim3((unsigned)small_groups), dim3(kThreads), 0, stream, p);
+        hipLaunchKernelGGL(hmar_fwd_small_steps_kernel<N>, dim3((unsigned)small_groups), dim3(kThreads), 0, stream, p);
     } else {
-        const auto kernel = leaves_maxima_out(max_tiles, total_tiles, n_heads, num_cus) ? hmar_fwd_steps_kernel<true>
-                                                                                        : hmar_fwd_steps_kernel<false>;
+        const auto kernel = leaves_maxima_out(max_tiles, total_tiles, n_heads, num_cus) ? hmar_fwd_steps_kernel<true, false, N>
+                            : whole_rows_fwd(groups, num_cus)                           ? hmar_fwd_steps_kernel<false, true, N>
+                                                                                        : hmar_fwd_steps_kernel<false, false, N>;
         hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
     }
     const hipError_t e = hipGetLastError();
     profile_after(kKernelFwd, stream);
     return e;
+}
+
+hipError_t launch_fwd_steps(const StepLaunch& L, int n_heads, float sm_scale, int num_cus, hipStream_t stream) {
+    if (L.n_steps < 1 || L.n_steps > kMaxSteps) return hipErrorInvalidValue;
+    return L.n_steps == 1 ? launch_fwd_steps_n<1>(L, n_heads, sm_scale, num_cus, stream)
+                          : launch_fwd_steps_n<kMaxSteps>(L, n_heads, sm_scale, num_cus, stream);
 }
 
 }  // namespace hmar

@@ -74,6 +74,26 @@ inline bool leaves_maxima_out(int max_tiles, long long total_tiles, int n_heads,
     return max_tiles >= HMAR_TUNE_LONG_STREAM && 4 * total_tiles * n_heads >= 7LL * num_cus * max_tiles;
 }
 
+// Whether the wavefronts of a launch ask for their own rows as whole rows and turn them round (request_rows in
+// csrc/device_common.h; no bits depend on it).  So they cost less address work (a dQ workgroup asks for 48 loads ahead of
+// its first tile), which is what a workgroup's start waits for while the launch leaves the chip room; on a fuller chip it
+// waits for memory, and the detour through LDS comes on top.  The backward of short streams (fewer than 8 tiles), mostly
+// starts with two or three operands each, still gains there.  (A switch inside the kernels costs launches of either kind 1
+// to 2 %: they are built twice.)  In operand layout -> as whole rows, us, by workgroups per compute unit:
+//   forward: 1.8 12.4 -> 12.0 (64 heads of 680 tokens), 3.6 19.5 -> 20.1, 21 72.1 -> 72.4; where maxima are left out 142.2 ->
+//     145.6 (192 heads of 2240 tokens); steps: 0.4 8.85 -> 8.60 (48 heads, 256 queries, 425 keys), 6 23.9 -> 25.5 (1536 heads,
+//     100 queries, 164 keys)
+//   dQ, 7 tiles: 1.8 14.7 -> 13.7, 3.6 22.7 -> 22.8, 4.4 25.7 -> 26.5, 7 36.3 -> 35.9, 21 90.6 -> 88.4; 25 tiles: 3.9 54.9 -> 55.4
+//   dK/dV, 7 tiles: 1.8 16.0 -> 15.4, 3.6 26.9 -> 25.5, 21 127.1 -> 126.5; 25 tiles: 3.9 78.3 -> 80.8, 100 tiles: 422 -> 424
+constexpr int kShortStream = 8;
+inline bool whole_rows_fwd(long long units, int num_cus) { return units <= 3LL * num_cus; }
+inline bool whole_rows_dq(long long units, int max_tiles, int num_cus) {
+    return units <= 3LL * num_cus || (max_tiles < kShortStream && units >= 7LL * num_cus);
+}
+inline bool whole_rows_dkdv(long long units, int max_tiles, int num_cus) {
+    return units <= 2LL * num_cus || max_tiles < kShortStream;
+}
+
 // Whether a backward is one launch of both kernels' items (hmar_bwd_both_kernel; no bits depend on it): work for at
 // most two of the longest items on every compute unit, and windows whose statistics fit the LDS of two workgroups per
 // compute unit.  Forward and backward in us, two launches -> one, by `fill` = tiles of both lists / (tiles of the
