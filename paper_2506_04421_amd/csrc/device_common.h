@@ -119,7 +119,7 @@ typedef const __attribute__((address_space(1))) void global_void;
 //    the last `tail_groups` groups, which form one batch walked item by item (all their
 //    heaviest items, then the next, ...): the launch then ends on the lightest items, and the
 //    period in which the device drains is as short as those.  The batch is sized to about one
-//    round of resident workgroups, small enough for its heads' K and V to share the L2.
+//    round of resident workgroups, small enough for its heads' K and V to share the L2 (launch_map in csrc/kernels.h).
 //  - The n_heads % 8 heads that fill no group are walked with that batch, the units of an item behind those of the
 //    batch's groups, so that they are dealt out to all XCDs: their rows are fetched by several L2s, but no XCD
 //    works on a head while others have none.  Against an XCD for each of them (forward / dK,dV / dQ in us): 12 heads

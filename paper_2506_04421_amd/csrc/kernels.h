@@ -47,11 +47,30 @@ struct UnitMap {
     int last_group_head;       // first head of the last group
     uint32_t inv_items, inv_batch;
 };
-inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads) {
-    const int n_groups = n_heads / 8, tail = std::min(tail_groups_for(num_cus, n_items), n_groups);
+inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_groups = 0) {
+    const int n_groups = n_heads / 8, tail = std::min(batch_groups > 0 ? batch_groups : tail_groups_for(num_cus, n_items), n_groups);
     const int batch = 8 * tail + n_heads % 8;
     return {n_items, 8 * (n_groups - tail) * n_items, 8 * (n_groups - tail), batch, 8 * tail, 8 * (n_groups - 1),
             inverse_of(n_items), inverse_of(batch)};
+}
+// The map of a launch.  Two orders, each where it measured best (units of an XCD: n_items * n_heads / 8; a compute unit
+// holds four workgroups of the forward and dQ, two of dK/dV):
+//  - Head by head with the batch at the end.  The batch is tail_groups_for() groups, half of it where an item list is
+//    short or the batch would swallow the launch: a launch that is one batch starts with its heaviest items alone, in step,
+//    all waiting for memory and then all computing, and leaves the L2 no locality.  Forward / dK,dV / dQ in us, whole or
+//    full batch -> half: 256 heads of 680 tokens (7 items) 29.1 / 49.8 / 36.4 -> 28.9 / 44.6 / 34.5, 200 heads 24.7 / 39.8 / 30.3
+//    -> 24.0 / 35.6 / 28.8, 320 heads 35.3 / 55.3 / 43.5 -> 34.5 / 54.6 / 41.3; 320 of 466 tokens (4 items) dK,dV 37.6 -> 35.3;
+//    96 of 1485 tokens (15 items) 55.5 / 81.5 / 69.7 -> 50.5 / 81.3 / 63.3, but 160 of them, where the full batch is not the whole
+//    launch, 77.2 / 127.9 / 99.0 -> 78.8 / 129.0 / 100.1; a step of 256 queries, 1536 heads 75.3 -> 69.7; 20 items: 64 heads of
+//    2240 tokens 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5.
+//  - Item by item altogether, where less than one unit per compute unit would be left ahead of the batch (160 heads of
+//    680 tokens, dK,dV: 32.2, with two groups ahead 34.2).
+inline UnitMap launch_map(int num_cus, int n_items, int n_heads) {
+    const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
+    int tail = tail_groups_for(num_cus, n_items);
+    if (n_items <= 8 || (n_items < 16 && tail >= n_groups)) tail = std::max(1, tail / 2);
+    if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(num_cus, n_items, n_heads, tail);
+    return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups));
 }
 
 // Workgroups of a launch over n_items items of each head, or 0 if they would be too many for a grid.

@@ -26,6 +26,13 @@ extern "C" unsigned units(int n_items, int n_heads, int cus, int reverse, int* h
     for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
     return n;
 }
+extern "C" unsigned launch_units(int n_items, int n_heads, int cus, int reverse, int* head, int* item) {
+    const unsigned n = hmar::launch_groups(n_items, n_heads);
+    if (!head) return n;
+    const hmar::UnitMap m = hmar::launch_map(cus, n_items, n_heads);
+    for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
+    return n;
+}
 extern "C" int quotient(int n, int d) { return hmar::divide(n, d, hmar::inverse_of(d)); }
 """
 
@@ -76,6 +83,20 @@ def test_whole_groups_are_walked_head_by_head_and_the_last_batch_item_by_item(li
         group = np.where(slot < first, slot // n_items, groups - tail + (slot - first) % tail)
         assert (item == np.where(slot < first, slot % n_items, (slot - first) // tail)).all()
         assert (head == (groups - 1 - group if reverse else group) * 8 + xcd).all()
+
+
+@pytest.mark.parametrize("cus", [256, 304, 64])
+def test_every_unit_of_a_launch_has_one_workgroup(lib, cus):
+    for n_items in [1, 2, 3, 7, 8, 9, 15, 16, 20, 31, 70, 300]:
+        for n_heads in list(range(1, 42)) + [63, 64, 72, 100, 104, 160, 256, 288, 768, 1023]:
+            for reverse in (0, 1):
+                n = n_items * n_heads
+                head, item = np.zeros(n, np.int32), np.zeros(n, np.int32)
+                p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
+                lib.launch_units(n_items, n_heads, cus, reverse, p(head), p(item))
+                assert np.array_equal(np.sort(head.astype(np.int64) * n_items + item), np.arange(n))
+                xcd, grouped = np.arange(n) % 8, head < n_heads // 8 * 8
+                assert (head[grouped] % 8 == xcd[grouped]).all()
 
 
 def test_quotients_by_the_inverse(lib):
