@@ -120,6 +120,8 @@ typedef const __attribute__((address_space(1))) void global_void;
 //    heaviest items, then the next, ...): the launch then ends on the lightest items, and the
 //    period in which the device drains is as short as those.  The batch is sized to about one
 //    round of resident workgroups, small enough for its heads' K and V to share the L2 (launch_map in csrc/kernels.h).
+//  - With `turned`, a number of workgroups of an XCD, its workgroups turned .. 2 * turned - 1 are taken backwards: where that
+//    is one per compute unit, the second workgroup of each is the lighter the heavier its first.
 //  - The n_heads % 8 heads that fill no group are walked with that batch, the units of an item behind those of the
 //    batch's groups, so that they are dealt out to all XCDs: their rows are fetched by several L2s, but no XCD
 //    works on a head while others have none.  Against an XCD for each of them (forward / dK,dV / dQ in us): 12 heads
@@ -141,6 +143,11 @@ __device__ __forceinline__ void map_unit(int wg, const UnitMap& m, int* head, in
     const int xcd = wg & 7;
     bool grouped = true;
     int h, it;
+    if (m.turned) {
+        const int slot = wg >> 3, slots = (m.units - xcd + 7) >> 3;          // of this XCD
+        const int end = slots < 2 * m.turned ? slots : 2 * m.turned;
+        if (slot >= m.turned && slot < end) wg = 8 * (m.turned + end - 1 - slot) + xcd;
+    }
     if (wg < m.head_major) {
         const int slot = wg >> 3, group = divide(slot, m.n_items, m.inv_items);
         it = slot - group * m.n_items;

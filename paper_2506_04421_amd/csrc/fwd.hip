@@ -497,7 +497,7 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(s.n_items[0], n_heads);
     if (groups == 0) return hipErrorInvalidValue;
-    p.map = launch_map(s.num_cus, s.n_items[0], n_heads);
+    p.map = launch_map(s.num_cus, s.n_items[0], n_heads, turn_units_fwd(s.num_cus));
     profile_before(kKernelFwd, stream);
 #ifdef HMAR_TUNE_FWD_STUDY
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
@@ -556,7 +556,7 @@ static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(items, n_heads);
     if (groups == 0) return hipErrorInvalidValue;
-    p.map = launch_map(num_cus, items, n_heads);
+    p.map = launch_map(num_cus, items, n_heads, N == 1 ? 0 : turn_units_fwd(num_cus));     // the items of one step are alike
     profile_before(kKernelFwd, stream);
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
     const long long small_groups = ((long long)n_heads * p.n_pack + 3) / 4;

@@ -46,14 +46,16 @@ struct UnitMap {
     int batch, batch_grouped;  // its heads, and those of them that fill groups of eight
     int last_group_head;       // first head of the last group
     uint32_t inv_items, inv_batch;
+    int turned;                // 0, or: an XCD's workgroups turned .. 2 * turned - 1 are taken backwards
+    int units;                 // workgroups of the launch
 };
-inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_groups = 0) {
+inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_groups = 0, int turned = 0) {
     const int n_groups = n_heads / 8, tail = std::min(batch_groups > 0 ? batch_groups : tail_groups_for(num_cus, n_items), n_groups);
     const int batch = 8 * tail + n_heads % 8;
     return {n_items, 8 * (n_groups - tail) * n_items, 8 * (n_groups - tail), batch, 8 * tail, 8 * (n_groups - 1),
-            inverse_of(n_items), inverse_of(batch)};
+            inverse_of(n_items), inverse_of(batch), turned, n_items * n_heads};
 }
-// The map of a launch.  Two orders, each where it measured best (units of an XCD: n_items * n_heads / 8; a compute unit
+// The map of a launch.  Three orders, each where it measured best (units of an XCD: n_items * n_heads / 8; a compute unit
 // holds four workgroups of the forward and dQ, two of dK/dV):
 //  - Head by head with the batch at the end.  The batch is tail_groups_for() groups, half of it where an item list is
 //    short or the batch would swallow the launch: a launch that is one batch starts with its heaviest items alone, in step,
@@ -65,13 +67,20 @@ inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_gro
 //    2240 tokens 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5.
 //  - Item by item altogether, where less than one unit per compute unit would be left ahead of the batch (160 heads of
 //    680 tokens, dK,dV: 32.2, with two groups ahead 34.2).
-inline UnitMap launch_map(int num_cus, int n_items, int n_heads) {
+//  - The same with the second unit of every compute unit dealt backwards, so that the heaviest first unit meets the lightest
+//    second one: for launches of at most `turn_units` of an XCD whose items differ.  dK,dV of 64 heads of 680 tokens 15.5 -> 14.7,
+//    of 21 of 2240 tokens 44.7 -> 41.0; both lists in one launch, 32 heads of 680 tokens 18.2 -> 16.1, 24 of 1485 54.3 -> 50.2;
+//    forward / dQ of 160 heads of 680 tokens 22.1 / 26.4 -> 21.5 / 25.4.  Beyond (dK,dV of 83 heads 18.6 -> 19.0) it does not pay.
+inline UnitMap launch_map(int num_cus, int n_items, int n_heads, int turn_units) {
     const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
     int tail = tail_groups_for(num_cus, n_items);
     if (n_items <= 8 || (n_items < 16 && tail >= n_groups)) tail = std::max(1, tail / 2);
     if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(num_cus, n_items, n_heads, tail);
-    return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups));
+    const long long units = (long long)n_items * n_heads;
+    return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups), units > num_cus && units <= 8LL * turn_units ? cus : 0);
 }
+inline int turn_units_fwd(int num_cus) { return 6 * (num_cus / 8); }        // the forward and dQ
+inline int turn_units_dkdv(int num_cus) { return 2 * (num_cus / 8); }       // dK/dV, and both lists in one launch
 
 // Workgroups of a launch over n_items items of each head, or 0 if they would be too many for a grid.
 inline unsigned launch_groups(int n_items, int n_heads) {

@@ -26,12 +26,12 @@ extern "C" unsigned units(int n_items, int n_heads, int cus, int reverse, int* h
     for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
     return n;
 }
-extern "C" unsigned launch_units(int n_items, int n_heads, int cus, int reverse, int* head, int* item) {
+extern "C" unsigned launch_units(int n_items, int n_heads, int cus, int reverse, int turn_units, int* head, int* item) {
     const unsigned n = hmar::launch_groups(n_items, n_heads);
     if (!head) return n;
-    const hmar::UnitMap m = hmar::launch_map(cus, n_items, n_heads);
+    const hmar::UnitMap m = hmar::launch_map(cus, n_items, n_heads, turn_units);
     for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
-    return n;
+    return n | (m.turned ? 1u << 31 : 0);
 }
 extern "C" int quotient(int n, int d) { return hmar::divide(n, d, hmar::inverse_of(d)); }
 """
@@ -86,17 +86,27 @@ def test_whole_groups_are_walked_head_by_head_and_the_last_batch_item_by_item(li
 
 
 @pytest.mark.parametrize("cus", [256, 304, 64])
-def test_every_unit_of_a_launch_has_one_workgroup(lib, cus):
+@pytest.mark.parametrize("turn", [0, 2, 6])
+def test_every_unit_of_a_launch_has_one_workgroup(lib, turn, cus):
+    turned = 0
     for n_items in [1, 2, 3, 7, 8, 9, 15, 16, 20, 31, 70, 300]:
         for n_heads in list(range(1, 42)) + [63, 64, 72, 100, 104, 160, 256, 288, 768, 1023]:
             for reverse in (0, 1):
                 n = n_items * n_heads
                 head, item = np.zeros(n, np.int32), np.zeros(n, np.int32)
                 p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
-                lib.launch_units(n_items, n_heads, cus, reverse, p(head), p(item))
+                lib.launch_units.restype = ctypes.c_uint
+                back = lib.launch_units(n_items, n_heads, cus, reverse, turn * (cus // 8), p(head), p(item)) >> 31
                 assert np.array_equal(np.sort(head.astype(np.int64) * n_items + item), np.arange(n))
                 xcd, grouped = np.arange(n) % 8, head < n_heads // 8 * 8
                 assert (head[grouped] % 8 == xcd[grouped]).all()
+                assert not back or cus < n <= turn * cus
+                if back:        # first unit of a compute unit heavy to light, second light to heavy
+                    for x in range(8):
+                        mine, c = item[x::8], cus // 8
+                        assert (np.diff(mine[:c]) >= 0).all() and (np.diff(mine[c:2 * c]) <= 0).all()
+                turned += back
+    assert (turned > 0) == (turn > 0)
 
 
 def test_quotients_by_the_inverse(lib):
