@@ -556,7 +556,9 @@ static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(items, n_heads);
     if (groups == 0) return hipErrorInvalidValue;
-    p.map = launch_map(num_cus, items, n_heads, N == 1 ? 0 : turn_units_fwd(num_cus));     // the items of one step are alike
+    // The items of one step are alike and share all their keys: head by head, there is nothing to end the launch on.  256
+    // queries, 425 keys: 1536 heads 70.8 -> 68.6 us, 768 39.6 -> 38.8, 600 34.8 -> 32.1 against the batch of launch_map.
+    p.map = N == 1 ? unit_map_for(num_cus, items, n_heads, 1) : launch_map(num_cus, items, n_heads, turn_units_fwd(num_cus));
     profile_before(kKernelFwd, stream);
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
     const long long small_groups = ((long long)n_heads * p.n_pack + 3) / 4;
