@@ -42,7 +42,7 @@ def launch_command(out: str, defines=()) -> list:
             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
             "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"), "-I", os.path.join(rocm, "include"),
             "-I", sysconfig.get_paths()["include"], *[f"-D{d}" for d in defines], os.path.join(CSRC, "py_launch.cpp"),
-            "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python", "-lc10_hip", "-o", out]
+            "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python", "-lc10_hip", "-ltorch_hip", "-o", out]
 
 
 def build_library(verbose: bool = False, variant: str = "", defines=()) -> str:
