@@ -333,13 +333,17 @@ __device__ __forceinline__ OwnRows request_rows(const __bf16* head, int own, Row
     }
     return rows;
 }
+// Whole rows to 32 rows of LDS in the layout of a tile.
+__device__ __forceinline__ void rows_to_lds(uint32_t rows32, const OwnRows& rows, int lane) {
+    typedef __attribute__((address_space(3))) bf16x8 lds_out;
+    const uint32_t even = rows32 + (lane >> 3) * kRowBytes + (((lane & 7) ^ swz(lane >> 3)) << 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *(lds_out*)((j & 1 ? even ^ 32 : even) + j * 1024) = rows.chunk[j];   // swz(r + 8) = swz(r) ^ 2
+}
 template <bool WHOLE>
 __device__ __forceinline__ void turn_rows(uint32_t patch, OwnRows& rows, const LaneOffsets& o, int lane) {
     if constexpr (WHOLE) {
-        typedef __attribute__((address_space(3))) bf16x8 lds_out;
-        const uint32_t even = patch + (lane >> 3) * kRowBytes + (((lane & 7) ^ swz(lane >> 3)) << 4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) *(lds_out*)((j & 1 ? even ^ 32 : even) + j * 1024) = rows.chunk[j];   // swz(r + 8) = swz(r) ^ 2
+        rows_to_lds(patch, rows, lane);
 #pragma unroll
         for (int t = 0; t < 4; ++t) rows.chunk[t] = lds_a_row(patch, o, 0, t);
     }

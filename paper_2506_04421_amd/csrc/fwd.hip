@@ -82,12 +82,11 @@ constexpr int kFwdStages = HMAR_FWD_STAGES;
 static_assert(kFwdStages >= 2 && kFwdStages <= 4, "ring depth");
 
 // A unit of the small steps (at most 64 keys): one wavefront computes 32 query rows of one head
-// alone, without the workgroup: the rows and the step's key rows go from global memory straight into
-// registers (both are row-wise operands), the value rows go by DMA into the wavefront's own 8 KB of
-// LDS (one tile, at Vt), from where the transpose load feeds the second contraction; the same LDS
-// then serves as the patch of the result.  One tile holds all keys, so the softmax is the plain
+// alone, without the workgroup: the rows and the step's key rows go through registers into operands, the value rows
+// into the wavefront's own 8 KB of LDS (one tile, at Vt), from where the transpose load feeds the second contraction;
+// the same LDS then serves as the patch of the result.  One tile holds all keys, so the softmax is the plain
 // one: row maximum, exponentials, row sum.  No barrier: nothing is shared between wavefronts.
-template <int N>
+template <bool WHOLE, int N>
 __device__ __forceinline__ void small_step_unit(const StepParams<N>& p, int head, int unit, uint32_t Vt, const LaneOffsets& lo_) {
     const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
     static_assert(kPatchBytes <= kTileBytes, "the result patch reuses the value tile");
@@ -100,39 +99,59 @@ __device__ __forceinline__ void small_step_unit(const StepParams<N>& p, int head
     const __bf16* Vh = sd.V + in_head * Lk * kD;
     const bool two_blocks = Lk > 32;                    // uniform: keys 32..63 exist
 
-    // value rows: this wavefront moves the whole tile, 8 rows per load, rows clamped to the
-    // last key (every LDS row the contraction reads must hold finite numbers).  The
-    // previous unit's patch reads have been consumed by its stores' operands by now.
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        if (b < 4 || two_blocks) {
-            const int r = 8 * b + (lane >> 3);
-            const uint32_t voff = min(r, Lk - 1) * kRowBytes + (((lane & 7) ^ swz(r)) << 4);
-            dma16(Vh, voff, Vt + b * 1024);
-        }
-    }
     const int qrow = min(row0 + lr, n_q - 1);
-    bf16x8 q[4], ka[2][4];
+    // All rows are in flight before the first one is awaited (clamped to the last one: what the contractions read must be
+    // finite).
+    OwnRows q, ka[2];
+    if constexpr (WHOLE) {
+        // Whole rows; query and key rows are turned round through the LDS that the value rows then stay in.  A step
+        // of 36 queries, 61 keys, 1536 heads: 7.2 us, in operand layout with the value rows by DMA (below) 8.6; of 25 and 41: 5.7,
+        // 6.3; 768 heads of 30 and 60: 4.5, 5.0.  It takes 118 registers, which the pack of a launch with larger steps
+        // does not have.
+        auto key_row = [&](int r) { return min(r, Lk - 1); };
+        auto late_key_row = [&](int r) { return min(32 + r, Lk - 1); };
+        OwnRows v[2];
+        q = request_rows<true>(Qh, 0, [&](int r) { return min(row0 + r, n_q - 1); }, lane);
+        ka[0] = request_rows<true>(Kh, 0, key_row, lane);
+        if (two_blocks) ka[1] = request_rows<true>(Kh, 0, late_key_row, lane);
+        v[0] = request_rows<true>(Vh, 0, key_row, lane);
+        if (two_blocks) v[1] = request_rows<true>(Vh, 0, late_key_row, lane);
+        turn_rows<true>(Vt, q, lo_, lane);
+        turn_rows<true>(Vt, ka[0], lo_, lane);
+        if (two_blocks) turn_rows<true>(Vt, ka[1], lo_, lane);
+        rows_to_lds(Vt, v[0], lane);
+        if (two_blocks) rows_to_lds(Vt + 4096, v[1], lane);
+    } else {
+        // value rows: this wavefront moves the whole tile, 8 rows per load.  The
+        // previous unit's patch reads have been consumed by its stores' operands by now.
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        q[t] = *reinterpret_cast<const bf16x8*>(Qh + (size_t)qrow * kD + 16 * t + 8 * h);
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-            ka[kb][t] = *reinterpret_cast<const bf16x8*>(Kh + (size_t)min(32 * kb + lr, Lk - 1) * kD + 16 * t + 8 * h);
+        for (int b = 0; b < 8; ++b) {
+            if (b < 4 || two_blocks) {
+                const int r = 8 * b + (lane >> 3);
+                const uint32_t voff = min(r, Lk - 1) * kRowBytes + (((lane & 7) ^ swz(r)) << 4);
+                dma16(Vh, voff, Vt + b * 1024);
+            }
+        }
+        auto none = [](int r) { return r; };
+        q = request_rows<false>(Qh, qrow, none, lane);
+        ka[0] = request_rows<false>(Kh, min(lr, Lk - 1), none, lane);
+        ka[1] = request_rows<false>(Kh, min(32 + lr, Lk - 1), none, lane);
+        // loads complete in order, so the value tile requested before them has landed as well
+        asm volatile("" :: "v"(q.chunk[0]), "v"(q.chunk[1]), "v"(q.chunk[2]), "v"(q.chunk[3]), "v"(ka[0].chunk[0]), "v"(ka[0].chunk[1]),
+                     "v"(ka[0].chunk[2]), "v"(ka[0].chunk[3]), "v"(ka[1].chunk[0]), "v"(ka[1].chunk[1]), "v"(ka[1].chunk[2]),
+                     "v"(ka[1].chunk[3]));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (already true; the compiler cannot know)
     }
-    // all twelve loads are in flight before the first one is awaited; loads complete in order,
-    // so the value tile requested before them has landed as well
-    asm volatile("" :: "v"(q[0]), "v"(q[1]), "v"(q[2]), "v"(q[3]), "v"(ka[0][0]), "v"(ka[0][1]), "v"(ka[0][2]),
-                 "v"(ka[0][3]), "v"(ka[1][0]), "v"(ka[1][1]), "v"(ka[1][2]), "v"(ka[1][3]));
 
     f32x16 s[2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+        if (kb == 0 || two_blocks)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) s[kb] = mfma32(ka[kb][t], q[t], s[kb]);
+            for (int t = 0; t < 4; ++t) s[kb] = mfma32(ka[kb].chunk[t], q.chunk[t], s[kb]);
     }
     // element i of block kb is key 4h + 32kb + 8(i/4) + i%4; keys >= Lk do not exist
 #pragma unroll
@@ -152,7 +171,6 @@ __device__ __forceinline__ void small_step_unit(const StepParams<N>& p, int head
             lsum += pv;
             s[kb][i] = pv;
         }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (already true; the compiler cannot know)
     f32x16 o[2];
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
@@ -181,13 +199,14 @@ __device__ __forceinline__ void small_steps_pack(const StepParams<N>& p, int hea
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LaneOffsets lo_ = make_lane_offsets(threadIdx.x & 63, 0);
     const uint32_t Vt = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kTileBytes);
-    for (int u = wave; u < p.n_pack; u += 4) small_step_unit(p, head, p.pack_unit[u], Vt, lo_);
+    for (int u = wave; u < p.n_pack; u += 4) small_step_unit<false>(p, head, p.pack_unit[u], Vt, lo_);
 }
 
 // A launch of small steps alone: every wavefront takes one unit of one head, the units of a head side by
 // side.  (One workgroup per head, as the pack has it, leaves three of four wavefronts without work in a
 // step of up to 32 rows, and 1536 heads take two rounds of workgroups where this takes less than one.
-// Steps of 1, 4, 9, 16, 25, 36 tokens: 8.8 9.2 9.8 10.6 12.4 15.7 -> 5.5 5.7 6.8 7.8 10.7 13.3 us.)
+// Steps of 1, 4, 9, 16, 25, 36 tokens: 8.8 9.2 9.8 10.6 12.4 15.7 -> 5.5 5.7 6.8 7.8 10.7 13.3 us, before
+// the whole rows of small_step_unit.)
 template <int N>
 __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_steps_kernel(StepParams<N> p) {
     __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];
@@ -196,7 +215,7 @@ __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_s
     const unsigned head = u / (unsigned)p.n_pack;
     if (head >= (unsigned)p.n_heads) return;
     const LaneOffsets lo_ = make_lane_offsets(threadIdx.x & 63, 0);
-    small_step_unit(p, (int)head, p.pack_unit[u % (unsigned)p.n_pack],
+    small_step_unit<true>(p, (int)head, p.pack_unit[u % (unsigned)p.n_pack],
                     __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kTileBytes), lo_);
 }
 
