@@ -63,7 +63,7 @@ inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_gro
 //    full batch -> half: 256 heads of 680 tokens (7 items) 29.1 / 49.8 / 36.4 -> 28.9 / 44.6 / 34.5, 200 heads 24.7 / 39.8 / 30.3
 //    -> 24.0 / 35.6 / 28.8, 320 heads 35.3 / 55.3 / 43.5 -> 34.5 / 54.6 / 41.3; 320 of 466 tokens (4 items) dK,dV 37.6 -> 35.3;
 //    96 of 1485 tokens (15 items) 55.5 / 81.5 / 69.7 -> 50.5 / 81.3 / 63.3, but 160 of them, where the full batch is not the whole
-//    launch, 77.2 / 127.9 / 99.0 -> 78.8 / 129.0 / 100.1; a step of 256 queries, 1536 heads 75.3 -> 69.7; 20 items: 64 heads of
+//    launch, 77.2 / 127.9 / 99.0 -> 78.8 / 129.0 / 100.1, nor 300 of 741 tokens (8 items) 49.3 / 74.0 / 61.9 -> 50.5 / 74.9 / 62.1; a step of 256 queries, 1536 heads 75.3 -> 69.7; 20 items: 64 heads of
 //    2240 tokens 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5.
 //  - Item by item altogether, where less than one unit per compute unit would be left ahead of the batch (160 heads of
 //    680 tokens, dK,dV: 32.2, with two groups ahead 34.2).
@@ -74,7 +74,7 @@ inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_gro
 inline UnitMap launch_map(int num_cus, int n_items, int n_heads, int turn_units) {
     const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
     int tail = tail_groups_for(num_cus, n_items);
-    if (n_items <= 8 || (n_items < 16 && tail >= n_groups)) tail = std::max(1, tail / 2);
+    if (n_items < 8 || (n_items < 16 && tail >= n_groups)) tail = std::max(1, tail / 2);
     if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(num_cus, n_items, n_heads, tail);
     const long long units = (long long)n_items * n_heads;
     return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups), units > num_cus && units <= 8LL * turn_units ? cus : 0);
