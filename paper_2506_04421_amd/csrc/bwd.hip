@@ -11,6 +11,7 @@
 //                       seen by the queries of scales k and k+1).  Recomputes P and dS with
 //                       the keys in the lane dimension and accumulates dV^T += dO^T P,
 //                       dK^T += Q^T dS.
+//   hmar_bwd_both_kernel: both kernels' items in one launch, for backwards that leave the chip room.
 // Both main kernels recompute the probabilities, so no gradient is accumulated across
 // workgroups: results are deterministic and nothing needs zero-initialising.  Streamed
 // tiles are row-major in LDS and serve both as row-wise operands (S, dP) and, through the
