@@ -100,6 +100,7 @@ void pack_tables(const Schedule& s, unsigned char* staging, unsigned char* base,
             dev->total_tiles[d] += tiles;
         }
     }
+    dev->full_batch = s.mask_kind == kMaskBlockCausal;
     dev->L = s.L;
     dev->Lk = s.Lk;
 }

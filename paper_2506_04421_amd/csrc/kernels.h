@@ -18,6 +18,7 @@ struct DeviceSchedule {
     int32_t L;                 // rows of Q, O, LSE per head
     int32_t Lk;                // rows of K, V per head
     int32_t num_cus;           // compute units of the device the tables live on
+    bool full_batch;           // launch_map: the batch is not halved
 };
 
 // Number of head groups (8 heads each) in the batch that ends a launch item by item (see
@@ -65,16 +66,18 @@ inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_gro
 //    96 of 1485 tokens (15 items) 55.5 / 81.5 / 69.7 -> 50.5 / 81.3 / 63.3, but 160 of them, where the full batch is not the whole
 //    launch, 77.2 / 127.9 / 99.0 -> 78.8 / 129.0 / 100.1, nor 300 of 741 tokens (8 items) 49.3 / 74.0 / 61.9 -> 50.5 / 74.9 / 62.1; a step of 256 queries, 1536 heads 75.3 -> 69.7; 20 items: 64 heads of
 //    2240 tokens 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5.
+//    Not under the block-causal mask, whose items share a head's first keys: 256 heads of 680 tokens, fastest card, 33.9 / 56.5 /
+//    42.8 -> 34.4 / 57.8 / 42.7.
 //  - Item by item altogether, where less than one unit per compute unit would be left ahead of the batch (160 heads of
 //    680 tokens, dK,dV: 32.2, with two groups ahead 34.2).
 //  - The same with the second unit of every compute unit dealt backwards, so that the heaviest first unit meets the lightest
 //    second one: for launches of at most `turn_units` of an XCD whose items differ.  dK,dV of 64 heads of 680 tokens 15.5 -> 14.7,
 //    of 21 of 2240 tokens 44.7 -> 41.0; both lists in one launch, 32 heads of 680 tokens 18.2 -> 16.1, 24 of 1485 54.3 -> 50.2;
 //    forward / dQ of 160 heads of 680 tokens 22.1 / 26.4 -> 21.5 / 25.4.  Beyond (dK,dV of 83 heads 18.6 -> 19.0) it does not pay.
-inline UnitMap launch_map(int num_cus, int n_items, int n_heads, int turn_units) {
+inline UnitMap launch_map(int num_cus, int n_items, int n_heads, int turn_units, bool full_batch = false) {
     const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
     int tail = tail_groups_for(num_cus, n_items);
-    if (n_items < 8 || (n_items < 16 && tail >= n_groups)) tail = std::max(1, tail / 2);
+    if (!full_batch && (n_items < 8 || (n_items < 16 && tail >= n_groups))) tail = std::max(1, tail / 2);
     if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(num_cus, n_items, n_heads, tail);
     const long long units = (long long)n_items * n_heads;
     return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups), units > num_cus && units <= 8LL * turn_units ? cus : 0);
