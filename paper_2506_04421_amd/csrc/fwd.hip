@@ -575,17 +575,23 @@ static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(items, n_heads);
     if (groups == 0) return hipErrorInvalidValue;
-    // The items of one step are alike and share all their keys: head by head, there is nothing to end the launch on.  256
-    // queries, 425 keys: 1536 heads 70.8 -> 68.6 us, 768 39.6 -> 38.8, 600 34.8 -> 32.1 against the batch of launch_map.
-    p.map = N == 1 ? unit_map_for(num_cus, items, n_heads, 1) : launch_map(num_cus, items, n_heads, turn_units_fwd(num_cus));
+    // The items of one step share all their keys: where they are alike (a last item of at least 64 rows) and fill the
+    // chip they are walked head by head, there is nothing to end the launch on.  256 queries, 425 keys: 1536 heads 70.8 ->
+    // 68.6 us, 768 39.6 -> 38.8, 600 34.8 -> 32.1 against the order of launch_map; but 139 rows, 269 keys, 424 heads 14.8 -> 16.8.
+    const int last_rows = (p.step[0].n_q + 127) % 128 + 1;
+    const bool alike = N == 1 && last_rows >= 64 && (long long)items * n_heads > 4LL * num_cus;
+    p.map = alike ? unit_map_for(num_cus, items, n_heads, 1) : launch_map(num_cus, items, n_heads, turn_units_fwd(num_cus));
     profile_before(kKernelFwd, stream);
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
     const long long small_groups = ((long long)n_heads * p.n_pack + 3) / 4;
     if (p.n_tiled == 0 && small_groups * kThreads < 1LL << 32) {
         hipLaunchKernelGGL(hmar_fwd_small_steps_kernel<N>, dim3((unsigned)small_groups), dim3(kThreads), 0, stream, p);
     } else {
+        // (one step of few rows keeps the operand layout: its loads touch few lines; 40 rows, 117 keys, 540 heads 6.9 us, as
+        // whole rows 7.1)
+        const bool whole = whole_rows_fwd(groups, num_cus) && !(N == 1 && p.step[0].n_q <= 64);
         const auto kernel = leaves_maxima_out(max_tiles, total_tiles, n_heads, num_cus) ? hmar_fwd_steps_kernel<true, false, N>
-                            : whole_rows_fwd(groups, num_cus)                           ? hmar_fwd_steps_kernel<false, true, N>
+                            : whole                                                     ? hmar_fwd_steps_kernel<false, true, N>
                                                                                         : hmar_fwd_steps_kernel<false, false, N>;
         hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
     }
