@@ -13,8 +13,10 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/EmptyTensor.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/record_function.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
@@ -99,15 +101,23 @@ bool to_sizes(PyObject* address, PyObject* count, PyObject* L, Sizes* out) {
     return out->array != nullptr;
 }
 
-// A new tensor: at::empty, without its way through the dispatcher (0.3 us of a call's 5 each) where nothing could
-// wait on that way, that is, where this thread has no dispatch keys but the ones every thread has (function transforms,
-// dispatch modes and the like add theirs).
+// A new tensor: at::empty, without its way through the dispatcher (0.3 us of a call's 5 each) where nothing waits on
+// that way.  What can wait there:
+//  - dispatch keys beyond the ones every thread has (function transforms, dispatch modes and the like add theirs);
+//  - observers of operators (the profiler);
+//  - the fill that torch.use_deterministic_algorithms asks of new memory (torch.utils.deterministic's
+//    fill_uninitialized_memory), which is part of the operator: a row list leaves rows unwritten.
+bool nothing_waits() {
+    return (c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() && !at::hasCallbacks() &&
+           !(at::globalContext().deterministicAlgorithms() && at::globalContext().deterministicFillUninitializedMemory());
+}
 at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& q) {
-#ifndef HMAR_LAUNCH_HOST
-    const c10::DispatchKeySet keys = c10::impl::tls_local_dispatch_key_set().included_;
-    if ((keys - c10::default_included_set).empty()) return at::Tensor(at::detail::empty_cuda(shape, type, q.device(), std::nullopt));
+    if (!nothing_waits()) return at::empty(shape, q.options().dtype(type));
+#ifdef HMAR_LAUNCH_HOST
+    return at::Tensor(at::detail::empty_cpu(shape, type));
+#else
+    return at::Tensor(at::detail::empty_cuda(shape, type, q.device(), std::nullopt));
 #endif
-    return at::empty(shape, q.options().dtype(type));
 }
 
 // an output tensor the caller gave (checked), or a new one

@@ -112,7 +112,7 @@ def test_two_threads_that_meet_a_schedule_first_share_one_array(monkeypatch, mom
     assert binding._known_sides((23, 29), 0) == (ctypes.addressof(kept), 2, 1370)
 
 
-TRANSFORMS = """
+HOST_MODULE = """
 import ctypes, importlib.util, sys, threading
 import torch
 spec = importlib.util.spec_from_file_location("_launch", sys.argv[1])
@@ -146,6 +146,9 @@ given = {
     "step": lambda: native.step(q, k, v, 0, o, lse, 0.0),
     "steps": lambda: native.steps([q], [k], [v], [0], [o], [lse], 0.0),
     "rows": lambda: native.rows(q, k, v, 0, rows, o, lse, 0.0)}
+"""
+
+TRANSFORMS = HOST_MODULE + """
 def transforms(f):
     res = []
     def body(x):
@@ -173,13 +176,74 @@ print("done")
 """
 
 
-def test_function_transforms_around_a_call_are_left_to_the_python_path(tmp_path):
+@pytest.fixture(scope="module")
+def host_module(tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("host_module") / "_launch.so")
+    subprocess.run(build.launch_command(path, ["HMAR_LAUNCH_HOST"]), check=True, timeout=300)
+    return path
+
+
+def _run_on_host_module(program, path):
+    res = subprocess.run([sys.executable, "-c", program, path], capture_output=True, text=True, timeout=300, cwd=ROOT)
+    assert res.returncode == 0 and res.stdout.strip().endswith("done"), res.stdout + res.stderr
+
+
+def test_function_transforms_around_a_call_are_left_to_the_python_path(host_module):
     # inside torch.func.grad and its like a new tensor is a wrapper without memory, also where every input is a plain
     # constant of the closure; met with the GIL released that ended the process, hence one of its own here
-    path = str(tmp_path / "_launch.so")
-    subprocess.run(build.launch_command(path, ["HMAR_LAUNCH_HOST"]), check=True, timeout=300)
-    res = subprocess.run([sys.executable, "-c", TRANSFORMS, path], capture_output=True, text=True, timeout=300, cwd=ROOT)
-    assert res.returncode == 0 and res.stdout.strip().endswith("done"), res.stdout + res.stderr
+    _run_on_host_module(TRANSFORMS, host_module)
+
+
+NEW_OUTPUTS = HOST_MODULE + """
+# what waits on the way of a new tensor: the fill of deterministic algorithms, and observers.  The stand-ins write
+# nothing, so a filled output stays NaN
+new["rows"] = lambda: native.rows(q, k, v, 0, rows, None, None, 0.0)
+def outputs(x):
+    return [t for y in x for t in (y if isinstance(y, list) else [y])]
+for name, f in new.items():
+    for fill in (True, False):
+        torch.use_deterministic_algorithms(True)
+        torch.utils.deterministic.fill_uninitialized_memory = fill
+        given_too = {o.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr()}
+        for i in range(3):
+            junk = [torch.zeros(s) for s in ((1, 2, 5, 32), (1, 2, 5))]        # what the allocator hands out next is not NaN
+            del junk
+            made = [t for t in outputs(f()) if t.data_ptr() not in given_too]
+            assert made or name == "bwd, workspace", name
+            assert not fill or all(t.float().isnan().all() for t in made), name
+        torch.use_deterministic_algorithms(False)
+    allocations = {"fwd": 2, "fwd, O given": 1, "bwd": 3, "bwd, workspace": 1, "step": 2, "steps": 2, "rows": 2}[name]
+    with torch.autograd.profiler.profile() as prof:
+        assert f() is not None
+    assert sum(e.name == "aten::empty" for e in prof.function_events) == allocations, (name, prof.function_events)
+    assert f() is not None
+print("done")
+"""
+
+
+def test_new_outputs_are_filled_and_observed_as_the_python_paths_are(host_module):
+    _run_on_host_module(NEW_OUTPUTS, host_module)
+
+
+@pytest.mark.gpu
+def test_new_outputs_of_a_row_list_are_filled_and_observed_on_both_paths():
+    dev = torch.device("cuda:0")
+    q, k, v = (_tensors(1, (1, 2, n, D), dev, seed=n)[0] for n in (90, 130, 130))
+    rows = torch.tensor([3, 70], dtype=torch.int32, device=dev)
+    others = [i for i in range(90) if i not in (3, 70)]
+    junk = [torch.zeros_like(q) for _ in range(4)] + [torch.zeros((1, 2, 90), device=dev) for _ in range(4)]
+    del junk                                            # the blocks the allocator hands out next hold no NaN
+    torch.use_deterministic_algorithms(True)
+    try:
+        for scale in (np.float64(0.0), 0.0):            # the Python path, the native one
+            O, LSE = hm.hmar_attn_step_fwd_rows(q, k, v, 40, rows, None, None, scale)
+            assert O[:, :, others].isnan().all() and LSE[:, :, others].isnan().all()
+            assert O[:, :, [3, 70]].isfinite().all() and LSE[:, :, [3, 70]].isfinite().all()
+    finally:
+        torch.use_deterministic_algorithms(False)
+    with torch.autograd.profiler.profile() as prof:
+        hm.hmar_attn_step_fwd(q, k, v, 40)
+    assert sum(e.name == "aten::empty" for e in prof.function_events) == 2
 
 
 @pytest.mark.gpu
