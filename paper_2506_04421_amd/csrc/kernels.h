@@ -126,21 +126,26 @@ inline bool whole_rows_dkdv(long long units, int max_tiles, int num_cus) {
 }
 
 // Whether a backward is one launch of both kernels' items (hmar_bwd_both_kernel; no bits depend on it): work for at
-// most two of the longest items on every compute unit, and windows whose statistics fit the LDS of two workgroups per
-// compute unit.  Forward and backward in us, two launches -> one, by `fill` = tiles of both lists / (tiles of the
-// longest item * compute units), 256 compute units:
-//   680 tokens (7 tiles):   4 heads, 0.1  31.0 -> 21.8;  32, 1.1  31.7 -> 25.6;  48, 1.7  33.9 -> 30.4;  64, 2.3  36.4 -> 33.1;
-//                           80, 2.9  42.0 -> 39.4;  100, 3.6  48.0 -> 48.2
-//   2240 tokens (25 tiles): 4 heads, 0.4  80.8 -> 59.3;  13, 1.3  83.3 -> 72.9;  20, 2.0  96.5 -> 96.1;  26, 2.6  101 -> 112
-//   466 tokens (6 tiles):   48 heads, 1.1  29.3 -> 23.4;  75, 1.7  33.2 -> 29.8;  100, 2.3  34.5 -> 35.0
+// most two of the longest items on every compute unit, 9/5 of them where streams are long, and windows whose statistics
+// fit the LDS of two workgroups per compute unit.  What it saves is a launch and the wait for the first kernel's last item;
+// what it costs is that dQ items run two to a compute unit, not four, and that a window is read twice, which weighs
+// more the longer the streams.  Time of two launches / of one, geometric mean (least .. most) over
+// schedules of both masks, by `fill` = tiles of both lists / (tiles of the longest item * compute units), 256 compute units:
+//   fill             up to 1.1          1.1 .. 1.5         1.5 .. 1.8         1.8 .. 2
+//    1 to 7 tiles    1.64 (1.39..1.76)  1.38 (1.24..1.59)  1.30 (1.20..1.53)  1.22 (1.03..1.53)
+//    8 to 15         1.53 (1.18..1.68)  1.21 (1.12..1.40)  1.19 (0.99..1.39)  1.09 (0.95..1.26)
+//   16 to 25         1.51 (1.21..1.60)  1.17 (1.08..1.36)  1.14 (0.95..1.39)  1.03 (0.91..1.26)
+//   26 to 32         1.47 (1.16..1.55)  1.12 (1.05..1.28)  1.10 (1.02..1.22)  1.01 (0.90..1.19)
+//   33 to 64         1.45 (1.11..1.59)  1.10 (1.00..1.25)  1.07 (0.91..1.22)  0.97 (0.86..1.06)
 constexpr int kBothMaxTiles = 64;          // tiles a dK/dV item may visit
+constexpr int kBothLongTiles = 33;         // from where on streams are long
 #ifndef HMAR_TUNE_BOTH_FILL
-#define HMAR_TUNE_BOTH_FILL 2              // measurement builds: the line (0: always two launches)
+#define HMAR_TUNE_BOTH_FILL 2              // measurement builds: the line for short streams (0: always two launches)
 #endif
 inline bool one_backward_launch(const DeviceSchedule& s, int n_heads) {
-    const long long total = (s.total_tiles[0] + s.total_tiles[1]) * n_heads;
-    return s.n_items[0] == s.n_items[1] && s.max_tiles[1] <= kBothMaxTiles &&
-           total <= (long long)HMAR_TUNE_BOTH_FILL * std::max(s.max_tiles[0], s.max_tiles[1]) * s.num_cus;
+    const long long total = (s.total_tiles[0] + s.total_tiles[1]) * n_heads, longest = std::max(s.max_tiles[0], s.max_tiles[1]);
+    const int tenths = 10 * HMAR_TUNE_BOTH_FILL - (longest >= kBothLongTiles ? 2 : 0);
+    return s.n_items[0] == s.n_items[1] && s.max_tiles[1] <= kBothMaxTiles && 10 * total <= tenths * longest * s.num_cus;
 }
 
 // Per-kernel event bracketing for hmar_profile_begin/end (no-ops unless profiling is on).
