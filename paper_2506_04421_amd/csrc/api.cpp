@@ -95,11 +95,12 @@ void pack_tables(const Schedule& s, unsigned char* staging, unsigned char* base,
         dev->max_tiles[d] = 0;
         dev->total_tiles[d] = 0;
         for (const TileItem& it : s.items[d]) {
-            const int32_t tiles = (it.other_end - it.other_begin + 63) / 64;
+            const int32_t tiles = tiles_of(it);
             dev->max_tiles[d] = std::max(dev->max_tiles[d], tiles);
             dev->total_tiles[d] += tiles;
         }
     }
+    dev->long_items = items_to_last_long(s.items[0]);
     dev->full_batch = s.mask_kind == kMaskBlockCausal;
     dev->L = s.L;
     dev->Lk = s.Lk;

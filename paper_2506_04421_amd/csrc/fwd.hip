@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_small_s
 
 // One body serves both launches: with STEPS the item, its buffers and its (trivial) pair ranges
 // come from the step descriptors, otherwise from the schedule tables.
-template <bool STEPS, bool LAZY, bool WHOLE, typename Params>
+template <bool STEPS, bool LAZY, bool WHOLE, bool AHEAD, typename Params>
 __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     int head, item_id;
     map_workgroup(p.map, &head, &item_id);
@@ -345,12 +345,12 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
-                if constexpr (!STEPS && !LAZY) {
+                if constexpr (AHEAD) {
                     // all eight operands are requested ahead of the first contraction; left to itself the compiler
-                    // reads each next to its use and waits for it there: 4 heads of 2240 tokens 25.6 -> 24.1 us, 32 of
-                    // 680 tokens 11.6 -> 11.2, -0.6 % on full launches.  The other forms do without: there is no
-                    // room for it where maxima are left out (2240 tokens, 192 heads: +2 %), and steps, without
-                    // edges to mask inside their stream, come out better scheduled (25 tiles of a row list: 46.2 us, with it 46.9)
+                    // reads each next to its use and waits for it there.  When: keys_ahead (csrc/kernels.h).  The
+                    // other forms do without: there is no room for it where maxima are left out (2240 tokens, 192
+                    // heads: +2 %), and steps, without edges to mask inside their stream, come out better
+                    // scheduled (25 tiles of a row list: 46.2 us, with it 46.9)
                     bf16x8 a[2][4];
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
@@ -467,20 +467,20 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     }
 }
 
-template <bool LAZY, bool WHOLE>
+template <bool LAZY, bool WHOLE, bool AHEAD>
 __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_kernel(FwdParams p) {
     // ring of stages, each a K tile followed by a V tile
     __shared__ __attribute__((aligned(1024))) char smem[kFwdStages * 2 * kTileBytes];
 #ifdef HMAR_TUNE_LDS_PAD_FWD
     HMAR_TUNE_LDS_PAD(HMAR_TUNE_LDS_PAD_FWD)
 #endif
-    fwd_body<false, LAZY, WHOLE>(p, smem);
+    fwd_body<false, LAZY, WHOLE, AHEAD>(p, smem);
 }
 
 template <bool LAZY, bool WHOLE, int N>
 __global__ __launch_bounds__(kThreads, HMAR_FWD_MIN_WAVES) void hmar_fwd_steps_kernel(StepParams<N> p) {
     __shared__ __attribute__((aligned(1024))) char smem[kFwdStages * 2 * kTileBytes];
-    fwd_body<true, LAZY, WHOLE>(p, smem);
+    fwd_body<true, LAZY, WHOLE, false>(p, smem);
 }
 
 #ifdef HMAR_TUNE_FWD_STUDY
@@ -522,9 +522,10 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
                        dim3(groups), dim3(64 * HMAR_STUDY_NW), 0, stream, p);
 #else
-    const auto kernel = leaves_maxima_out(s.max_tiles[0], s.total_tiles[0], n_heads, s.num_cus) ? hmar_fwd_kernel<true, false>
-                        : whole_rows_fwd(groups, s.num_cus)                                     ? hmar_fwd_kernel<false, true>
-                                                                                                : hmar_fwd_kernel<false, false>;
+    const bool whole = whole_rows_fwd(groups, s.num_cus), ahead = keys_ahead(s.max_tiles[0], s.long_items, n_heads, s.num_cus);
+    const auto kernel = leaves_maxima_out(s.max_tiles[0], s.total_tiles[0], n_heads, s.num_cus) ? hmar_fwd_kernel<true, false, false>
+                        : whole ? (ahead ? hmar_fwd_kernel<false, true, true> : hmar_fwd_kernel<false, true, false>)
+                                : (ahead ? hmar_fwd_kernel<false, false, true> : hmar_fwd_kernel<false, false, false>);
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, stream, p);
 #endif
     const hipError_t e = hipGetLastError();

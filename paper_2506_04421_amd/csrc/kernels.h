@@ -13,6 +13,7 @@ struct DeviceSchedule {
     int32_t n_items[2];
     int32_t max_tiles[2];      // streamed 64-row tiles of a list's longest item
     int64_t total_tiles[2];    // and of all its items
+    int32_t long_items;        // of the forward's list: items_to_last_long
     const int32_t* row_lo[2];  // L entries
     const int32_t* row_hi[2];
     int32_t L;                 // rows of Q, O, LSE per head
@@ -103,6 +104,21 @@ inline unsigned launch_groups(int n_items, int n_heads) {
 #endif
 inline bool leaves_maxima_out(int max_tiles, long long total_tiles, int n_heads, int num_cus) {
     return max_tiles >= HMAR_TUNE_LONG_STREAM && 4 * total_tiles * n_heads >= 7LL * num_cus * max_tiles;
+}
+
+// Whether a forward of the training shapes that takes every maximum requests all key operands of a tile ahead of its first
+// contraction (csrc/fwd.hip; no bits depend on it).  That shortens the chain of a workgroup that has its compute unit to
+// itself; where two long chains share one (their wavefronts the same SIMDs), each covers the other's waits and the earlier
+// reads only get in the way.  `long units` = heads * items up to the last long one.  Time with the compiler's order / ahead,
+// geometric mean (least .. most), 256 compute units, by long units per compute unit:
+//   up to 1:   1.05 (0.99..1.06) for 16 to 64 tiles, 1.04 (0.98..1.06) for 3 to 15, 1.00 for fewer; 4 heads of 2240 tokens
+//              25.6 -> 24.1 us, 32 of 680 tokens 11.6 -> 11.2
+//   1 .. 2:    0.95 (0.92..0.98) and 0.99 (0.94..1.02); 14 heads of 64, 256, 784, 1296 tokens a scale 37.3 -> 40.1 us, 10 of 4089
+//              tokens 72.4 -> 75.9
+//   beyond 2:  0.96 and 1.00 (0.91..1.04): no difference on short streams
+inline bool keys_ahead(int max_tiles, int long_items, int n_heads, int num_cus) {
+    const long long units = (long long)long_items * n_heads;
+    return units <= num_cus || (max_tiles < HMAR_TUNE_LONG_STREAM && units > 2LL * num_cus);
 }
 
 // Whether the wavefronts of a launch ask for their own rows as whole rows and turn them round (request_rows in

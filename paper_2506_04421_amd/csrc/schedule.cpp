@@ -89,4 +89,12 @@ bool build_schedule(const int32_t* sides, int32_t num_scales, bool sizes_are_cou
     return true;
 }
 
+int32_t items_to_last_long(const std::vector<TileItem>& items) {
+    int32_t longest = 0, n = 0;
+    for (const TileItem& it : items) longest = std::max(longest, tiles_of(it));
+    for (size_t i = 0; i < items.size(); ++i)
+        if (10 * tiles_of(items[i]) >= 7 * longest) n = (int32_t)i + 1;
+    return n;
+}
+
 }  // namespace hmar

@@ -22,6 +22,8 @@ struct TileItem {
     int32_t own_begin, own_end;      // rows owned by the workgroup, own_end - own_begin <= rows_per_item
     int32_t other_begin, other_end;  // union of the owned rows' pair ranges
 };
+// 64-row tiles of the pair range: the length of the workgroup's chain
+inline int32_t tiles_of(const TileItem& it) { return (it.other_end - it.other_begin + 63) / 64; }
 
 enum MaskKind : int32_t { kMaskMarkov = 0, kMaskBlockCausal = 1 };
 
@@ -45,5 +47,9 @@ struct Schedule {
 // sizes are invalid (non-positive, too many, or L beyond max_len).
 bool build_schedule(const int32_t* sizes, int32_t num_scales, bool sizes_are_counts, int32_t mask_kind,
                     int32_t rows_per_item, int32_t max_scales, int64_t max_len, Schedule* out);
+
+// Items of a list up to the last one whose chain is at least 7/10 of the longest: launched item by item, these
+// come first.
+int32_t items_to_last_long(const std::vector<TileItem>& items);
 
 }  // namespace hmar

@@ -13,6 +13,7 @@ CUS = 256
 
 PROGRAM = """
 #include "kernels.h"
+#include "schedule.h"
 #define __device__
 #define __forceinline__ inline
 static inline uint32_t __umulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
@@ -39,6 +40,12 @@ extern "C" int one_launch(int n_q, int n_k, int max_q, int max_k, int total, int
     s.total_tiles[0] = total / 2; s.total_tiles[1] = total - total / 2; s.num_cus = cus;
     return hmar::one_backward_launch(s, n_heads);
 }
+extern "C" int ahead(int max_tiles, int long_items, int n_heads, int cus) { return hmar::keys_ahead(max_tiles, long_items, n_heads, cus); }
+extern "C" int last_long(const int* tiles, int n) {
+    std::vector<hmar::TileItem> items;
+    for (int i = 0; i < n; ++i) items.push_back({0, 1, 64 * i, 64 * (i + tiles[i]) - 63 * (i & 1)});
+    return hmar::items_to_last_long(items);
+}
 extern "C" int quotient(int n, int d) { return hmar::divide(n, d, hmar::inverse_of(d)); }
 """
 
@@ -51,7 +58,7 @@ def lib(tmp_path_factory):
     (d / "hip").mkdir()
     (d / "hip" / "hip_runtime.h").write_text("#pragma once\n#include <cstddef>\ntypedef int hipError_t; typedef void* hipStream_t;\n")
     (d / "map.cpp").write_text(PROGRAM % text[begin:text.index("__device__ __forceinline__ void map_workgroup(")])
-    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", str(d), "-I", CSRC, str(d / "map.cpp"),
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", str(d), "-I", CSRC, str(d / "map.cpp"), os.path.join(CSRC, "schedule.cpp"),
            "-o", str(d / "map.so")]
     subprocess.run(cmd, check=True)
     return ctypes.CDLL(str(d / "map.so"))
@@ -125,6 +132,16 @@ def test_a_backward_is_one_launch_up_to_its_line(lib, tiles, tenths):
         assert lib.one_launch(3, 3, tiles, 1, line // 8, 8, cus) and not lib.one_launch(3, 3, 1, tiles, line // 8 + 1, 8, cus)
         assert not lib.one_launch(3, 4, tiles, tiles, line, 1, cus)          # lists of one length only
         assert not lib.one_launch(3, 3, tiles, 65, 1, 1, cus) and lib.one_launch(3, 3, 65, tiles, 1, 1, cus)
+
+
+def test_key_operands_are_asked_for_ahead_where_no_two_long_chains_share_a_compute_unit(lib):
+    for cus in (256, 304):
+        for tiles in (1, 15, 16, 64):
+            short = int(tiles < 16)
+            assert [lib.ahead(tiles, 2, h, cus) for h in (1, cus // 2, cus // 2 + 1, cus, cus + 1, 9 * cus)] == [1, 1, 0, 0, short, short]
+        assert not lib.ahead(15, 1 << 14, 1 << 18, cus) == lib.ahead(16, 1 << 14, 1 << 18, cus)          # beyond 32 bits
+    for tiles, n in (([7, 7, 4, 7, 5, 3, 3], 5), ([3], 1), ([5, 5, 5], 3), ([10, 7, 6, 6], 2), ([10, 6, 6, 1], 1), ([6, 1, 1, 10], 4)):
+        assert lib.last_long((ctypes.c_int * len(tiles))(*tiles), len(tiles)) == n, tiles
 
 
 def test_quotients_by_the_inverse(lib):
