@@ -516,7 +516,7 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(s.n_items[0], n_heads);
     if (groups == 0) return hipErrorInvalidValue;
-    p.map = launch_map(s.num_cus, s.n_items[0], n_heads, turn_units_fwd(s.num_cus), s.full_batch);
+    p.map = launch_map(s.num_cus, s.n_items[0], n_heads, kOrderFwd, s.full_batch);
     profile_before(kKernelFwd, stream);
 #ifdef HMAR_TUNE_FWD_STUDY
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),
@@ -581,7 +581,7 @@ static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_
     // 68.6 us, 768 39.6 -> 38.8, 600 34.8 -> 32.1 against the order of launch_map; but 139 rows, 269 keys, 424 heads 14.8 -> 16.8.
     const int last_rows = (p.step[0].n_q + 127) % 128 + 1;
     const bool alike = N == 1 && last_rows >= 64 && (long long)items * n_heads > 4LL * num_cus;
-    p.map = alike ? unit_map_for(num_cus, items, n_heads, 1) : launch_map(num_cus, items, n_heads, turn_units_fwd(num_cus));
+    p.map = alike ? unit_map_for(num_cus, items, n_heads, 1) : launch_map(num_cus, items, n_heads, kOrderFwd);
     profile_before(kKernelFwd, stream);
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
     const long long small_groups = ((long long)n_heads * p.n_pack + 3) / 4;

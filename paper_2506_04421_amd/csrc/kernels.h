@@ -57,34 +57,41 @@ inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_gro
     return {n_items, 8 * (n_groups - tail) * n_items, 8 * (n_groups - tail), batch, 8 * tail, 8 * (n_groups - 1),
             inverse_of(n_items), inverse_of(batch), turned, n_items * n_heads};
 }
-// The map of a launch.  Three orders, each where it measured best (units of an XCD: n_items * n_heads / 8; a compute unit
-// holds four workgroups of the forward and dQ, two of dK/dV):
+// How a kind of launch orders its units (launch_map).
+struct Order {
+    int turn_rounds;           // the second unit of every compute unit is dealt backwards up to so many units per compute unit
+    int half_below;            // the batch is halved for lists of fewer items than this,
+    int half_whole_below;      // and, where it would be the whole launch, for lists of fewer items than this
+};
+constexpr Order kOrderFwd = {6, 8, 8}, kOrderDq = {6, 8, 16};
+constexpr Order kOrderDkDv = {2, 8, 16};       // and both lists in one launch
+// The map of a launch.  Three orders, each where it measured best (us; a compute unit holds four workgroups of the forward
+// and dQ, two of dK/dV):
 //  - Head by head with the batch at the end.  The batch is tail_groups_for() groups, half of it where an item list is
-//    short or the batch would swallow the launch: a launch that is one batch starts with its heaviest items alone, in step,
-//    all waiting for memory and then all computing, and leaves the L2 no locality.  Forward / dK,dV / dQ in us, whole or
-//    full batch -> half: 256 heads of 680 tokens (7 items) 29.1 / 49.8 / 36.4 -> 28.9 / 44.6 / 34.5, 200 heads 24.7 / 39.8 / 30.3
-//    -> 24.0 / 35.6 / 28.8, 320 heads 35.3 / 55.3 / 43.5 -> 34.5 / 54.6 / 41.3; 320 of 466 tokens (4 items) dK,dV 37.6 -> 35.3;
-//    96 of 1485 tokens (15 items) 55.5 / 81.5 / 69.7 -> 50.5 / 81.3 / 63.3, but 160 of them, where the full batch is not the whole
-//    launch, 77.2 / 127.9 / 99.0 -> 78.8 / 129.0 / 100.1, nor 300 of 741 tokens (8 items) 49.3 / 74.0 / 61.9 -> 50.5 / 74.9 / 62.1; a step of 256 queries, 1536 heads 75.3 -> 69.7; 20 items: 64 heads of
-//    2240 tokens 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5.
+//    short: a launch that is one batch starts with its heaviest items alone, in step, all waiting for memory and
+//    then all computing, and leaves the L2 no locality.  Full batch -> half:
+//      7 items (680 tokens)   forward / dK,dV / dQ: 256 heads 29.1 / 49.8 / 36.4 -> 28.9 / 44.6 / 34.5, 200 heads
+//                             24.7 / 39.8 / 30.3 -> 24.0 / 35.6 / 28.8, 320 heads 35.3 / 55.3 / 43.5 -> 34.5 / 54.6 / 41.3
+//      4 items (466 tokens)   320 heads, dK,dV: 37.6 -> 35.3
+//      8 to 15 items, launches that are one batch: forward +2 % (-8..+21 %), dK,dV -0.3 %, dQ -0.1 % (150 schedules)
+//      20 items (2240 tokens) 64 heads: 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5
 //    Not under the block-causal mask, whose items share a head's first keys: 256 heads of 680 tokens, fastest card, 33.9 / 56.5 /
 //    42.8 -> 34.4 / 57.8 / 42.7.
 //  - Item by item altogether, where less than one unit per compute unit would be left ahead of the batch (160 heads of
 //    680 tokens, dK,dV: 32.2, with two groups ahead 34.2).
 //  - The same with the second unit of every compute unit dealt backwards, so that the heaviest first unit meets the lightest
-//    second one: for launches of at most `turn_units` of an XCD whose items differ.  dK,dV of 64 heads of 680 tokens 15.5 -> 14.7,
+//    second one, in launches of at most `turn_rounds` units per compute unit.  dK,dV of 64 heads of 680 tokens 15.5 -> 14.7,
 //    of 21 of 2240 tokens 44.7 -> 41.0; both lists in one launch, 32 heads of 680 tokens 18.2 -> 16.1, 24 of 1485 54.3 -> 50.2;
 //    forward / dQ of 160 heads of 680 tokens 22.1 / 26.4 -> 21.5 / 25.4.  Beyond (dK,dV of 83 heads 18.6 -> 19.0) it does not pay.
-inline UnitMap launch_map(int num_cus, int n_items, int n_heads, int turn_units, bool full_batch = false) {
+inline UnitMap launch_map(int num_cus, int n_items, int n_heads, const Order& order, bool full_batch = false) {
     const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
     int tail = tail_groups_for(num_cus, n_items);
-    if (!full_batch && (n_items < 8 || (n_items < 16 && tail >= n_groups))) tail = std::max(1, tail / 2);
+    if (!full_batch && (n_items < order.half_below || (n_items < order.half_whole_below && tail >= n_groups))) tail = std::max(1, tail / 2);
     if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(num_cus, n_items, n_heads, tail);
     const long long units = (long long)n_items * n_heads;
-    return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups), units > num_cus && units <= 8LL * turn_units ? cus : 0);
+    const bool turned = units > num_cus && units <= 8LL * order.turn_rounds * cus;
+    return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups), turned ? cus : 0);
 }
-inline int turn_units_fwd(int num_cus) { return 6 * (num_cus / 8); }        // the forward and dQ
-inline int turn_units_dkdv(int num_cus) { return 2 * (num_cus / 8); }       // dK/dV, and both lists in one launch
 
 // Workgroups of a launch over n_items items of each head, or 0 if they would be too many for a grid.
 inline unsigned launch_groups(int n_items, int n_heads) {

@@ -10,6 +10,7 @@ import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_04421_amd", "csrc")
 CUS = 256
+KINDS = ["fwd", "dq", "dkdv"]
 
 PROGRAM = """
 #include "kernels.h"
@@ -27,10 +28,14 @@ extern "C" unsigned units(int n_items, int n_heads, int cus, int reverse, int* h
     for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
     return n;
 }
-extern "C" unsigned launch_units(int n_items, int n_heads, int cus, int reverse, int turn_units, int* head, int* item) {
+const hmar::Order orders[] = {hmar::kOrderFwd, hmar::kOrderDq, hmar::kOrderDkDv};
+extern "C" int batch_groups(int n_items, int n_heads, int cus, int kind) {
+    return hmar::launch_map(cus, n_items, n_heads, orders[kind]).batch_grouped / 8;
+}
+extern "C" unsigned launch_units(int n_items, int n_heads, int cus, int reverse, int kind, int* head, int* item) {
     const unsigned n = hmar::launch_groups(n_items, n_heads);
     if (!head) return n;
-    const hmar::UnitMap m = hmar::launch_map(cus, n_items, n_heads, turn_units);
+    const hmar::UnitMap m = hmar::launch_map(cus, n_items, n_heads, orders[kind]);
     for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
     return n | (m.turned ? 1u << 31 : 0);
 }
@@ -99,9 +104,9 @@ def test_whole_groups_are_walked_head_by_head_and_the_last_batch_item_by_item(li
 
 
 @pytest.mark.parametrize("cus", [256, 304, 64])
-@pytest.mark.parametrize("turn", [0, 2, 6])
-def test_every_unit_of_a_launch_has_one_workgroup(lib, turn, cus):
-    turned = 0
+@pytest.mark.parametrize("kind", KINDS)
+def test_every_unit_of_a_launch_has_one_workgroup(lib, kind, cus):
+    turned, turn = 0, 2 if kind == "dkdv" else 6
     for n_items in [1, 2, 3, 7, 8, 9, 15, 16, 20, 31, 70, 300]:
         for n_heads in list(range(1, 42)) + [63, 64, 72, 100, 104, 160, 256, 288, 768, 1023]:
             for reverse in (0, 1):
@@ -109,7 +114,7 @@ def test_every_unit_of_a_launch_has_one_workgroup(lib, turn, cus):
                 head, item = np.zeros(n, np.int32), np.zeros(n, np.int32)
                 p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
                 lib.launch_units.restype = ctypes.c_uint
-                back = lib.launch_units(n_items, n_heads, cus, reverse, turn * (cus // 8), p(head), p(item)) >> 31
+                back = lib.launch_units(n_items, n_heads, cus, reverse, KINDS.index(kind), p(head), p(item)) >> 31
                 assert np.array_equal(np.sort(head.astype(np.int64) * n_items + item), np.arange(n))
                 xcd, grouped = np.arange(n) % 8, head < n_heads // 8 * 8
                 assert (head[grouped] % 8 == xcd[grouped]).all()
@@ -119,7 +124,23 @@ def test_every_unit_of_a_launch_has_one_workgroup(lib, turn, cus):
                         mine, c = item[x::8], cus // 8
                         assert (np.diff(mine[:c]) >= 0).all() and (np.diff(mine[c:2 * c]) <= 0).all()
                 turned += back
-    assert (turned > 0) == (turn > 0)
+    assert turned > 0
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_the_batch_that_ends_a_launch(lib, kind):
+    # groups that hold eight units for every compute unit of an XCD, half of them for lists of up to seven items and,
+    # where the batch would be the whole launch, up to fifteen in the backward; the whole launch where less than a unit per
+    # compute unit would be left ahead of it
+    for cus in (256, 304):
+        for n_items in (1, 3, 7, 8, 11, 15, 16, 20, 300):
+            for n_heads in list(range(1, 60)) + list(range(60, 700, 13)) + [768, 1536]:
+                groups, full = n_heads // 8, max(1, cus // 8 * 8 // n_items)
+                half = n_items < 8 or (n_items < 16 and full >= groups and kind != "fwd")
+                batch = min(groups, max(1, full // 2) if half else full)
+                if (groups - batch) * n_items < cus // 8:
+                    batch = groups
+                assert lib.batch_groups(n_items, n_heads, cus, KINDS.index(kind)) == batch, (n_items, n_heads, cus)
 
 
 @pytest.mark.parametrize("tiles,tenths", [(1, 20), (7, 20), (25, 20), (32, 20), (33, 18), (64, 18)])
