@@ -101,7 +101,7 @@ void pack_tables(const Schedule& s, unsigned char* staging, unsigned char* base,
         }
     }
     dev->long_items = items_to_last_long(s.items[0]);
-    dev->full_batch = s.mask_kind == kMaskBlockCausal;
+    dev->causal = s.mask_kind == kMaskBlockCausal;
     dev->L = s.L;
     dev->Lk = s.Lk;
 }

@@ -521,7 +521,7 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
         p.row_lo = s.row_lo[0];
         p.row_hi = s.row_hi[0];
         const int units = s.n_items[0] + s.n_items[1];
-        p.map = launch_map(s.num_cus, units, n_heads, kOrderDkDv, s.full_batch);
+        p.map = launch_map(s.num_cus, units, n_heads, kOrderDkDv);
         b.p = p;
         profile_before(kKernelDkDv, stream);
         hipLaunchKernelGGL(hmar_bwd_both_kernel, dim3(launch_groups(units, n_heads)), dim3(kThreads), 0, stream, b);
@@ -536,7 +536,7 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const void* O
         p.row_hi = s.row_hi[dir];
         const unsigned groups = launch_groups(s.n_items[dir], n_heads);
         if (groups == 0) return hipErrorInvalidValue;
-        p.map = launch_map(s.num_cus, s.n_items[dir], n_heads, dir == 1 ? kOrderDkDv : kOrderDq, s.full_batch);
+        p.map = launch_map(s.num_cus, s.n_items[dir], n_heads, dir == 1 ? kOrderDkDv : kOrderDq);
         const bool whole = dir == 1 ? whole_rows_dkdv(groups, s.max_tiles[dir], s.num_cus) : whole_rows_dq(groups, s.max_tiles[dir], s.num_cus);
         const int kid = dir == 1 ? kKernelDkDv : kKernelDq;
         profile_before(kid, stream);

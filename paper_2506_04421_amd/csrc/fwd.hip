@@ -516,7 +516,7 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     p.c = sm_scale * kLog2e;
     const unsigned groups = launch_groups(s.n_items[0], n_heads);
     if (groups == 0) return hipErrorInvalidValue;
-    p.map = launch_map(s.num_cus, s.n_items[0], n_heads, kOrderFwd, s.full_batch);
+    p.map = launch_map(s.num_cus, s.n_items[0], n_heads, s.causal ? kOrderFwdCausal : kOrderFwd);
     profile_before(kKernelFwd, stream);
 #ifdef HMAR_TUNE_FWD_STUDY
     hipLaunchKernelGGL((hmar_fwd_study_kernel<HMAR_STUDY_RB, HMAR_STUDY_NW, HMAR_STUDY_MINW, HMAR_STUDY_PIPE != 0>),

@@ -19,7 +19,7 @@ struct DeviceSchedule {
     int32_t L;                 // rows of Q, O, LSE per head
     int32_t Lk;                // rows of K, V per head
     int32_t num_cus;           // compute units of the device the tables live on
-    bool full_batch;           // launch_map: the batch is not halved
+    bool causal;               // the block-causal mask
 };
 
 // Number of head groups (8 heads each) in the batch that ends a launch item by item (see
@@ -63,7 +63,7 @@ struct Order {
     int half_below;            // the batch is halved for lists of fewer items than this,
     int half_whole_below;      // and, where it would be the whole launch, for lists of fewer items than this
 };
-constexpr Order kOrderFwd = {6, 8, 8}, kOrderDq = {6, 8, 16};
+constexpr Order kOrderFwd = {6, 8, 8}, kOrderFwdCausal = {6, 0, 0}, kOrderDq = {6, 8, 16};
 constexpr Order kOrderDkDv = {2, 8, 16};       // and both lists in one launch
 // The map of a launch.  Three orders, each where it measured best (us; a compute unit holds four workgroups of the forward
 // and dQ, two of dK/dV):
@@ -75,18 +75,18 @@ constexpr Order kOrderDkDv = {2, 8, 16};       // and both lists in one launch
 //      4 items (466 tokens)   320 heads, dK,dV: 37.6 -> 35.3
 //      8 to 15 items, launches that are one batch: forward +2 % (-8..+21 %), dK,dV -0.3 %, dQ -0.1 % (150 schedules)
 //      20 items (2240 tokens) 64 heads: 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5
-//    Not under the block-causal mask, whose items share a head's first keys: 256 heads of 680 tokens, fastest card, 33.9 / 56.5 /
-//    42.8 -> 34.4 / 57.8 / 42.7.
+//      block-causal, 2 to 7 items, 4 to 24 units per compute unit, 126 schedules: backward -1.1 % (-10..+4 %), but forward
+//                             +0.1 % (-11..+6 %), whose items share a head's first keys: it keeps the full batch
 //  - Item by item altogether, where less than one unit per compute unit would be left ahead of the batch (160 heads of
 //    680 tokens, dK,dV: 32.2, with two groups ahead 34.2).
 //  - The same with the second unit of every compute unit dealt backwards, so that the heaviest first unit meets the lightest
 //    second one, in launches of at most `turn_rounds` units per compute unit.  dK,dV of 64 heads of 680 tokens 15.5 -> 14.7,
 //    of 21 of 2240 tokens 44.7 -> 41.0; both lists in one launch, 32 heads of 680 tokens 18.2 -> 16.1, 24 of 1485 54.3 -> 50.2;
 //    forward / dQ of 160 heads of 680 tokens 22.1 / 26.4 -> 21.5 / 25.4.  Beyond (dK,dV of 83 heads 18.6 -> 19.0) it does not pay.
-inline UnitMap launch_map(int num_cus, int n_items, int n_heads, const Order& order, bool full_batch = false) {
+inline UnitMap launch_map(int num_cus, int n_items, int n_heads, const Order& order) {
     const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
     int tail = tail_groups_for(num_cus, n_items);
-    if (!full_batch && (n_items < order.half_below || (n_items < order.half_whole_below && tail >= n_groups))) tail = std::max(1, tail / 2);
+    if (n_items < order.half_below || (n_items < order.half_whole_below && tail >= n_groups)) tail = std::max(1, tail / 2);
     if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(num_cus, n_items, n_heads, tail);
     const long long units = (long long)n_items * n_heads;
     const bool turned = units > num_cus && units <= 8LL * order.turn_rounds * cus;

@@ -10,7 +10,7 @@ import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_04421_amd", "csrc")
 CUS = 256
-KINDS = ["fwd", "dq", "dkdv"]
+KINDS = ["fwd", "causal fwd", "dq", "dkdv"]
 
 PROGRAM = """
 #include "kernels.h"
@@ -28,7 +28,7 @@ extern "C" unsigned units(int n_items, int n_heads, int cus, int reverse, int* h
     for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
     return n;
 }
-const hmar::Order orders[] = {hmar::kOrderFwd, hmar::kOrderDq, hmar::kOrderDkDv};
+const hmar::Order orders[] = {hmar::kOrderFwd, hmar::kOrderFwdCausal, hmar::kOrderDq, hmar::kOrderDkDv};
 extern "C" int batch_groups(int n_items, int n_heads, int cus, int kind) {
     return hmar::launch_map(cus, n_items, n_heads, orders[kind]).batch_grouped / 8;
 }
@@ -131,12 +131,12 @@ def test_every_unit_of_a_launch_has_one_workgroup(lib, kind, cus):
 def test_the_batch_that_ends_a_launch(lib, kind):
     # groups that hold eight units for every compute unit of an XCD, half of them for lists of up to seven items and,
     # where the batch would be the whole launch, up to fifteen in the backward; the whole launch where less than a unit per
-    # compute unit would be left ahead of it
+    # compute unit would be left ahead of it.  The forward under the block-causal mask: never half
     for cus in (256, 304):
         for n_items in (1, 3, 7, 8, 11, 15, 16, 20, 300):
             for n_heads in list(range(1, 60)) + list(range(60, 700, 13)) + [768, 1536]:
                 groups, full = n_heads // 8, max(1, cus // 8 * 8 // n_items)
-                half = n_items < 8 or (n_items < 16 and full >= groups and kind != "fwd")
+                half = kind != "causal fwd" and (n_items < 8 or (n_items < 16 and full >= groups and kind != "fwd"))
                 batch = min(groups, max(1, full // 2) if half else full)
                 if (groups - batch) * n_items < cus // 8:
                     batch = groups
