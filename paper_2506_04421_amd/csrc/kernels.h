@@ -131,22 +131,23 @@ inline bool keys_ahead(int max_tiles, int long_items, int n_heads, int num_cus) 
 // Whether the wavefronts of a launch ask for their own rows as whole rows and turn them round (request_rows in
 // csrc/device_common.h; no bits depend on it).  So they cost less address work (a dQ workgroup asks for 48 loads ahead of
 // its first tile), which is what a workgroup's start waits for while the launch leaves the chip room; on a fuller chip it
-// waits for memory, and the detour through LDS comes on top.  The backward of short streams (fewer than 8 tiles), mostly
-// starts with two or three operands each, still gains there.  (A switch inside the kernels costs launches of either kind 1
-// to 2 %: they are built twice.)  In operand layout -> as whole rows, us, by workgroups per compute unit:
+// waits for memory, and the detour through LDS comes on top.  The backward of short streams, mostly starts with two
+// or three operands each, still gains there.  (A switch inside the kernels costs launches of either kind 1 to 2 %: they are
+// built twice.)  In operand layout -> as whole rows, us, by workgroups per compute unit:
 //   forward: 1.8 12.4 -> 12.0 (64 heads of 680 tokens), 3.6 19.5 -> 20.1, 21 72.1 -> 72.4; where maxima are left out 142.2 ->
 //     145.6 (192 heads of 2240 tokens); steps: 0.4 8.85 -> 8.60 (48 heads, 256 queries, 425 keys), 6 23.9 -> 25.5 (1536 heads,
 //     100 queries, 164 keys)
-//   dQ, 7 tiles: 1.8 14.7 -> 13.7, 3.6 22.7 -> 22.8, 4.4 25.7 -> 26.5, 7 36.3 -> 35.9, 21 90.6 -> 88.4; 25 tiles: 3.9 54.9 -> 55.4
-//   dK/dV, 7 tiles: 1.8 16.0 -> 15.4, 3.6 26.9 -> 25.5, 21 127.1 -> 126.5; 25 tiles: 3.9 78.3 -> 80.8, 100 tiles: 422 -> 424
-constexpr int kShortStream = 8;
+//   dQ, 7 tiles: 1.8 14.7 -> 13.7, 21 90.6 -> 88.4; dK/dV, 7 tiles: 1.8 16.0 -> 15.4, 3.6 26.9 -> 25.5, 21 127.1 -> 126.5
+// and the whole backward, geometric mean (least .. most) of 540 schedules, both masks:
+//   workgroups     2 .. 3             3 .. 4             4 .. 5.5           5.5 .. 7           7 .. 9
+//    1 to 7 tiles  0.98 (0.96..1.00)  0.96 (0.92..1.01)  0.99 (0.95..1.05)  0.98 (0.94..1.02)  0.98 (0.95..1.03)
+//    8 to 15       0.99 (0.96..1.00)  0.99 (0.96..1.04)  1.00 (0.98..1.02)  1.00 (0.97..1.02)  0.99 (0.96..1.01)
+//   16 to 35       0.99 (0.98..1.01)  1.00 (0.99..1.01)  1.01 (0.99..1.02)  1.01 (0.99..1.03)  1.00 (0.99..1.02)
+//   36 to 64       1.00 (0.99..1.01)  1.01 (1.00..1.01)  1.01 (1.00..1.02)  1.02 (1.00..1.03)  1.01 (1.00..1.02)
+constexpr int kShortStream = 16;
 inline bool whole_rows_fwd(long long units, int num_cus) { return units <= 3LL * num_cus; }
-inline bool whole_rows_dq(long long units, int max_tiles, int num_cus) {
-    return units <= 3LL * num_cus || (max_tiles < kShortStream && units >= 7LL * num_cus);
-}
-inline bool whole_rows_dkdv(long long units, int max_tiles, int num_cus) {
-    return units <= 2LL * num_cus || max_tiles < kShortStream;
-}
+inline bool whole_rows_dq(long long units, int max_tiles, int num_cus) { return units <= 3LL * num_cus || max_tiles < kShortStream; }
+inline bool whole_rows_dkdv(long long units, int max_tiles, int num_cus) { return units <= 2LL * num_cus || max_tiles < kShortStream; }
 
 // Whether a backward is one launch of both kernels' items (hmar_bwd_both_kernel; no bits depend on it): work for at
 // most two of the longest items on every compute unit, 9/5 of them where streams are long, and windows whose statistics

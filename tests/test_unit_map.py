@@ -46,6 +46,10 @@ extern "C" int one_launch(int n_q, int n_k, int max_q, int max_k, int total, int
     return hmar::one_backward_launch(s, n_heads);
 }
 extern "C" int ahead(int max_tiles, int long_items, int n_heads, int cus) { return hmar::keys_ahead(max_tiles, long_items, n_heads, cus); }
+extern "C" int whole_rows(int kind, long long units, int max_tiles, int cus) {
+    return kind == 0 ? hmar::whole_rows_fwd(units, cus) : kind == 1 ? hmar::whole_rows_dq(units, max_tiles, cus)
+                                                                    : hmar::whole_rows_dkdv(units, max_tiles, cus);
+}
 extern "C" int last_long(const int* tiles, int n) {
     std::vector<hmar::TileItem> items;
     for (int i = 0; i < n; ++i) items.push_back({0, 1, 64 * i, 64 * (i + tiles[i]) - 63 * (i & 1)});
@@ -153,6 +157,16 @@ def test_a_backward_is_one_launch_up_to_its_line(lib, tiles, tenths):
         assert lib.one_launch(3, 3, tiles, 1, line // 8, 8, cus) and not lib.one_launch(3, 3, 1, tiles, line // 8 + 1, 8, cus)
         assert not lib.one_launch(3, 4, tiles, tiles, line, 1, cus)          # lists of one length only
         assert not lib.one_launch(3, 3, tiles, 65, 1, 1, cus) and lib.one_launch(3, 3, 65, tiles, 1, 1, cus)
+
+
+def test_own_rows_are_asked_for_whole_up_to_one_line(lib):
+    # the fuller the launch and the longer its streams, the less whole rows pay: one line in each direction, no gap
+    lib.whole_rows.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
+    for cus in (256, 304):
+        for kind, rounds in ((0, 3), (1, 3), (2, 2)):
+            for tiles in (1, 7, 8, 15, 16, 64):
+                whole = [lib.whole_rows(kind, units, tiles, cus) for units in (1, rounds * cus, rounds * cus + 1, 5 * cus, 7 * cus, 1 << 33)]
+                assert whole == [1, 1] + 4 * [int(kind > 0 and tiles < 16)], (kind, tiles)
 
 
 def test_key_operands_are_asked_for_ahead_where_no_two_long_chains_share_a_compute_unit(lib):
