@@ -45,7 +45,7 @@ struct StepDesc {
 // workgroup: they come last in `step` and share ONE item per head, the launch's last, in which
 // every wavefront works on its own: unit u of the pack is the 32-row block pack_unit[u] % 2 of step
 // pack_unit[u] / 2, taken by wavefront u % 4 (see small_steps_pack).
-// N: steps there is room for, kMaxSteps or 1.  A call of one step, as a sampling loop makes them, hands over 120 bytes
+// N: steps there is room for, kMaxSteps or 1.  A call of one step, as a sampling loop makes them, hands over 128 bytes
 // instead of 1.2 KB: they fill two cache lines, and the host does not write the rest.
 template <int N>
 struct StepParams {
@@ -57,6 +57,7 @@ struct StepParams {
     StepDesc step[N];           // the n_tiled steps that get items of their own, then the packed ones
     int pack_unit[2 * N];
 };
+static_assert(sizeof(StepParams<1>) == 128, "two cache lines");
 
 // Softmax reference.  Probabilities are formed against a row's reference maximum and are at most 2^8,
 // which fp32 sums and bf16 operands hold without loss.  The reference is raised when a tile's maximum exceeds
@@ -194,8 +195,7 @@ __device__ __forceinline__ void small_step_unit(const StepParams<N>& p, int head
 
 // The pack item of a steps launch that has larger steps too: wavefront w takes the units w, w + 4, ... of the
 // workgroup's head.
-template <int N>
-__device__ __forceinline__ void small_steps_pack(const StepParams<N>& p, int head, char* smem) {
+__device__ __forceinline__ void small_steps_pack(const StepParams<kMaxSteps>& p, int head, char* smem) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LaneOffsets lo_ = make_lane_offsets(threadIdx.x & 63, 0);
     const uint32_t Vt = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * kTileBytes);
@@ -232,9 +232,11 @@ __device__ __forceinline__ void fwd_body(const Params& p, char* smem) {
     int q_stride_rows = 0;            // rows per head of those buffers (steps)
     const int32_t* row_lo = nullptr; const int32_t* row_hi = nullptr;
     if constexpr (STEPS) {
-        if (p.n_pack > 0 && item_id == p.map.n_items - 1) {
-            small_steps_pack(p, head, smem);
-            return;
+        if constexpr (Params::kRoom > 1) { // (one small step alone never comes here)
+            if (p.n_pack > 0 && item_id == p.map.n_items - 1) {
+                small_steps_pack(p, head, smem);
+                return;
+            }
         }
         int si = 0;                        // n_tiled is 1 where there is room for one
         while (Params::kRoom > 1 && si + 1 < p.n_tiled && item_id >= p.step[si + 1].first_item) ++si;
@@ -584,8 +586,9 @@ static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_
     p.map = alike ? unit_map_for(num_cus, items, n_heads, 1) : launch_map(num_cus, items, n_heads, kOrderFwd);
     profile_before(kKernelFwd, stream);
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
+    // (up to 2^24 heads; one step, two units at most, stays below)
     const long long small_groups = ((long long)n_heads * p.n_pack + 3) / 4;
-    if (p.n_tiled == 0 && small_groups * kThreads < 1LL << 32) {
+    if (p.n_tiled == 0 && (N == 1 || small_groups * kThreads < 1LL << 32)) {
         hipLaunchKernelGGL(hmar_fwd_small_steps_kernel<N>, dim3((unsigned)small_groups), dim3(kThreads), 0, stream, p);
     } else {
         // (one step of few rows keeps the operand layout: its loads touch few lines; 40 rows, 117 keys, 540 heads 6.9 us, as
