@@ -413,7 +413,8 @@ def hmar_profile_begin() -> None:
 
 
 def hmar_profile_end():
-    """{kernel name: (total ms, launches)} of the launches since hmar_profile_begin()."""
+    """{kernel name: (total ms, launches)} of the launches since hmar_profile_begin().  A small backward is one launch, in
+    the place of the dK/dV kernel."""
     ms = (ctypes.c_double * len(KERNEL_NAMES))()
     n = (ctypes.c_int64 * len(KERNEL_NAMES))()
     _check(load_library().hmar_profile_end(ms, n), "hmar_profile_end")

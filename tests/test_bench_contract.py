@@ -45,6 +45,21 @@ def test_kernel_byte_and_flop_models_match_the_schedule_arithmetic():
     assert bench.METRIC.startswith("useful TFLOP/s fwd+bwd (680 tok, H=24, D=64)")
 
 
+def test_a_backward_in_one_launch_is_charged_with_both_kernels_work():
+    sys.path.insert(0, ROOT)
+    import bench
+    w = si.WORKLOADS["tiny"]
+    A, n_heads = orc.allowed_pairs(w.sides), w.B * w.H
+    two, one = (bench.kernel_models(n_heads, w.L, w.D, A, o) for o in (False, True))
+    assert one["hmar_fwd_kernel"] == two["hmar_fwd_kernel"]
+    both = one["hmar_dkdv_kernel"]
+    for k in ("flops", "useful_flops"):
+        assert both[k] == two["hmar_dkdv_kernel"][k] + two["hmar_dq_kernel"][k]
+    assert both["useful_flops"] == 10 * w.D * A * n_heads
+    # Q, K, V, O, dO and LSE in, dQ, dK, dV out
+    assert both["bytes"] == n_heads * w.L * (8 * 128 + 4)
+
+
 def test_traffic_file_is_readable_and_close_to_the_algorithmic_bytes():
     sys.path.insert(0, ROOT)
     import bench
