@@ -837,17 +837,27 @@ def test_results_do_not_depend_on_the_batch(sides, B, few):
     ((8, 11), 0, 70, 200),                                # a last tile of 57 rows
     ((130, 70, 300), hm.HMAR_SCALE_COUNTS, 30, 160),
     ((3, 9, 14), hm.HMAR_MASK_BLOCK_CAUSAL, 24, 140),
-    ((64,), 0, 1, 16), ((63, 12), 0, 1, 16),              # windows of 64 tiles, the most one launch takes
-    ((4097,), hm.HMAR_SCALE_COUNTS, 1, 16)])              # 65: two launches at any batch
+    ((36, 28), 0, 2, 40),                                 # 33 tiles
+    ((64,), 0, 1, 16),                                    # windows of 64 tiles, the most one launch takes
+    ((63, 11), 0, 1, 16), ((4033,), hm.HMAR_SCALE_COUNTS, 1, 16), ((4095,), hm.HMAR_SCALE_COUNTS, 1, 16),   # with a ragged last one
+    ((4097,), hm.HMAR_SCALE_COUNTS, 1, 16), ((63, 12), 0, 1, 16)])      # 65: two launches at any batch
 def test_backward_in_one_launch_gives_the_bits_of_two(sizes, kind, few, many):
-    # `few` heads leave the chip so empty that one launch holds both kernels' items, `many` do not
+    # `few` heads leave the chip so empty that one launch (in the dK/dV kernel's place) holds both kernels' items, `many` do not
     d, L = _dev(), sum(n if kind & hm.HMAR_SCALE_COUNTS else n * n for n in sizes)
     q, k, v, g = (t.to(d) for t in si.draw((1, many, L, 64), seed=1900 + L, n_tensors=4))
     O, LSE = hm.hmar_attn_fwd_masked(q, k, v, sizes, kind)
-    whole = hm.hmar_attn_bwd_masked(q, k, v, O, g, LSE, sizes, kind)
+
+    def launches(call):
+        hm.hmar_profile_begin()
+        call()
+        profile = hm.hmar_profile_end()
+        return profile["hmar_dkdv_kernel"][1], profile["hmar_dq_kernel"][1]
+    whole = []
+    assert launches(lambda: whole.extend(hm.hmar_attn_bwd_masked(q, k, v, O, g, LSE, sizes, kind))) == (1, 1)
     part = [t[:, :few].contiguous() for t in (q, k, v, O, g, LSE)]
     out = [torch.full_like(part[0], float("nan")) for _ in range(3)]
-    hm.hmar_attn_bwd_masked(*part, sizes, kind, dQ=out[0], dK=out[1], dV=out[2])
+    assert launches(lambda: hm.hmar_attn_bwd_masked(*part, sizes, kind, dQ=out[0], dK=out[1], dV=out[2])) == (
+        (1, 1) if sizes in ((4097,), (63, 12)) else (1, 0))
     for name, a, b in zip(("dQ", "dK", "dV"), out, whole):
         assert torch.equal(a, b[:, :few]), name
 
