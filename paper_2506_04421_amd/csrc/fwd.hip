@@ -583,7 +583,7 @@ static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_
     // 68.6 us, 768 39.6 -> 38.8, 600 34.8 -> 32.1 against the order of launch_map; but 139 rows, 269 keys, 424 heads 14.8 -> 16.8.
     const int last_rows = (p.step[0].n_q + 127) % 128 + 1;
     const bool alike = N == 1 && last_rows >= 64 && (long long)items * n_heads > 4LL * num_cus;
-    p.map = alike ? unit_map_for(num_cus, items, n_heads, 1) : launch_map(num_cus, items, n_heads, kOrderFwd);
+    p.map = alike ? unit_map_for(items, n_heads, 1) : launch_map(num_cus, items, n_heads, kOrderFwd);
     profile_before(kKernelFwd, stream);
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head
     // (up to 2^24 heads; one step, two units at most, stays below)

@@ -51,8 +51,8 @@ struct UnitMap {
     int turned;                // 0, or: an XCD's workgroups turned .. 2 * turned - 1 are taken backwards
     int units;                 // workgroups of the launch
 };
-inline UnitMap unit_map_for(int num_cus, int n_items, int n_heads, int batch_groups = 0, int turned = 0) {
-    const int n_groups = n_heads / 8, tail = std::min(batch_groups > 0 ? batch_groups : tail_groups_for(num_cus, n_items), n_groups);
+inline UnitMap unit_map_for(int n_items, int n_heads, int batch_groups, int turned = 0) {
+    const int n_groups = n_heads / 8, tail = std::min(batch_groups, n_groups);
     const int batch = 8 * tail + n_heads % 8;
     return {n_items, 8 * (n_groups - tail) * n_items, 8 * (n_groups - tail), batch, 8 * tail, 8 * (n_groups - 1),
             inverse_of(n_items), inverse_of(batch), turned, n_items * n_heads};
@@ -87,10 +87,10 @@ inline UnitMap launch_map(int num_cus, int n_items, int n_heads, const Order& or
     const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
     int tail = tail_groups_for(num_cus, n_items);
     if (n_items < order.half_below || (n_items < order.half_whole_below && tail >= n_groups)) tail = std::max(1, tail / 2);
-    if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(num_cus, n_items, n_heads, tail);
+    if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(n_items, n_heads, tail);
     const long long units = (long long)n_items * n_heads;
     const bool turned = units > num_cus && units <= 8LL * order.turn_rounds * cus;
-    return unit_map_for(num_cus, n_items, n_heads, std::max(1, n_groups), turned ? cus : 0);
+    return unit_map_for(n_items, n_heads, std::max(1, n_groups), turned ? cus : 0);
 }
 
 // Workgroups of a launch over n_items items of each head, or 0 if they would be too many for a grid.

@@ -21,10 +21,10 @@ static inline uint32_t __umulhi(uint32_t a, uint32_t b) { return (uint32_t)(((ui
 namespace hmar {
 %s
 }
-extern "C" unsigned units(int n_items, int n_heads, int cus, int reverse, int* head, int* item) {
+extern "C" unsigned units(int n_items, int n_heads, int batch_groups, int reverse, int* head, int* item) {
     const unsigned n = hmar::launch_groups(n_items, n_heads);
     if (!head) return n;
-    const hmar::UnitMap m = hmar::unit_map_for(cus, n_items, n_heads);
+    const hmar::UnitMap m = hmar::unit_map_for(n_items, n_heads, batch_groups);
     for (unsigned wg = 0; wg < n; ++wg) hmar::map_unit((int)wg, m, head + wg, item + wg, reverse != 0);
     return n;
 }
@@ -73,19 +73,41 @@ def lib(tmp_path_factory):
     return ctypes.CDLL(str(d / "map.so"))
 
 
-def _units(lib, n_items, n_heads, reverse=False):
-    n = lib.units(n_items, n_heads, CUS, 0, None, None)
+def _units(lib, n_items, n_heads, batch_groups, reverse=False):
+    n = lib.units(n_items, n_heads, 1, 0, None, None)
     head, item = np.zeros(n, np.int32), np.zeros(n, np.int32)
     p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
-    lib.units(n_items, n_heads, CUS, int(reverse), p(head), p(item))
+    lib.units(n_items, n_heads, batch_groups, int(reverse), p(head), p(item))
     return head, item
 
 
+def _launch_units(lib, n_items, n_heads, cus, kind, reverse=False):
+    """(heads, items, whether the second units are dealt backwards) of the workgroups of a launch."""
+    n = n_items * n_heads
+    head, item = np.zeros(n, np.int32), np.zeros(n, np.int32)
+    p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
+    lib.launch_units.restype = ctypes.c_uint
+    back = lib.launch_units(n_items, n_heads, cus, int(reverse), KINDS.index(kind), p(head), p(item)) >> 31
+    return head, item, back
+
+
+def _batch(n_items, n_heads, cus, kind):
+    """Groups of eight heads in the batch that ends a launch: eight units for every compute unit of an XCD, half of them for
+    lists of up to seven items and, where the batch would be the whole launch, up to fifteen in the backward; the whole
+    launch where less than a unit per compute unit would be left ahead of it.  The forward under the block-causal mask:
+    never half."""
+    groups, full = n_heads // 8, max(1, cus // 8 * 8 // n_items)
+    half = kind != "causal fwd" and (n_items < 8 or (n_items < 16 and full >= groups and kind != "fwd"))
+    batch = min(groups, max(1, full // 2) if half else full)
+    return groups if (groups - batch) * n_items < cus // 8 else batch
+
+
+@pytest.mark.parametrize("batch_groups", [1, 2, 7, 40, 1000])         # 1: a single step of items that are alike
 @pytest.mark.parametrize("reverse", [False, True])
 @pytest.mark.parametrize("n_items", [1, 2, 3, 5, 7, 8, 20, 70, 255, 256, 257, 1000])
-def test_every_unit_has_one_workgroup(lib, n_items, reverse):
-    for n_heads in list(range(1, 42)) + [48, 63, 100, 104, 107, 768, 1023, 1536]:
-        head, item = _units(lib, n_items, n_heads, reverse)
+def test_every_unit_has_one_workgroup(lib, n_items, reverse, batch_groups):
+    for n_heads in list(range(1, 42)) + [48, 63, 100, 104, 107] + ([768, 1023, 1536] if n_items < 100 else [300]):
+        head, item = _units(lib, n_items, n_heads, batch_groups, reverse)
         assert len(head) == n_items * n_heads
         assert head.min() >= 0 and head.max() < n_heads and item.min() >= 0 and item.max() < n_items
         assert np.bincount(head.astype(np.int64) * n_items + item, minlength=n_items * n_heads).max() == 1
@@ -94,17 +116,28 @@ def test_every_unit_has_one_workgroup(lib, n_items, reverse):
         assert (head[grouped] % 8 == xcd[grouped]).all()
 
 
-@pytest.mark.parametrize("n_items,n_heads", [(7, 768), (20, 192), (7, 256), (1, 1536), (70, 48), (300, 16)])
-def test_whole_groups_are_walked_head_by_head_and_the_last_batch_item_by_item(lib, n_items, n_heads):
+def _assert_order(head, item, n_items, n_heads, batch, reverse):
+    # whole groups head by head, the last `batch` of them item by item
     groups = n_heads // 8
-    tail = min(max(CUS // n_items, 1), groups)
+    slot, xcd = np.arange(len(head)) // 8, np.arange(len(head)) % 8
+    first = (groups - batch) * n_items
+    group = np.where(slot < first, slot // n_items, groups - batch + (slot - first) % batch)
+    assert (item == np.where(slot < first, slot % n_items, (slot - first) // batch)).all()
+    assert (head == (groups - 1 - group if reverse else group) * 8 + xcd).all()
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n_items,n_heads", [(7, 768), (20, 192), (7, 256), (8, 256), (12, 200), (12, 480), (1, 4096), (70, 48), (300, 16)])
+def test_whole_groups_are_walked_head_by_head_and_the_last_batch_item_by_item(lib, n_items, n_heads, kind):
     for reverse in (False, True):
-        head, item = _units(lib, n_items, n_heads, reverse)
-        slot, xcd = np.arange(len(head)) // 8, np.arange(len(head)) % 8
-        first = (groups - tail) * n_items
-        group = np.where(slot < first, slot // n_items, groups - tail + (slot - first) % tail)
-        assert (item == np.where(slot < first, slot % n_items, (slot - first) // tail)).all()
-        assert (head == (groups - 1 - group if reverse else group) * 8 + xcd).all()
+        head, item, back = _launch_units(lib, n_items, n_heads, CUS, kind, reverse)
+        assert not back
+        _assert_order(head, item, n_items, n_heads, _batch(n_items, n_heads, CUS, kind), reverse)
+
+
+@pytest.mark.parametrize("n_items,n_heads", [(2, 1536), (5, 600), (12, 48)])
+def test_a_step_of_items_that_are_alike_is_walked_head_by_head(lib, n_items, n_heads):
+    _assert_order(*_units(lib, n_items, n_heads, 1), n_items, n_heads, 1, False)
 
 
 @pytest.mark.parametrize("cus", [256, 304, 64])
@@ -115,10 +148,7 @@ def test_every_unit_of_a_launch_has_one_workgroup(lib, kind, cus):
         for n_heads in list(range(1, 42)) + [63, 64, 72, 100, 104, 160, 256, 288, 768, 1023]:
             for reverse in (0, 1):
                 n = n_items * n_heads
-                head, item = np.zeros(n, np.int32), np.zeros(n, np.int32)
-                p = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
-                lib.launch_units.restype = ctypes.c_uint
-                back = lib.launch_units(n_items, n_heads, cus, reverse, KINDS.index(kind), p(head), p(item)) >> 31
+                head, item, back = _launch_units(lib, n_items, n_heads, cus, kind, reverse)
                 assert np.array_equal(np.sort(head.astype(np.int64) * n_items + item), np.arange(n))
                 xcd, grouped = np.arange(n) % 8, head < n_heads // 8 * 8
                 assert (head[grouped] % 8 == xcd[grouped]).all()
@@ -133,18 +163,11 @@ def test_every_unit_of_a_launch_has_one_workgroup(lib, kind, cus):
 
 @pytest.mark.parametrize("kind", KINDS)
 def test_the_batch_that_ends_a_launch(lib, kind):
-    # groups that hold eight units for every compute unit of an XCD, half of them for lists of up to seven items and,
-    # where the batch would be the whole launch, up to fifteen in the backward; the whole launch where less than a unit per
-    # compute unit would be left ahead of it.  The forward under the block-causal mask: never half
     for cus in (256, 304):
         for n_items in (1, 3, 7, 8, 11, 15, 16, 20, 300):
             for n_heads in list(range(1, 60)) + list(range(60, 700, 13)) + [768, 1536]:
-                groups, full = n_heads // 8, max(1, cus // 8 * 8 // n_items)
-                half = kind != "causal fwd" and (n_items < 8 or (n_items < 16 and full >= groups and kind != "fwd"))
-                batch = min(groups, max(1, full // 2) if half else full)
-                if (groups - batch) * n_items < cus // 8:
-                    batch = groups
-                assert lib.batch_groups(n_items, n_heads, cus, KINDS.index(kind)) == batch, (n_items, n_heads, cus)
+                got = lib.batch_groups(n_items, n_heads, cus, KINDS.index(kind))
+                assert got == _batch(n_items, n_heads, cus, kind), (n_items, n_heads, cus)
 
 
 @pytest.mark.parametrize("tiles,tenths", [(1, 20), (7, 20), (25, 20), (32, 20), (33, 18), (64, 18)])
