@@ -440,8 +440,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(HMAR_D
 // item's chain of tiles (about 1 us a tile) and of the launch itself.  What puts the dK/dV kernel behind the dQ
 // kernel are the two row statistics; here every dK/dV item forms those of the rows it visits by itself, before its first
 // step (in the step ahead of their use they cost registers: spills, 0.7 us a tile).  Both work lists hold the same number of
-// items, heaviest first: the units of a head alternate between them.  32 heads of 680 tokens: 11.5 + 11.6 us in two
-// launches, 16.2 in one; 4 heads 11.1 + 11.1 -> 12.7.  Where the line lies: one_backward_launch (csrc/kernels.h).
+// items, heaviest first: the units of a head alternate between them.  32 heads of 680 tokens: 22.0 us in two
+// launches, 14.4 in one; 4 heads 20.9 -> 12.5.  Where the line lies: one_backward_launch (csrc/kernels.h).
 struct BwdBothParams {
     BwdParams p;                                    // items, row_lo, row_hi: of the dQ list; map: of both lists
     const Item* k_items; const int32_t* k_row_lo; const int32_t* k_row_hi;

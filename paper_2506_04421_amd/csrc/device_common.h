@@ -74,6 +74,9 @@ struct alignas(16) Item { int32_t own_begin, own_end, other_begin, other_end; };
 //   HMAR_TUNE_LONG_STREAM = tiles                 from which stream length on the forward leaves maxima out (csrc/kernels.h)
 //   HMAR_TUNE_TAIL_PERCENT / HMAR_TUNE_BOTH_FILL   size of the batch that ends a launch; up to which fill a backward is one
 //                                                 launch (csrc/kernels.h)
+//   HMAR_TUNE_TURN / _HALF_BATCH / _HEAD_BY_HEAD / _WHOLE_ROWS / _KEYS_AHEAD = 0   no launch deals second units backwards / ends on
+//                                                 half a batch / walks a step head by head / asks for whole rows / for
+//                                                 key operands ahead (csrc/kernels.h, csrc/fwd.hip)
 //   HMAR_NT_O / HMAR_NT_GRADS / HMAR_NT_ROW_LOADS = 0 | 1   cache policy of result stores and row loads (see below)
 //   HMAR_DKDV_PERSIST                             the dK/dV kernel of tuning/dkdv_persist.inc instead: two resident
 //                                                 workgroups per CU walk the (head, item) units, the next unit's

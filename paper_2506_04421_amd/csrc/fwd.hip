@@ -535,6 +535,9 @@ hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, floa
     return e;
 }
 
+#ifndef HMAR_TUNE_HEAD_BY_HEAD
+#define HMAR_TUNE_HEAD_BY_HEAD 1
+#endif
 template <int N>
 static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_scale, int num_cus, hipStream_t stream) {
     StepParams<N> p;
@@ -579,10 +582,10 @@ static hipError_t launch_fwd_steps_n(const StepLaunch& L, int n_heads, float sm_
     const unsigned groups = launch_groups(items, n_heads);
     if (groups == 0) return hipErrorInvalidValue;
     // The items of one step share all their keys: where they are alike (a last item of at least 64 rows) and fill the
-    // chip they are walked head by head, there is nothing to end the launch on.  256 queries, 425 keys: 1536 heads 70.8 ->
-    // 68.6 us, 768 39.6 -> 38.8, 600 34.8 -> 32.1 against the order of launch_map; but 139 rows, 269 keys, 424 heads 14.8 -> 16.8.
+    // chip they are walked head by head, there is nothing to end the launch on.  256 queries, 425 keys: 1536 heads 66.5 ->
+    // 64.2 us, 768 36.1 -> 34.3, 600 28.9 -> 28.2 against the order of launch_map; but 139 rows, 269 keys, 424 heads 14.8 -> 16.8.
     const int last_rows = (p.step[0].n_q + 127) % 128 + 1;
-    const bool alike = N == 1 && last_rows >= 64 && (long long)items * n_heads > 4LL * num_cus;
+    const bool alike = HMAR_TUNE_HEAD_BY_HEAD && N == 1 && last_rows >= 64 && (long long)items * n_heads > 4LL * num_cus;
     p.map = alike ? unit_map_for(items, n_heads, 1) : launch_map(num_cus, items, n_heads, kOrderFwd);
     profile_before(kKernelFwd, stream);
     // a launch holds fewer than 2^32 threads: more units than that are left to the pack item, one workgroup per head

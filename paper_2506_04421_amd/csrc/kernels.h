@@ -57,6 +57,20 @@ inline UnitMap unit_map_for(int n_items, int n_heads, int batch_groups, int turn
     return {n_items, 8 * (n_groups - tail) * n_items, 8 * (n_groups - tail), batch, 8 * tail, 8 * (n_groups - 1),
             inverse_of(n_items), inverse_of(batch), turned, n_items * n_heads};
 }
+// measurement builds: 0 takes the order, or the form, out of every launch
+#ifndef HMAR_TUNE_TURN
+#define HMAR_TUNE_TURN 1
+#endif
+#ifndef HMAR_TUNE_HALF_BATCH
+#define HMAR_TUNE_HALF_BATCH 1
+#endif
+#ifndef HMAR_TUNE_WHOLE_ROWS
+#define HMAR_TUNE_WHOLE_ROWS 1
+#endif
+#ifndef HMAR_TUNE_KEYS_AHEAD
+#define HMAR_TUNE_KEYS_AHEAD 1
+#endif
+
 // How a kind of launch orders its units (launch_map).
 struct Order {
     int turn_rounds;           // the second unit of every compute unit is dealt backwards up to so many units per compute unit
@@ -65,31 +79,33 @@ struct Order {
 };
 constexpr Order kOrderFwd = {6, 8, 8}, kOrderFwdCausal = {6, 0, 0}, kOrderDq = {6, 8, 16};
 constexpr Order kOrderDkDv = {2, 8, 16};       // and both lists in one launch
-// The map of a launch.  Three orders, each where it measured best (us; a compute unit holds four workgroups of the forward
-// and dQ, two of dK/dV):
-//  - Head by head with the batch at the end.  The batch is tail_groups_for() groups, half of it where an item list is
-//    short: a launch that is one batch starts with its heaviest items alone, in step, all waiting for memory and
-//    then all computing, and leaves the L2 no locality.  Full batch -> half:
-//      7 items (680 tokens)   forward / dK,dV / dQ: 256 heads 29.1 / 49.8 / 36.4 -> 28.9 / 44.6 / 34.5, 200 heads
-//                             24.7 / 39.8 / 30.3 -> 24.0 / 35.6 / 28.8, 320 heads 35.3 / 55.3 / 43.5 -> 34.5 / 54.6 / 41.3
-//      4 items (466 tokens)   320 heads, dK,dV: 37.6 -> 35.3
-//      8 to 15 items, launches that are one batch: forward +2 % (-8..+21 %), dK,dV -0.3 %, dQ -0.1 % (150 schedules)
-//      20 items (2240 tokens) 64 heads: 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5
-//      block-causal, 2 to 7 items, 4 to 24 units per compute unit, 126 schedules: backward -1.1 % (-10..+4 %), but forward
-//                             +0.1 % (-11..+6 %), whose items share a head's first keys: it keeps the full batch
-//  - Item by item altogether, where less than one unit per compute unit would be left ahead of the batch (160 heads of
-//    680 tokens, dK,dV: 32.2, with two groups ahead 34.2).
-//  - The same with the second unit of every compute unit dealt backwards, so that the heaviest first unit meets the lightest
-//    second one, in launches of at most `turn_rounds` units per compute unit.  dK,dV of 64 heads of 680 tokens 15.5 -> 14.7,
-//    of 21 of 2240 tokens 44.7 -> 41.0; both lists in one launch, 32 heads of 680 tokens 18.2 -> 16.1, 24 of 1485 54.3 -> 50.2;
-//    forward / dQ of 160 heads of 680 tokens 22.1 / 26.4 -> 21.5 / 25.4.  Beyond (dK,dV of 83 heads 18.6 -> 19.0) it does not pay.
+// The map of a launch.
+//  1. Head by head, with a batch of tail_groups_for() groups at the end that is walked item by item.
+//  2. The same with half that batch, for short lists.  A launch that is one batch starts with its heaviest items alone, in
+//     step, all waiting for memory and then all computing, and leaves the L2 no locality.
+//  3. Item by item altogether, where less than one unit per compute unit would be left ahead of the batch.
+//  4. Item by item with the second unit of every compute unit dealt backwards, in launches of at most `turn_rounds`
+//     units per compute unit: the heaviest first unit meets the lightest second one.
+// What they measured (profiles/launch_rules.txt; us, forward / backward, one card, unless it says otherwise; a compute unit
+// holds four workgroups of the forward and dQ, two of dK/dV):
+//   1 -> 2   7 items (680 tokens): 200 heads 20.6 / 61.0 -> 20.2 / 56.9, 256 heads 25.9 / 77.1 -> 25.8 / 73.5, 320 heads
+//            33.8 / 94.4 -> 30.9 / 88.8
+//            8 to 15 items, launches that are one batch, 150 schedules: forward +2 % (-8..+21 %), dK,dV -0.3 %, dQ -0.1 %
+//            20 items (2240 tokens), 64 heads, another card: forward / dK,dV / dQ 52.8 / 91.5 / 69.4 -> 55.2 / 93.4 / 70.5
+//            block-causal, 2 to 7 items, 4 to 24 units per compute unit, 126 schedules: backward -1.1 % (-10..+4 %), but
+//            forward +0.1 % (-11..+6 %), whose items share a head's first keys: it keeps the full batch
+//   2 -> 3   160 heads of 680 tokens, dK,dV, another card: two groups ahead of the batch 34.2, none 32.2
+//   3 -> 4   680 tokens: 32 heads, both lists in one launch, 16.3 -> 14.4; 64 heads, backward, 25.6 -> 24.5; 160 heads 18.3 / 49.8
+//            -> 17.8 / 49.0; 21 heads of 2240 tokens, backward, 69.8 -> 65.7.  140 schedules, 2 to 3.5 units per compute unit:
+//            forward -1.4 % (-17..+9 %); 196 of 3.5 to 6: -0.2 % (-8..+2 %).  Beyond that many for each kernel (dK,dV of 83
+//            heads of 680 tokens, another card, 18.6 -> 19.0) it does not pay
 inline UnitMap launch_map(int num_cus, int n_items, int n_heads, const Order& order) {
     const int cus = num_cus / 8, n_groups = n_heads / 8;                    // of an XCD; heads of an XCD
     int tail = tail_groups_for(num_cus, n_items);
-    if (n_items < order.half_below || (n_items < order.half_whole_below && tail >= n_groups)) tail = std::max(1, tail / 2);
+    if (HMAR_TUNE_HALF_BATCH && (n_items < order.half_below || (n_items < order.half_whole_below && tail >= n_groups))) tail = std::max(1, tail / 2);
     if ((long long)(n_groups - tail) * n_items >= cus) return unit_map_for(n_items, n_heads, tail);
     const long long units = (long long)n_items * n_heads;
-    const bool turned = units > num_cus && units <= 8LL * order.turn_rounds * cus;
+    const bool turned = HMAR_TUNE_TURN && units > num_cus && units <= 8LL * order.turn_rounds * cus;
     return unit_map_for(n_items, n_heads, std::max(1, n_groups), turned ? cus : 0);
 }
 
@@ -125,7 +141,7 @@ inline bool leaves_maxima_out(int max_tiles, long long total_tiles, int n_heads,
 //   beyond 2:  0.96 and 1.00 (0.91..1.04): no difference on short streams
 inline bool keys_ahead(int max_tiles, int long_items, int n_heads, int num_cus) {
     const long long units = (long long)long_items * n_heads;
-    return units <= num_cus || (max_tiles < HMAR_TUNE_LONG_STREAM && units > 2LL * num_cus);
+    return HMAR_TUNE_KEYS_AHEAD && (units <= num_cus || (max_tiles < HMAR_TUNE_LONG_STREAM && units > 2LL * num_cus));
 }
 
 // Whether the wavefronts of a launch ask for their own rows as whole rows and turn them round (request_rows in
@@ -145,9 +161,13 @@ inline bool keys_ahead(int max_tiles, int long_items, int n_heads, int num_cus) 
 //   16 to 35       0.99 (0.98..1.01)  1.00 (0.99..1.01)  1.01 (0.99..1.02)  1.01 (0.99..1.03)  1.00 (0.99..1.02)
 //   36 to 64       1.00 (0.99..1.01)  1.01 (1.00..1.01)  1.01 (1.00..1.02)  1.02 (1.00..1.03)  1.01 (1.00..1.02)
 constexpr int kShortStream = 16;
-inline bool whole_rows_fwd(long long units, int num_cus) { return units <= 3LL * num_cus; }
-inline bool whole_rows_dq(long long units, int max_tiles, int num_cus) { return units <= 3LL * num_cus || max_tiles < kShortStream; }
-inline bool whole_rows_dkdv(long long units, int max_tiles, int num_cus) { return units <= 2LL * num_cus || max_tiles < kShortStream; }
+inline bool whole_rows_fwd(long long units, int num_cus) { return HMAR_TUNE_WHOLE_ROWS && units <= 3LL * num_cus; }
+inline bool whole_rows_dq(long long units, int max_tiles, int num_cus) {
+    return HMAR_TUNE_WHOLE_ROWS && (units <= 3LL * num_cus || max_tiles < kShortStream);
+}
+inline bool whole_rows_dkdv(long long units, int max_tiles, int num_cus) {
+    return HMAR_TUNE_WHOLE_ROWS && (units <= 2LL * num_cus || max_tiles < kShortStream);
+}
 
 // Whether a backward is one launch of both kernels' items (hmar_bwd_both_kernel; no bits depend on it): work for at
 // most two of the longest items on every compute unit, 9/5 of them where streams are long, and windows whose statistics

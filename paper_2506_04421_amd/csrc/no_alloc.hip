@@ -1,7 +1,8 @@
 // hmar_attn_bwd_noalloc: the backward for callers that cannot allocate device memory.
 //
 // Everything the backward keeps on the device besides the caller's tensors -- the two fp32
-// [B,H,L] row statistics its two kernels exchange and the tile schedule tables -- lives in one
+// [B,H,L] row statistics its two kernels exchange (a small backward, one launch, needs none) and the tile
+// schedule tables -- lives in one
 // fixed array of the library's device image.  Each GPU holds its own copy of that array at its
 // own address; the address is looked up once per device with hipGetSymbolAddress while that
 // device is current.  The tables reach the array through kernel arguments (a small writer
@@ -119,8 +120,8 @@ extern "C" hmar_status hmar_attn_bwd_noalloc(const void* Q, const void* K, const
         }
         ds = state.dev;
     }
-    // The statistics need no clearing: the dQ kernel writes every row before the dK/dV kernel,
-    // queued behind it on the same stream, reads it.
+    // The statistics need no clearing: where they are used, the dQ kernel writes every row before the dK/dV
+    // kernel, queued behind it on the same stream, reads it.  (A backward in one launch forms them itself.)
     const hipError_t e = hmar::launch_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, reinterpret_cast<float*>(base), ds,
                                           pb.n_heads, hmar::resolve_scale(sm_scale, D), s);
     return e == hipSuccess ? HMAR_OK : HMAR_ERR_HIP;

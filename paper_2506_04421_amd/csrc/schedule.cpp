@@ -78,7 +78,8 @@ bool build_schedule(const int32_t* sides, int32_t num_scales, bool sizes_are_cou
             it.other_begin = lo;
             it.other_end = hi;
         }
-        // heaviest items first: the light ones fill the tail of the launch
+        // heaviest items first (rows times window: a chunk of few rows comes late, also where its window, and with it its
+        // chain of tiles, is the longest): the light ones fill the tail of the launch
         std::stable_sort(s.items[dir].begin(), s.items[dir].end(), [](const TileItem& a, const TileItem& b) {
             const int64_t ca = (int64_t)(a.own_end - a.own_begin) * (a.other_end - a.other_begin);
             const int64_t cb = (int64_t)(b.own_end - b.own_begin) * (b.other_end - b.other_begin);

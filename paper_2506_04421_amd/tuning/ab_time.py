@@ -4,6 +4,8 @@
   python -m paper_2506_04421_amd.build --variant occ2 -DHMAR_TUNE_LDS_PAD_FWD=32768
   python -m paper_2506_04421_amd.tuning.ab_time 256px_b32_h24 main occ2
 
+The workload is a name of synth_inputs.WORKLOADS, SIDES/HEADS[/causal] (1,2,3,4,5,6,8,10,13,16/64), or one inference
+step N_PREV,N_CUR/HEADS/step (169,256/1536/step; then there is no backward).
 `main` is libhmar_attn.so, any other name libhmar_attn_<name>.so (see build.py).  Every build
 runs forward and backward on the same three rotating buffer sets (larger than the last-level
 cache), in rounds that alternate between the builds so that clock and temperature drift hit all
@@ -33,20 +35,29 @@ def _load(name: str) -> ctypes.CDLL:
     vp, i32, f32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float, ctypes.c_size_t
     pi32 = ctypes.POINTER(i32)
     lib = ctypes.CDLL(LIB_PATH if name == "main" else variant_path(name))
-    lib.hmar_attn_fwd.restype = ctypes.c_int
-    lib.hmar_attn_fwd.argtypes = [vp, vp, vp, vp, vp, pi32, i32, i32, i32, i32, f32, vp]
-    lib.hmar_attn_bwd.restype = ctypes.c_int
-    lib.hmar_attn_bwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, pi32, i32, i32, i32, i32, f32, vp, sz, vp]
-    lib.hmar_attn_bwd_workspace_bytes.restype = sz
-    lib.hmar_attn_bwd_workspace_bytes.argtypes = [pi32, i32, i32, i32, i32]
+    lib.hmar_attn_fwd_masked.argtypes = [vp, vp, vp, vp, vp, pi32, i32, i32, i32, i32, i32, f32, vp]
+    lib.hmar_attn_bwd_masked.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, pi32, i32, i32, i32, i32, i32, f32, vp, sz, vp]
+    lib.hmar_attn_step_fwd.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, f32, vp]
     return lib
+
+
+def _workload(spec: str):
+    """(workload, mask kind, n_prev of a step or None)"""
+    if spec in si.WORKLOADS:
+        return si.WORKLOADS[spec], 0, None
+    sizes, heads, *kind = spec.split("/")
+    sizes = tuple(int(x) for x in sizes.split(","))
+    if kind == ["step"]:
+        return si.Workload(spec, sizes, 1, int(heads), 64, 0), 0, sizes[0]
+    return si.Workload(spec, sizes, 1, int(heads), 64, 0), int(kind == ["causal"]), None
 
 
 def main() -> int:
     if len(sys.argv) < 3:
         print(__doc__)
         return 2
-    w = si.WORKLOADS[sys.argv[1]]
+    w, kind, n_prev = _workload(sys.argv[1])
+    rows, keys = (w.L, w.L) if n_prev is None else (w.sides[1], sum(w.sides))
     names = sys.argv[2:]
     libs = {n: _load(n) for n in names}
     dev = torch.device("cuda:0")
@@ -55,24 +66,29 @@ def main() -> int:
     g.manual_seed(1)
     sets = []
     for _ in range(3):
-        q, k, v, do = (torch.randn((w.B, w.H, w.L, w.D), device=dev, generator=g).to(torch.bfloat16) for _ in range(4))
-        sets.append([q, k, v, do, torch.empty_like(q), torch.empty((w.B, w.H, w.L), device=dev, dtype=torch.float32),
+        q, k, v, do = (torch.randn((w.B, w.H, n, w.D), device=dev, generator=g).to(torch.bfloat16) for n in (rows, keys, keys, rows))
+        sets.append([q, k, v, do, torch.empty_like(q), torch.empty((w.B, w.H, rows), device=dev, dtype=torch.float32),
                      torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)])
-    need = max(int(lib.hmar_attn_bwd_workspace_bytes(sides, len(w.sides), w.B, w.H, w.D)) for lib in libs.values())
+    need = 8 * w.B * w.H * rows
     ws = torch.empty(need, dtype=torch.uint8, device=dev)
     stream = torch.cuda.current_stream().cuda_stream
 
     def fwd(lib, s):
         q, k, v, do, O, LSE, dq, dk, dv = s
-        rc = lib.hmar_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), O.data_ptr(), LSE.data_ptr(), sides,
-                               len(w.sides), w.B, w.H, w.D, 0.0, stream)
+        ptrs = [t.data_ptr() for t in (q, k, v, O, LSE)]
+        if n_prev is None:
+            rc = lib.hmar_attn_fwd_masked(*ptrs, sides, len(w.sides), kind, w.B, w.H, w.D, 0.0, stream)
+        else:
+            rc = lib.hmar_attn_step_fwd(*ptrs, n_prev, rows, w.B, w.H, w.D, 0.0, stream)
         assert rc == 0, rc
 
     def bwd(lib, s):
+        if n_prev is not None:
+            return
         q, k, v, do, O, LSE, dq, dk, dv = s
-        rc = lib.hmar_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), O.data_ptr(), do.data_ptr(), LSE.data_ptr(),
-                               dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), sides, len(w.sides), w.B, w.H, w.D, 0.0,
-                               ws.data_ptr(), need, stream)
+        rc = lib.hmar_attn_bwd_masked(q.data_ptr(), k.data_ptr(), v.data_ptr(), O.data_ptr(), do.data_ptr(), LSE.data_ptr(),
+                                      dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), sides, len(w.sides), kind, w.B, w.H, w.D, 0.0,
+                                      ws.data_ptr(), need, stream)
         assert rc == 0, rc
 
     ref = None
@@ -84,7 +100,7 @@ def main() -> int:
         fwd(lib, s)
         bwd(lib, s)
         torch.cuda.synchronize()
-        outs = [t.float().clone() for t in s[4:]]
+        outs = [t.float().clone() for t in (s[4:] if n_prev is None else s[4:6])]
         if ref is None:
             ref = outs
         else:
@@ -105,11 +121,19 @@ def main() -> int:
         fwd(lib, s)
         bwd(lib, s)
 
-    rounds, inner = 12, 9
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    for s in sets:
+        step(libs[names[0]], s)
+    e1.record()
+    torch.cuda.synchronize()
+    rounds, inner = 12, 3 * max(3, min(20, int(1 / e0.elapsed_time(e1))))      # more calls of a short step
     res = {n: {"fwd": [], "bwd": [], "step": []} for n in names}
     for _ in range(rounds):
         for n in names:
             for what, fn in (("fwd", fwd), ("bwd", bwd), ("step", step)):
+                for s in sets:                          # the build before this one leaves other rows in the caches
+                    fn(libs[n], s)
                 e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
                 e0.record()
                 for i in range(inner):
@@ -124,6 +148,9 @@ def main() -> int:
         f = statistics.median(res[n]["fwd"])
         b = statistics.median(res[n]["bwd"])
         st = statistics.median(res[n]["step"])
+        if n_prev is not None:
+            print(f"{w.name} {n:14s} {f:7.1f} us ({(f / f0 - 1) * 100:+5.1f} %)", flush=True)
+            continue
         print(f"{w.name} {n:14s} fwd {f:7.1f} us ({(f / f0 - 1) * 100:+5.1f} %)  bwd {b:7.1f} us "
               f"({(b / b0 - 1) * 100:+5.1f} %)  fwd+bwd {st:7.1f} us ({(st / s0 - 1) * 100:+5.1f} %)", flush=True)
     return 0
