@@ -101,8 +101,8 @@ bool to_sizes(PyObject* address, PyObject* count, PyObject* L, Sizes* out) {
     return out->array != nullptr;
 }
 
-// A new tensor: at::empty, without its way through the dispatcher (0.3 us of a call's 5 each) where nothing waits on
-// that way.  What can wait there:
+// New tensors: at::empty, without its way through the dispatcher (0.3 us of a call's 5 each) where nothing waits on
+// that way; looked up once a call (0.05 us).  What can wait there:
 //  - dispatch keys beyond the ones every thread has (function transforms, dispatch modes and the like add theirs);
 //  - observers of operators (the profiler);
 //  - the fill that torch.use_deterministic_algorithms asks of new memory (torch.utils.deterministic's
@@ -111,8 +111,8 @@ bool nothing_waits() {
     return (c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() && !at::hasCallbacks() &&
            !(at::globalContext().deterministicAlgorithms() && at::globalContext().deterministicFillUninitializedMemory());
 }
-at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& q) {
-    if (!nothing_waits()) return at::empty(shape, q.options().dtype(type));
+at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& q, bool direct) {
+    if (!direct) return at::empty(shape, q.options().dtype(type));
 #ifdef HMAR_LAUNCH_HOST
     return at::Tensor(at::detail::empty_cpu(shape, type));
 #else
@@ -120,10 +120,10 @@ at::Tensor fresh(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& q
 #endif
 }
 
-// an output tensor the caller gave (checked), or a new one
-bool output(PyObject* given, at::ScalarType type, at::IntArrayRef shape, const at::Tensor& q, at::Tensor* out) {
+// an output tensor the caller gave (checked), or a new one (direct: nothing_waits())
+bool output(PyObject* given, at::ScalarType type, at::IntArrayRef shape, const at::Tensor& q, bool direct, at::Tensor* out) {
     if (given == Py_None) {
-        *out = fresh(shape, type, q);
+        *out = fresh(shape, type, q, direct);
         return has_memory(*out);
     }
     const at::Tensor* t = checked(given, type, shape, q.device());
@@ -202,9 +202,10 @@ PyObject* fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (!q || q->size(2) != s.L || !ready(*q)) Py_RETURN_NONE;
         const at::Tensor* k = checked(a[1], at::kBFloat16, q->sizes(), q->device());
         const at::Tensor* v = checked(a[2], at::kBFloat16, q->sizes(), q->device());
+        const bool direct = nothing_waits();
         at::Tensor o, lse;
-        if (!k || !v || !output(a[3], at::kBFloat16, q->sizes(), *q, &o) ||
-            !output(a[4], at::kFloat, q->sizes().slice(0, 3), *q, &lse))
+        if (!k || !v || !output(a[3], at::kBFloat16, q->sizes(), *q, direct, &o) ||
+            !output(a[4], at::kFloat, q->sizes().slice(0, 3), *q, direct, &lse))
             Py_RETURN_NONE;
         void* stream = stream_of(*q);
         const void *Q = q->data_ptr(), *K = k->data_ptr(), *V = v->data_ptr();
@@ -230,13 +231,14 @@ PyObject* bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (!(in[i] = checked(a[1 + i], at::kBFloat16, q->sizes(), q->device()))) Py_RETURN_NONE;
         const at::Tensor* lse = checked(a[5], at::kFloat, q->sizes().slice(0, 3), q->device());
         if (!lse) Py_RETURN_NONE;
+        const bool direct = nothing_waits();
         at::Tensor out[3], ws;
         for (int i = 0; i < 3; ++i)
-            if (!output(a[6 + i], at::kBFloat16, q->sizes(), *q, &out[i])) Py_RETURN_NONE;
+            if (!output(a[6 + i], at::kBFloat16, q->sizes(), *q, direct, &out[i])) Py_RETURN_NONE;
         const int32_t B = (int32_t)q->size(0), H = (int32_t)q->size(1), D = (int32_t)q->size(3);
         if (a[9] == Py_None) {
             const int64_t need = (int64_t)g_ws_bytes(s.array, s.count, (int32_t)kind, B, H, D);
-            ws = fresh({need < 16 ? 16 : need}, at::kByte, *q);
+            ws = fresh({need < 16 ? 16 : need}, at::kByte, *q, direct);
             if (!has_memory(ws)) Py_RETURN_NONE;
         } else {
             const at::Tensor* t = plain(a[9]);
@@ -283,14 +285,14 @@ PyObject* bwd_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // The tensors of one inference step; false if a check fails.
 struct Step { at::Tensor q, k, v, o, lse; int64_t n_prev; };       // owners: lists can change while the GIL is free
-bool to_step(PyObject* Q, PyObject* K, PyObject* V, PyObject* n_prev, PyObject* O, PyObject* LSE, Step* s) {
+bool to_step(PyObject* Q, PyObject* K, PyObject* V, PyObject* n_prev, PyObject* O, PyObject* LSE, bool direct, Step* s) {
     const at::Tensor* q = checked_q(Q);
     if (!q || !to_int(n_prev, &s->n_prev)) return false;
     const int64_t kv[4] = {q->size(0), q->size(1), s->n_prev + q->size(2), q->size(3)};
     const at::Tensor* k = checked(K, at::kBFloat16, kv, q->device());
     const at::Tensor* v = checked(V, at::kBFloat16, kv, q->device());
-    if (!k || !v || !output(O, at::kBFloat16, q->sizes(), *q, &s->o) ||
-        !output(LSE, at::kFloat, q->sizes().slice(0, 3), *q, &s->lse))
+    if (!k || !v || !output(O, at::kBFloat16, q->sizes(), *q, direct, &s->o) ||
+        !output(LSE, at::kFloat, q->sizes().slice(0, 3), *q, direct, &s->lse))
         return false;
     s->q = *q;
     s->k = *k;
@@ -304,7 +306,7 @@ PyObject* step(PyObject*, PyObject* const* a, Py_ssize_t n) {
         Step s; float scale;
         if (n != 7 || !g_steps || !to_scale(a[6], &scale)) Py_RETURN_NONE;
         const at::Tensor* q = checked_q(a[0]);
-        if (!q || !ready(*q) || !to_step(a[0], a[1], a[2], a[3], a[4], a[5], &s)) Py_RETURN_NONE;
+        if (!q || !ready(*q) || !to_step(a[0], a[1], a[2], a[3], a[4], a[5], nothing_waits(), &s)) Py_RETURN_NONE;
         void* stream = stream_of(*q);
         const void *Q = q->data_ptr(), *K = s.k.data_ptr(), *V = s.v.data_ptr();
         void* O = s.o.data_ptr();
@@ -324,7 +326,7 @@ PyObject* rows(PyObject*, PyObject* const* a, Py_ssize_t n) {
         Step s; float scale;
         if (n != 8 || !g_rows || !to_scale(a[7], &scale)) Py_RETURN_NONE;
         const at::Tensor* q = checked_q(a[0]);
-        if (!q || !ready(*q) || !to_step(a[0], a[1], a[2], a[3], a[5], a[6], &s)) Py_RETURN_NONE;
+        if (!q || !ready(*q) || !to_step(a[0], a[1], a[2], a[3], a[5], a[6], nothing_waits(), &s)) Py_RETURN_NONE;
         const at::Tensor* r = plain(a[4]);
         if (!r || r->device() != q->device() || r->scalar_type() != at::kInt || r->dim() != 1 || !r->is_contiguous() ||
             r->numel() < 1 || r->numel() > q->size(2))
@@ -362,10 +364,11 @@ PyObject* steps(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor* first = checked_q(PySequence_Fast_GET_ITEM(a[0], 0));
         if (!first || !ready(*first)) Py_RETURN_NONE;
         const at::Tensor q0 = *first;
+        const bool direct = nothing_waits();
         for (Py_ssize_t i = 0; i < count; ++i) {
             auto item = [&](int k) { return a[k] == Py_None ? Py_None : PySequence_Fast_GET_ITEM(a[k], i); };
             Step& x = s[(size_t)i];
-            if (!to_step(item(0), item(1), item(2), item(3), item(4), item(5), &x)) Py_RETURN_NONE;
+            if (!to_step(item(0), item(1), item(2), item(3), item(4), item(5), direct, &x)) Py_RETURN_NONE;
             if (x.q.size(0) != q0.size(0) || x.q.size(1) != q0.size(1) || x.q.size(3) != q0.size(3) ||
                 x.q.device() != q0.device())
                 Py_RETURN_NONE;
