@@ -107,6 +107,7 @@ bool to_sizes(PyObject* address, PyObject* count, PyObject* L, Sizes* out) {
 //  - observers of operators (the profiler);
 //  - the fill that torch.use_deterministic_algorithms asks of new memory (torch.utils.deterministic's
 //    fill_uninitialized_memory), which is part of the operator: a row list leaves rows unwritten.
+// (A kernel that a program registers in place of aten::empty's own is not looked for.)
 bool nothing_waits() {
     return (c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() && !at::hasCallbacks() &&
            !(at::globalContext().deterministicAlgorithms() && at::globalContext().deterministicFillUninitializedMemory());
